@@ -19,35 +19,10 @@
 // slabs and writes its partial Y once; the Lanczos pass sums the blocks'
 // partials in block order.  All products and sums are FP64, in a fixed order.
 #include "tnslq_internal.h"
+#include "wave.h"
 
 namespace tnslq {
 namespace {
-
-// v plus its DPP-moved copy (both 32-bit halves moved alike); lanes of rows
-// outside ROWS add 0
-template <int CTRL, int ROWS>
-__device__ inline double dpp_add(double v) {
-    const long long b = __double_as_longlong(v);
-    const int lo = __builtin_amdgcn_update_dpp(0, (int)b, CTRL, ROWS, 0xf, false);
-    const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, ROWS, 0xf, false);
-    return v + __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
-}
-
-// The sum over the wave's 64 lanes, returned to every lane: pairs, quads,
-// half rows and rows of 16 by lane permutations within a row, then rows 0-1
-// into row 1 and rows 0-3 into row 3 by row broadcasts; lane 63 holds the
-// total.  A fixed order, done in registers.
-__device__ inline double wave_total(double v) {
-    v = dpp_add<0xB1, 0xf>(v);    // quad_perm [1, 0, 3, 2]
-    v = dpp_add<0x4E, 0xf>(v);    // quad_perm [2, 3, 0, 1]
-    v = dpp_add<0x141, 0xf>(v);   // row_half_mirror
-    v = dpp_add<0x140, 0xf>(v);   // row_mirror
-    v = dpp_add<0x142, 0xa>(v);   // row_bcast:15 into rows 1 and 3
-    v = dpp_add<0x143, 0xc>(v);   // row_bcast:31 into rows 2 and 3
-    const long long b = __double_as_longlong(v);
-    const int lo = __builtin_amdgcn_readlane((int)b, 63), hi = __builtin_amdgcn_readlane((int)(b >> 32), 63);
-    return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
-}
 
 // DB = d_B, KP = probes, FT = threads per block, RPT = rows of each slab per
 // thread (d_A = FT RPT), P = slabs in the ring of registers.

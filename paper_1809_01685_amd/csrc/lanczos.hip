@@ -8,6 +8,7 @@
 #include <float.h>
 
 #include "tnslq_internal.h"
+#include "wave.h"
 
 namespace tnslq {
 namespace {
@@ -40,14 +41,37 @@ __device__ inline double sum_partials(const double *p, int cnt, double *sh) {
 
 // Step (1-based) at which the probe broke down among steps 1..jmax, or 0.
 // Breakdown at step s: beta_{s+1} <= tol * (max_{i<=s} |alpha_i| + max_{2<=i<=s} beta_i).
-__device__ inline int first_break(const double *alpha_k, const double *beta_k, int jmax) {
-    double amax = 0.0, bmax = 0.0;
-    for (int s = 1; s <= jmax; ++s) {
-        amax = fmax(amax, fabs(alpha_k[s - 1]));
-        if (s >= 2) bmax = fmax(bmax, beta_k[s - 1]);
-        if (beta_k[s] <= BREAKDOWN_TOL * (amax + bmax)) return s;
+// Called by whole waves: lane i tests step i + 1 against running maxima taken
+// by a scan over the lanes (one thread walking the steps waited for memory at
+// each one, 5 us in each pass at step 40).  amax and bmax: the maxima over
+// all jmax steps.
+__device__ inline int first_break(const double *alpha_k, const double *beta_k, int jmax, double &amax, double &bmax) {
+    const int lane = threadIdx.x & 63;
+    amax = bmax = 0.0;
+    for (int s0 = 0; s0 < jmax; s0 += 64) {
+        const int s = s0 + lane + 1;
+        const bool in = s <= jmax;
+        double a = in ? fabs(alpha_k[s - 1]) : 0.0, b = in && s >= 2 ? beta_k[s - 1] : 0.0;
+        const double next = in ? beta_k[s] : INFINITY;
+        a = fmax(a, amax);
+        b = fmax(b, bmax);
+        for (int o = 1; o < 64; o <<= 1) {
+            const double ua = __shfl_up(a, o, 64), ub = __shfl_up(b, o, 64);
+            if (lane >= o) {
+                a = fmax(a, ua);
+                b = fmax(b, ub);
+            }
+        }
+        const unsigned long long hit = __ballot(in && next <= BREAKDOWN_TOL * (a + b));
+        if (hit) return s0 + __builtin_ctzll(hit) + 1;
+        amax = lane_value(a, 63);
+        bmax = lane_value(b, 63);
     }
     return 0;
+}
+__device__ inline int first_break(const double *alpha_k, const double *beta_k, int jmax) {
+    double amax, bmax;
+    return first_break(alpha_k, beta_k, jmax, amax, bmax);
 }
 
 __device__ inline void elem_range(int64_t n, int nblk, int64_t &beg, int64_t &end) {
@@ -206,18 +230,13 @@ __global__ void __launch_bounds__(256) k_passC(const double *__restrict__ nrmpar
     const int k = blockIdx.y;
     const double *ak = alpha + (int64_t)k * m;
     double *bk = beta + (int64_t)k * (m + 1);
-    const bool live = first_break(ak, bk, j - 1) == 0;
+    double amax, bmax;
+    const bool live = first_break(ak, bk, j - 1, amax, bmax) == 0;
     double b = sqrt(sum_partials(nrmpart + (int64_t)k * nblk, nblk, sh));
     if (!live) b = 0.0;
-    bool cont = live;
-    if (live) {
-        double amax = 0.0, bmax = 0.0;
-        for (int s = 1; s <= j; ++s) {
-            amax = fmax(amax, fabs(ak[s - 1]));
-            if (s >= 2) bmax = fmax(bmax, bk[s - 1]);
-        }
-        if (b <= BREAKDOWN_TOL * (amax + bmax)) cont = false;
-    }
+    amax = fmax(amax, fabs(ak[j - 1]));
+    if (j >= 2) bmax = fmax(bmax, bk[j - 1]);
+    const bool cont = live && !(b <= BREAKDOWN_TOL * (amax + bmax));
     const int64_t base = (int64_t)k * n;
     const int64_t gstride = (int64_t)gridDim.x * blockDim.x;
     for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += gstride) {
@@ -236,65 +255,102 @@ __global__ void __launch_bounds__(256) k_passC(const double *__restrict__ nrmpar
     if (blockIdx.x == 0 && threadIdx.x == 0) bk[j] = b;
 }
 
-__global__ void k_steps(const double *__restrict__ alpha, const double *__restrict__ beta, int K, int m,
-                        int jdone, int *__restrict__ steps) {
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= K) return;
+__global__ void __launch_bounds__(64) k_steps(const double *__restrict__ alpha, const double *__restrict__ beta, int m,
+                                              int jdone, int *__restrict__ steps) {
+    const int k = blockIdx.x;
     const int s = first_break(alpha + (int64_t)k * m, beta + (int64_t)k * (m + 1), jdone);
-    steps[k] = s ? s : jdone;
+    if (threadIdx.x == 0) steps[k] = s ? s : jdone;
 }
 
 // Eigenvalues and first eigenvector components of the symmetric tridiagonal
 // (d, e) by implicit QL with Wilkinson-type shifts (Bowdler, Martin, Reinsch
 // & Wilkinson 1968), accumulating only the first row of the eigenvector
-// matrix.  e[i] couples d[i] and d[i+1]; e[n-1] must be 0.  On return d holds
-// the eigenvalues and z the first components.  Entry i of each array sits at
-// index i * ST (the arrays of several threads interleaved in LDS).
-template <int ST>
-__device__ void tridiag_ql_first_row(int n, double *d_, double *e_, double *z_) {
-    auto d = [&](int i) -> double & { return d_[i * ST]; };
-    auto e = [&](int i) -> double & { return e_[i * ST]; };
-    auto z = [&](int i) -> double & { return z_[i * ST]; };
-    for (int i = 0; i < n; ++i) z(i) = (i == 0) ? 1.0 : 0.0;
+// matrix, by one wave: entry i lives in lane i % 64 of register i / 64.  e[i]
+// couples d[i] and d[i+1]; e[n-1] must be 0.  On return d holds the
+// eigenvalues and z the first components.  The rotations are one serial
+// chain, so the wave carries its state (g, s, c, p and the entries i + 1 of d
+// and z) uniformly, reads entry i by a lane read and writes entry i + 1 by a
+// lane select; the search for a negligible e is one ballot.  Magnitudes must
+// be scaled to about 1 (the squares of a rotation are taken as they are).
+template <int R>
+struct LaneVec {
+    double v[R];
+    __device__ inline double get(int i) const {
+        if constexpr (R == 1) return lane_value(v[0], i);
+        return i < 64 ? lane_value(v[0], i) : lane_value(v[R - 1], i - 64);
+    }
+    __device__ inline void set(int lane, int i, double x) {
+#pragma unroll
+        for (int r = 0; r < R; ++r) v[r] = lane + 64 * r == i ? x : v[r];
+    }
+};
+
+// 1 / sqrt(x) for a normal x: the hardware's estimate and one third-order step
+__device__ inline double rsqrt_step(double x) {
+    const double y = __builtin_amdgcn_rsq(x), h = fma(-x * y, y, 1.0);
+    return fma(y * h, fma(0.375, h, 0.5), y);
+}
+
+template <int R>
+__device__ void tridiag_ql_first_row(int n, int lane, LaneVec<R> &d, LaneVec<R> &e, LaneVec<R> &z) {
+    constexpr double R2_MIN = 1e-280;   // a rotation of smaller squares is one of zeros
+#pragma unroll
+    for (int r = 0; r < R; ++r) z.v[r] = lane + 64 * r == 0 ? 1.0 : 0.0;
     for (int l = 0; l < n; ++l) {
         int iter = 0;
         while (true) {
-            int mm = l;
-            for (; mm < n - 1; ++mm) {
-                const double dd = fabs(d(mm)) + fabs(d(mm + 1));
-                if (fabs(e(mm)) <= DBL_EPSILON * dd) break;
+            // the first negligible e[mm], l <= mm < n - 1 (else mm = n - 1)
+            int mm = n - 1;
+#pragma unroll
+            for (int r = R - 1; r >= 0; --r) {
+                double up = __shfl_down(d.v[r], 1, 64);
+                if (r + 1 < R) up = lane == 63 ? lane_value(d.v[R - 1], 0) : up;
+                const int i = lane + 64 * r;
+                const bool neg = i >= l && i < n - 1 && fabs(e.v[r]) <= DBL_EPSILON * (fabs(d.v[r]) + fabs(up));
+                const unsigned long long b = __ballot(neg);
+                if (b) mm = 64 * r + __builtin_ctzll(b);
             }
             if (mm == l || ++iter > 64) break;
-            double g = (d(l + 1) - d(l)) / (2.0 * e(l));
-            double r = hypot(g, 1.0);
-            g = d(mm) - d(l) + e(l) / (g + copysign(r, g));
+            const double dl = d.get(l), el = e.get(l);
+            double dn = d.get(mm), zn = z.get(mm);   // entries i + 1
+            double g = (d.get(l + 1) - dl) / (2.0 * el);
+            g = dn - dl + el / (g + copysign(sqrt(fma(g, g, 1.0)), g));
             double s = 1.0, c = 1.0, p = 0.0;
             bool early = false;
-            for (int i = mm - 1; i >= l; --i) {
-                const double f = s * e(i), bb = c * e(i);
-                r = hypot(f, g);
-                e(i + 1) = r;
-                if (r == 0.0) {
-                    d(i + 1) -= p;
-                    e(mm) = 0.0;
+            int i = mm - 1;
+            for (; i >= l; --i) {
+                const double ei = e.get(i), di = d.get(i), zi = z.get(i);
+                const double f = s * ei, bb = c * ei, r2 = fma(f, f, g * g);
+                if (r2 < R2_MIN) {
                     early = true;
                     break;
                 }
-                s = f / r;
-                c = g / r;
-                g = d(i + 1) - p;
-                r = (d(i) - g) * s + 2.0 * c * bb;
-                p = s * r;
-                d(i + 1) = g + p;
-                g = c * r - bb;
-                const double fz = z(i + 1);
-                z(i + 1) = s * z(i) + c * fz;
-                z(i) = c * z(i) - s * fz;
+                const double y = rsqrt_step(r2);
+                double r = r2 * y;
+                r = fma(0.5 * y, fma(-r, r, r2), r);
+                e.set(lane, i + 1, r);
+                s = f * y;
+                c = g * y;
+                g = dn - p;
+                const double t = fma(di - g, s, 2.0 * c * bb);
+                p = s * t;
+                d.set(lane, i + 1, g + p);
+                g = fma(c, t, -bb);
+                z.set(lane, i + 1, fma(s, zi, c * zn));
+                zn = fma(c, zi, -s * zn);
+                dn = di;
             }
-            if (early) continue;
-            d(l) -= p;
-            e(l) = g;
-            e(mm) = 0.0;
+            if (early) {
+                d.set(lane, i + 1, dn - p);
+                z.set(lane, i + 1, zn);
+                e.set(lane, i + 1, 0.0);
+                e.set(lane, mm, 0.0);
+                continue;
+            }
+            d.set(lane, l, dn - p);
+            z.set(lane, l, zn);
+            e.set(lane, l, g);
+            e.set(lane, mm, 0.0);
         }
     }
 }
@@ -308,33 +364,60 @@ __device__ inline double quad_f(int fn, double x) {
     return fabs(x);
 }
 
-// One thread per (probe, step); the threads of a block keep their d, e, z in
-// LDS, entry i of thread t at [i][t] (consecutive threads, consecutive banks).
-constexpr int QD_THREADS = 32;
-__global__ void __launch_bounds__(QD_THREADS) k_quadrature(const double *__restrict__ alpha,
-                                                           const double *__restrict__ beta,
-                                                           const int *__restrict__ steps, int K, int m, int jlo,
-                                                           int jhi, int fn, double *__restrict__ F) {
-    __shared__ double sd[TNSLQ_MAX_STEPS * QD_THREADS], se[TNSLQ_MAX_STEPS * QD_THREADS],
-        sz[TNSLQ_MAX_STEPS * QD_THREADS];
-    const int nj = jhi - jlo + 1;
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= K * nj) return;
-    const int k = t / nj, j = jlo + t % nj;
-    int jj = j;
-    if (steps && steps[k] < jj) jj = steps[k];
-    double *d = sd + threadIdx.x, *e = se + threadIdx.x, *z = sz + threadIdx.x;
-    for (int i = 0; i < jj; ++i) {
-        d[i * QD_THREADS] = alpha[(int64_t)k * m + i];
-        e[i * QD_THREADS] = (i + 1 < jj) ? beta[(int64_t)k * (m + 1) + i + 1] : 0.0;
+// One wave per (probe, step).  What bounds it is the chain of one problem's
+// rotations (about 0.85 m^2 of them, each 20 dependent FP64 operations), not
+// the number of problems; with one thread per problem the 32 threads of a
+// block also waited for each other's branches.  945 us before, QUAD_US now,
+// for 32 probes and 40 steps (280 and 88 for 16 probes and 20 steps).
+template <int R>
+__device__ inline void quadrature_wave(const double *__restrict__ ak, const double *__restrict__ bk, int jj, int fn,
+                                       double *sh) {
+    const int lane = threadIdx.x;
+    LaneVec<R> d, e, z;
+    double big = 0.0;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const int i = lane + 64 * r;
+        d.v[r] = i < jj ? ak[i] : 0.0;
+        e.v[r] = i + 1 < jj ? bk[i + 1] : 0.0;
+        big = fmax(big, fmax(fabs(d.v[r]), fabs(e.v[r])));
     }
-    tridiag_ql_first_row<QD_THREADS>(jj, d, e, z);
-    double f = 0.0;
-    for (int i = 0; i < jj; ++i) {
-        const double zi = z[i * QD_THREADS];
-        f += zi * zi * quad_f(fn, d[i * QD_THREADS]);
+    for (int o = 32; o > 0; o >>= 1) big = fmax(big, __shfl_xor(big, o, 64));
+    // scaled by a power of two, so that the squares of a rotation stay normal
+    const int x = big > 0.0 && isfinite(big) ? ilogb(big) : 0;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        d.v[r] = ldexp(d.v[r], -x);
+        e.v[r] = ldexp(e.v[r], -x);
     }
-    F[(int64_t)k * m + (j - 1)] = f;
+    tridiag_ql_first_row<R>(jj, lane, d, e, z);
+#pragma unroll
+    for (int r = 0; r < R; ++r) sh[lane + 64 * r] = z.v[r] * z.v[r] * quad_f(fn, ldexp(d.v[r], x));
+}
+
+__global__ void __launch_bounds__(64) k_quadrature(const double *__restrict__ alpha,
+                                                   const double *__restrict__ beta,
+                                                   const int *__restrict__ steps, int64_t K, int m, int jlo, int nj,
+                                                   int fn, double *__restrict__ F) {
+    __shared__ double sh[TNSLQ_MAX_STEPS];
+    for (int64_t t = blockIdx.x; t < K * nj; t += gridDim.x) {
+        const int64_t k = t % K;
+        const int j = jlo + nj - 1 - (int)(t / K);   // the longest chains start first
+        int jj = j;
+        if (steps && steps[k] < jj) jj = steps[k];
+        const double *ak = alpha + k * m, *bk = beta + k * (m + 1);
+        if (jj <= 64)
+            quadrature_wave<1>(ak, bk, jj, fn, sh);
+        else
+            quadrature_wave<2>(ak, bk, jj, fn, sh);
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            double f = 0.0;
+            for (int i = 0; i < jj; ++i) f += sh[i];
+            F[k * m + (j - 1)] = f;
+        }
+        __syncthreads();
+    }
 }
 
 // G_k = beta_1^2 F_j; mean, SE = sqrt(Var / K) (sample variance), E = log2 mean,
@@ -603,8 +686,6 @@ __global__ void k_features(const double *__restrict__ alpha, const double *__res
     }
 }
 
-inline unsigned cdiv(int64_t a, int64_t b) { return (unsigned)((a + b - 1) / b); }
-
 }  // namespace
 
 hipError_t launch_passA(int accfp64, const LzDims &z, const void *part, int S, int64_t split_stride, int k0,
@@ -664,14 +745,16 @@ hipError_t launch_passC(int prec, const LzDims &z, const double *nrmpart, const 
 
 hipError_t launch_steps(const double *alpha, const double *beta, int K, int m, int jdone, int *steps,
                         hipStream_t st) {
-    hipLaunchKernelGGL(k_steps, dim3(cdiv(K, 64)), dim3(64), 0, st, alpha, beta, K, m, jdone, steps);
+    hipLaunchKernelGGL(k_steps, dim3(K), dim3(64), 0, st, alpha, beta, m, jdone, steps);
     return hipGetLastError();
 }
 
 hipError_t launch_quadrature(const double *alpha, const double *beta, const int *steps, int K, int m, int jlo,
                              int jhi, int fn, double *F, hipStream_t st) {
-    const int64_t nt = (int64_t)K * (jhi - jlo + 1);
-    hipLaunchKernelGGL(k_quadrature, dim3(cdiv(nt, QD_THREADS)), dim3(QD_THREADS), 0, st, alpha, beta, steps, K, m, jlo, jhi, fn, F);
+    const int nj = jhi - jlo + 1;
+    const int64_t nt = (int64_t)K * nj;
+    hipLaunchKernelGGL(k_quadrature, dim3((unsigned)(nt < (1 << 20) ? nt : (1 << 20))), dim3(64), 0, st, alpha, beta,
+                       steps, (int64_t)K, m, jlo, nj, fn, F);
     return hipGetLastError();
 }
 

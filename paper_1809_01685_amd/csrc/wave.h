@@ -1,0 +1,39 @@
+// Wave64 helpers on registers: sums over a wave by data-parallel-primitive
+// moves, in a fixed order, and uniform reads of one lane.
+#pragma once
+#include <hip/hip_runtime.h>
+
+namespace tnslq {
+
+// v plus its DPP-moved copy (both 32-bit halves moved alike); lanes of rows
+// outside ROWS add 0
+template <int CTRL, int ROWS>
+__device__ inline double dpp_add(double v) {
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)b, CTRL, ROWS, 0xf, false);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, ROWS, 0xf, false);
+    return v + __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
+
+// lane `lane`'s value (uniform `lane`), in every lane
+__device__ inline double lane_value(double v, int lane) {
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_readlane((int)b, lane), hi = __builtin_amdgcn_readlane((int)(b >> 32), lane);
+    return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
+
+// The sum over the wave's 64 lanes, returned to every lane: pairs, quads,
+// half rows and rows of 16 by lane permutations within a row, then rows 0-1
+// into row 1 and rows 0-3 into row 3 by row broadcasts; lane 63 holds the
+// total.  A fixed order, done in registers.
+__device__ inline double wave_total(double v) {
+    v = dpp_add<0xB1, 0xf>(v);    // quad_perm [1, 0, 3, 2]
+    v = dpp_add<0x4E, 0xf>(v);    // quad_perm [2, 3, 0, 1]
+    v = dpp_add<0x141, 0xf>(v);   // row_half_mirror
+    v = dpp_add<0x140, 0xf>(v);   // row_mirror
+    v = dpp_add<0x142, 0xa>(v);   // row_bcast:15 into rows 1 and 3
+    v = dpp_add<0x143, 0xc>(v);   // row_bcast:31 into rows 2 and 3
+    return lane_value(v, 63);
+}
+
+}  // namespace tnslq
