@@ -347,7 +347,7 @@ int plan_rest(Plan &pl, int dtype, int prec, int K, int lanczos) {
         pl.off_G = take((size_t)K * 8);
         pl.off_stats = take((size_t)pl.m * 4 * 8);
         pl.off_red = take((size_t)2 * K * pl.nblk * 8);
-        pl.off_h = take((size_t)K * (pl.m + 1) * pl.nblk * 16 + (size_t)K * (pl.m + 1) * 16);
+        pl.off_h = take(pl.reorth ? reorth_part_bytes(n, K, pl.m) + (size_t)K * pl.m * 16 : 16);
         pl.off_steps = take((size_t)K * 4);
         pl.off_fit = take((size_t)2 * K * 8 + 8 * 8);
         pl.off_feat = take(64 * 4);
@@ -1111,7 +1111,7 @@ void bind(Ctx &c, void *ws, hipStream_t st) {
     c.dotpart = (double *)(c.ws + pl.off_red);
     c.nrmpart = c.dotpart + (size_t)pl.K * pl.nblk;
     c.hpart = (double *)(c.ws + pl.off_h);
-    c.h = (double2 *)(c.ws + pl.off_h + (size_t)pl.K * (pl.m + 1) * pl.nblk * 16);
+    c.h = (double2 *)(c.ws + pl.off_h + (pl.reorth ? reorth_part_bytes(pl.dAB, pl.K, pl.m) : 0));
     c.steps = (int *)(c.ws + pl.off_steps);
     c.finf = (double *)(c.ws + pl.off_fit);
     c.fsig = c.finf + pl.K;
@@ -1612,9 +1612,10 @@ int lanczos_step(Ctx &c, int j, StepEvents *se) {
         TNSLQ_HIP(hipEventRecord(se->pa(ch), c.st));
     }
     TNSLQ_HIP(hipEventRecord(se->mv1(), c.st));
-    TNSLQ_HIP(launch_passB(c.z, c.dotpart, q_cur, c.w, c.alpha, c.beta, j, c.nrmpart, pl.reorth ? 0 : 1, c.st));
     if (pl.reorth)
-        TNSLQ_HIP(launch_reorth(c.z, c.Q, j, slot, c.w, c.hpart, c.h, c.alpha, c.beta, j, c.nrmpart, c.st));
+        TNSLQ_HIP(launch_reorth(c.z, c.dotpart, c.Q, slot, c.w, c.hpart, c.h, c.alpha, c.beta, j, c.nrmpart, c.st));
+    else
+        TNSLQ_HIP(launch_passB(c.z, c.dotpart, q_cur, c.w, c.alpha, c.beta, j, c.nrmpart, c.st));
     TNSLQ_HIP(launch_passC(pl.prec, c.z, c.nrmpart, c.w, q_next, pl.stream ? nullptr : c.Xt, pl.nst1, c.alpha,
                            c.beta, j, c.st));
     TNSLQ_HIP(hipEventRecord(se->lz1(), c.st));
@@ -1986,7 +1987,7 @@ int make_splan(int dtype, int L, const int *s, int n_s, const tnslq_options *opt
     sp.off_G = take((size_t)K * 8);
     sp.off_stats = take((size_t)m * 4 * 8);
     sp.off_red = take((size_t)2 * K * sp.nblk * 8);
-    sp.off_h = take((size_t)K * (m + 1) * sp.nblk * 16 + (size_t)K * (m + 1) * 16);
+    sp.off_h = take(sp.reorth ? reorth_part_bytes(sp.d, K, m) + (size_t)K * m * 16 : 16);
     sp.off_steps = take((size_t)K * 4);
     sp.off_chk = take(STATE_CHECK_BYTES);
     sp.total = o;
@@ -2021,7 +2022,7 @@ int spectral_run(const SPlan &sp, const void *psi, const tnslq_options *opt, uin
     double *stats = (double *)(base + sp.off_stats);
     double *dotpart = (double *)(base + sp.off_red), *nrmpart = dotpart + (size_t)sp.K * sp.nblk;
     double *hpart = (double *)(base + sp.off_h);
-    double2 *h = (double2 *)(base + sp.off_h + (size_t)sp.K * (sp.m + 1) * sp.nblk * 16);
+    double2 *h = (double2 *)(base + sp.off_h + (sp.reorth ? reorth_part_bytes(sp.d, sp.K, sp.m) : 0));
     int *steps = (int *)(base + sp.off_steps);
     const LzDims z{sp.d, 1, sp.d, sp.K, sp.m, sp.nblk};
     const int64_t n = sp.d, slot = (int64_t)sp.K * n;
@@ -2069,8 +2070,10 @@ int spectral_run(const SPlan &sp, const void *psi, const tnslq_options *opt, uin
         TNSLQ_HIP(launch_colmac(sp.dtype, 0, plain_colmac(P2, sp.dR, sp.d, Z, sp.K, Yp, sp.S2), st));
         TNSLQ_HIP(hipEventRecord(mv1[j], st));
         TNSLQ_HIP(launch_passA(1, z, Yp, sp.S2, slot, 0, sp.K, q_prev, q_cur, w, alpha, beta, j, dotpart, st));
-        TNSLQ_HIP(launch_passB(z, dotpart, q_cur, w, alpha, beta, j, nrmpart, sp.reorth ? 0 : 1, st));
-        if (sp.reorth) TNSLQ_HIP(launch_reorth(z, Q, j, slot, w, hpart, h, alpha, beta, j, nrmpart, st));
+        if (sp.reorth)
+            TNSLQ_HIP(launch_reorth(z, dotpart, Q, slot, w, hpart, h, alpha, beta, j, nrmpart, st));
+        else
+            TNSLQ_HIP(launch_passB(z, dotpart, q_cur, w, alpha, beta, j, nrmpart, st));
         TNSLQ_HIP(launch_passC(TNSLQ_FP64, z, nrmpart, w, q_next, nullptr, 0, alpha, beta, j, st));
         TNSLQ_HIP(hipEventRecord(lz1[j], st));
     }

@@ -120,12 +120,11 @@ __global__ void __launch_bounds__(256) k_passA(const AccT *__restrict__ part, in
     if (threadIdx.x == 0) dotpart[(int64_t)k * nblk + blockIdx.x] = acc;
 }
 
-// alpha_j = Re<q_j, w>;  w -= alpha_j q_j;  optional partial sums of |w|^2.
+// alpha_j = Re<q_j, w>;  w -= alpha_j q_j;  partial sums of |w|^2.
 __global__ void __launch_bounds__(256) k_passB(const double *__restrict__ dotpart, int64_t n,
                                                const double2 *__restrict__ q_cur, double2 *__restrict__ w,
                                                double *__restrict__ alpha, const double *__restrict__ beta,
-                                               int m, int j, int nblk, double *__restrict__ nrmpart,
-                                               int want_norm) {
+                                               int m, int j, int nblk, double *__restrict__ nrmpart) {
     __shared__ double sh[16];
     const int k = blockIdx.y;
     const double *ak = alpha + (int64_t)k * m;
@@ -144,78 +143,177 @@ __global__ void __launch_bounds__(256) k_passB(const double *__restrict__ dotpar
         w[base + e] = v;
         acc += v.x * v.x + v.y * v.y;
     }
-    if (want_norm) {
-        acc = block_sum(acc, sh);
-        if (threadIdx.x == 0) nrmpart[(int64_t)k * nblk + blockIdx.x] = acc;
-    }
+    acc = block_sum(acc, sh);
+    if (threadIdx.x == 0) nrmpart[(int64_t)k * nblk + blockIdx.x] = acc;
     if (blockIdx.x == 0 && threadIdx.x == 0) alpha[(int64_t)k * m + (j - 1)] = a;
 }
 
-// Partial sums of h_i = <Q_i, w> for the nvec stored Lanczos vectors.
-__global__ void __launch_bounds__(256) k_reorth_dots(const double2 *__restrict__ Q, int nvec,
-                                                     int64_t slot, int64_t n, const double2 *__restrict__ w,
-                                                     int nblk, double2 *__restrict__ hpart) {
-    __shared__ double sh[16];
-    const int k = blockIdx.y;
-    int64_t beg, end;
-    elem_range(n, nblk, beg, end);
-    const int64_t base = (int64_t)k * n;
+// Classical Gram-Schmidt, twice, against the nvec stored vectors Q_i of the
+// probe.  It is bound by reading Q (nvec times the vector), so the recurrence
+// reads it three times instead of four: the kernels that change w also take
+// the next dot products of the chunk they hold, the second of them on the
+// chunk of Q just read, from cache.  A block holds a chunk of blockDim.x
+// elements of w, one per thread; for the dot products it leaves the chunk in
+// LDS and each wave takes every fourth (second, only) vector, so that one
+// wave sum ends a vector instead of two block sums.  Chunks are small (256
+// elements, down to 64 where the block count would leave the chip idle), so
+// that the chunks of Q in flight stay in cache between the two uses.  40 steps
+// of 32 probes: 28.1 to 21.2 ms at n = 65536 (4.4 TB/s of Q read), 4.24 to
+// 1.48 ms at n = 4096, where the block sums were most of the time.
+__device__ inline void chunk_dots(const double2 *__restrict__ Q, int nvec, int64_t slot, int64_t at, int cnt,
+                                  const double2 *ws, int nchunk, double2 *__restrict__ hpart) {
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6, nw = blockDim.x >> 6;
+    constexpr int VU = 2;   // vectors in flight per wave
+    double2 v[4];
+#pragma unroll
+    for (int x = 0; x < 4; ++x) v[x] = lane + 64 * x < cnt ? ws[lane + 64 * x] : make_double2(0.0, 0.0);
+    for (int i0 = wid; i0 < nvec; i0 += VU * nw) {
+        double2 q[VU][4];
+#pragma unroll
+        for (int u = 0; u < VU; ++u) {
+            const int i = i0 + u * nw;
+            const double2 *qi = Q + (int64_t)i * slot + at;
+#pragma unroll
+            for (int x = 0; x < 4; ++x)
+                q[u][x] = i < nvec && lane + 64 * x < cnt ? qi[lane + 64 * x] : make_double2(0.0, 0.0);
+        }
+#pragma unroll
+        for (int u = 0; u < VU; ++u) {
+            const int i = i0 + u * nw;
+            double re = 0.0, im = 0.0;
+#pragma unroll
+            for (int x = 0; x < 4; ++x) {
+                re += q[u][x].x * v[x].x + q[u][x].y * v[x].y;   // conj(q) * v
+                im += q[u][x].x * v[x].y - q[u][x].y * v[x].x;
+            }
+            re = wave_total(re);
+            im = wave_total(im);
+            if (lane == 0 && i < nvec) hpart[(int64_t)i * nchunk] = make_double2(re, im);
+        }
+    }
+}
+
+// v -= sum_i h_i Q_i of one element
+__device__ inline void remove_vectors(const double2 *__restrict__ Qe, int nvec, int64_t slot, const double2 *hs,
+                                      double2 &v) {
+#pragma unroll 8
     for (int i = 0; i < nvec; ++i) {
-        const double2 *qi = Q + i * slot + base;
-        double re = 0.0, im = 0.0;
-        for (int64_t e = beg + threadIdx.x; e < end; e += blockDim.x) {
-            double2 q = qi[e], v = w[base + e];
-            re += q.x * v.x + q.y * v.y;   // conj(q) * v
-            im += q.x * v.y - q.y * v.x;
-        }
-        re = block_sum(re, sh);
-        im = block_sum(im, sh);
-        if (threadIdx.x == 0) hpart[((int64_t)k * nvec + i) * nblk + blockIdx.x] = make_double2(re, im);
+        const double2 q = Qe[(int64_t)i * slot], c = hs[i];
+        v.x -= c.x * q.x - c.y * q.y;
+        v.y -= c.x * q.y + c.y * q.x;
     }
 }
 
-__global__ void k_reorth_reduce(const double2 *__restrict__ hpart, int nvec, int nblk,
-                                double2 *__restrict__ h) {
-    const int k = blockIdx.x;
+// The probe's h_i into LDS: from h, or, with few chunks, from their partial
+// sums
+__device__ inline void load_h(int k, int nvec, int nchunk, const double2 *__restrict__ hpart,
+                              const double2 *__restrict__ h, double2 *hs) {
     for (int i = threadIdx.x; i < nvec; i += blockDim.x) {
-        const double2 *p = hpart + ((int64_t)k * nvec + i) * nblk;
-        double re = 0.0, im = 0.0;
-        for (int b = 0; b < nblk; ++b) {
-            re += p[b].x;
-            im += p[b].y;
+        double2 s = make_double2(0.0, 0.0);
+        if (nchunk > REORTH_FOLD) {
+            s = h[(int64_t)k * nvec + i];
+        } else {
+            const double2 *p = hpart + ((int64_t)k * nvec + i) * nchunk;
+#pragma unroll 8
+            for (int b = 0; b < nchunk; ++b) {
+                s.x += p[b].x;
+                s.y += p[b].y;
+            }
         }
-        h[(int64_t)k * nvec + i] = make_double2(re, im);
+        hs[i] = s;
     }
+    __syncthreads();
 }
 
-// w -= sum_i h_i Q_i; optional partial sums of |w|^2.
+// passB of a reorthogonalised step: alpha_j, w -= alpha_j q_j, and the first
+// dot products.
+__global__ void __launch_bounds__(256) k_passB_dots(const double *__restrict__ dotpart, int nblk, int64_t n,
+                                                    const double2 *__restrict__ Q, int64_t slot,
+                                                    double2 *__restrict__ w, double *__restrict__ alpha,
+                                                    const double *__restrict__ beta, int m, int j, int nchunk,
+                                                    double2 *__restrict__ hpart) {
+    __shared__ double sh[16];
+    __shared__ double2 ws[256];
+    const int k = blockIdx.y;
+    const bool live = first_break(alpha + (int64_t)k * m, beta + (int64_t)k * (m + 1), j - 1) == 0;
+    double a = sum_partials(dotpart + (int64_t)k * nblk, nblk, sh);
+    if (!live) a = 0.0;
+    const int64_t beg = (int64_t)blockIdx.x * blockDim.x, at = (int64_t)k * n + beg;
+    const int cnt = (int)(n - beg < (int64_t)blockDim.x ? n - beg : (int64_t)blockDim.x);
+    if ((int)threadIdx.x < cnt) {
+        const double2 q = Q[(int64_t)(j - 1) * slot + at + threadIdx.x];
+        double2 v = w[at + threadIdx.x];
+        v.x -= a * q.x;
+        v.y -= a * q.y;
+        w[at + threadIdx.x] = v;
+        ws[threadIdx.x] = v;
+    }
+    __syncthreads();
+    chunk_dots(Q, j, slot, at, cnt, ws, nchunk, hpart + (int64_t)k * j * nchunk + blockIdx.x);
+    if (blockIdx.x == 0 && threadIdx.x == 0) alpha[(int64_t)k * m + (j - 1)] = a;
+}
+
+// w -= sum_i h_i Q_i and the second dot products.
+__global__ void __launch_bounds__(256) k_reorth_update_dots(const double2 *__restrict__ Q, int nvec, int64_t slot,
+                                                            int64_t n, const double2 *__restrict__ h,
+                                                            const double2 *__restrict__ hpart_in,
+                                                            double2 *__restrict__ w, int nchunk,
+                                                            double2 *__restrict__ hpart) {
+    __shared__ double2 ws[256];
+    __shared__ double2 hs[TNSLQ_MAX_STEPS + 1];
+    const int k = blockIdx.y;
+    load_h(k, nvec, nchunk, hpart_in, h, hs);
+    const int64_t beg = (int64_t)blockIdx.x * blockDim.x, at = (int64_t)k * n + beg;
+    const int cnt = (int)(n - beg < (int64_t)blockDim.x ? n - beg : (int64_t)blockDim.x);
+    if ((int)threadIdx.x < cnt) {
+        double2 v = w[at + threadIdx.x];
+        remove_vectors(Q + at + threadIdx.x, nvec, slot, hs, v);
+        w[at + threadIdx.x] = v;
+        ws[threadIdx.x] = v;
+    }
+    __syncthreads();
+    chunk_dots(Q, nvec, slot, at, cnt, ws, nchunk, hpart + (int64_t)k * nvec * nchunk + blockIdx.x);
+}
+
+// h_i = the sum of the chunks' partial sums, one wave per (probe, i).
+__global__ void __launch_bounds__(256) k_reorth_reduce(const double2 *__restrict__ hpart, int nvec, int nchunk,
+                                                       double2 *__restrict__ h) {
+    const int k = blockIdx.y, lane = threadIdx.x & 63, i = blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (i >= nvec) return;
+    const double2 *p = hpart + ((int64_t)k * nvec + i) * nchunk;
+    double re = 0.0, im = 0.0;
+    for (int b = lane; b < nchunk; b += 64) {
+        re += p[b].x;
+        im += p[b].y;
+    }
+    re = wave_total(re);
+    im = wave_total(im);
+    if (lane == 0) h[(int64_t)k * nvec + i] = make_double2(re, im);
+}
+
+// w -= sum_i h_i Q_i and the partial sums of |w|^2, over the recurrence's own
+// blocks.
 __global__ void __launch_bounds__(256) k_reorth_update(const double2 *__restrict__ Q, int nvec, int64_t slot,
                                                        int64_t n, const double2 *__restrict__ h,
+                                                       const double2 *__restrict__ hpart, int nchunk,
                                                        double2 *__restrict__ w, int nblk,
-                                                       double *__restrict__ nrmpart, int want_norm) {
+                                                       double *__restrict__ nrmpart) {
     __shared__ double sh[16];
     __shared__ double2 hs[TNSLQ_MAX_STEPS + 1];
     const int k = blockIdx.y;
-    for (int i = threadIdx.x; i < nvec; i += blockDim.x) hs[i] = h[(int64_t)k * nvec + i];
-    __syncthreads();
+    load_h(k, nvec, nchunk, hpart, h, hs);
     int64_t beg, end;
     elem_range(n, nblk, beg, end);
     const int64_t base = (int64_t)k * n;
     double acc = 0.0;
     for (int64_t e = beg + threadIdx.x; e < end; e += blockDim.x) {
         double2 v = w[base + e];
-        for (int i = 0; i < nvec; ++i) {
-            double2 q = Q[i * slot + base + e], c = hs[i];
-            v.x -= c.x * q.x - c.y * q.y;
-            v.y -= c.x * q.y + c.y * q.x;
-        }
+        remove_vectors(Q + base + e, nvec, slot, hs, v);
         w[base + e] = v;
         acc += v.x * v.x + v.y * v.y;
     }
-    if (want_norm) {
-        acc = block_sum(acc, sh);
-        if (threadIdx.x == 0) nrmpart[(int64_t)k * nblk + blockIdx.x] = acc;
-    }
+    acc = block_sum(acc, sh);
+    if (threadIdx.x == 0) nrmpart[(int64_t)k * nblk + blockIdx.x] = acc;
 }
 
 // beta_{j+1} = ||w||, breakdown test, q_{j+1} = w / beta_{j+1} (0 after a
@@ -367,7 +465,7 @@ __device__ inline double quad_f(int fn, double x) {
 // One wave per (probe, step).  What bounds it is the chain of one problem's
 // rotations (about 0.85 m^2 of them, each 20 dependent FP64 operations), not
 // the number of problems; with one thread per problem the 32 threads of a
-// block also waited for each other's branches.  945 us before, QUAD_US now,
+// block also waited for each other's branches.  945 us before, 299 now,
 // for 32 probes and 40 steps (280 and 88 for 16 probes and 20 steps).
 template <int R>
 __device__ inline void quadrature_wave(const double *__restrict__ ak, const double *__restrict__ bk, int jj, int fn,
@@ -702,28 +800,30 @@ hipError_t launch_passA(int accfp64, const LzDims &z, const void *part, int S, i
 }
 
 hipError_t launch_passB(const LzDims &z, const double *dotpart, const double2 *q_cur, double2 *w,
-                        double *alpha, const double *beta, int j, double *nrmpart, int want_norm,
-                        hipStream_t st) {
+                        double *alpha, const double *beta, int j, double *nrmpart, hipStream_t st) {
     dim3 grid(z.nblk, z.K), block(256);
     hipLaunchKernelGGL(k_passB, grid, block, 0, st, dotpart, z.n, q_cur, w, alpha, beta, z.m, j, z.nblk,
-                       nrmpart, want_norm);
+                       nrmpart);
     return hipGetLastError();
 }
 
-hipError_t launch_reorth(const LzDims &z, const double2 *Q, int nvec, int64_t slot, double2 *w,
-                         double *hpart, double2 *h, const double *alpha, const double *beta, int j,
-                         double *nrmpart, hipStream_t st) {
-    (void)alpha;
-    (void)beta;
-    (void)j;
-    dim3 grid(z.nblk, z.K), block(256);
-    for (int pass = 0; pass < 2; ++pass) {
-        hipLaunchKernelGGL(k_reorth_dots, grid, block, 0, st, Q, nvec, slot, z.n, (const double2 *)w, z.nblk,
-                           (double2 *)hpart);
-        hipLaunchKernelGGL(k_reorth_reduce, dim3(z.K), dim3(64), 0, st, (const double2 *)hpart, nvec, z.nblk, h);
-        hipLaunchKernelGGL(k_reorth_update, grid, block, 0, st, Q, nvec, slot, z.n, (const double2 *)h, w,
-                           z.nblk, nrmpart, pass == 1 ? 1 : 0);
-    }
+hipError_t launch_reorth(const LzDims &z, const double *dotpart, const double2 *Q, int64_t slot, double2 *w,
+                         double *hpart, double2 *h, double *alpha, const double *beta, int j, double *nrmpart,
+                         hipStream_t st) {
+    const int bt = reorth_chunk(z.n, z.K);
+    const int64_t chunks = reorth_chunks(z.n, z.K);
+    if (chunks > 0x7fffffff) return hipErrorInvalidConfiguration;
+    const int nc = (int)chunks;
+    const bool fold = nc <= REORTH_FOLD;
+    double2 *p0 = (double2 *)hpart, *p1 = fold ? p0 + (size_t)z.K * j * nc : p0;
+    const dim3 grid(nc, z.K), block(bt), rgrid((j + 3) / 4, z.K);
+    hipLaunchKernelGGL(k_passB_dots, grid, block, 0, st, dotpart, z.nblk, z.n, Q, slot, w, alpha, beta, z.m, j, nc, p0);
+    if (!fold) hipLaunchKernelGGL(k_reorth_reduce, rgrid, dim3(256), 0, st, (const double2 *)p0, j, nc, h);
+    hipLaunchKernelGGL(k_reorth_update_dots, grid, block, 0, st, Q, j, slot, z.n, (const double2 *)h,
+                       (const double2 *)p0, w, nc, p1);
+    if (!fold) hipLaunchKernelGGL(k_reorth_reduce, rgrid, dim3(256), 0, st, (const double2 *)p1, j, nc, h);
+    hipLaunchKernelGGL(k_reorth_update, dim3(z.nblk, z.K), dim3(256), 0, st, Q, j, slot, z.n, (const double2 *)h,
+                       (const double2 *)p1, nc, w, z.nblk, nrmpart);
     return hipGetLastError();
 }
 

@@ -130,11 +130,33 @@ hipError_t launch_passA(int accfp64, const LzDims &z, const void *part, int S, i
                         const double *alpha, const double *beta, int j, double *dotpart,
                         hipStream_t st);
 hipError_t launch_passB(const LzDims &z, const double *dotpart, const double2 *q_cur, double2 *w,
-                        double *alpha, const double *beta, int j, double *nrmpart, int want_norm,
-                        hipStream_t st);
-hipError_t launch_reorth(const LzDims &z, const double2 *Q, int nvec, int64_t q_slot_stride,
-                         double2 *w, double *hpart, double2 *h, const double *alpha,
-                         const double *beta, int j, double *nrmpart, hipStream_t st);
+                        double *alpha, const double *beta, int j, double *nrmpart, hipStream_t st);
+// Elements per block of the reorthogonalisation's dot products (one per
+// thread): 256, or down to 64 to give every CU two blocks; the blocks per
+// probe; and the bytes of their partial sums against up to m vectors.  Up to
+// REORTH_FOLD chunks the kernels that need the sums add the partials
+// themselves (a launch less; a thread's loads are one latency), reading one
+// set while they write another; beyond that a kernel adds them into h.
+constexpr int REORTH_FOLD = 32;
+inline int reorth_chunk(int64_t n, int K) {
+    int c = 256;
+    while (c > 64 && (n + c - 1) / c * K < 512) c /= 2;
+    return c;
+}
+inline int64_t reorth_chunks(int64_t n, int K) {
+    const int c = reorth_chunk(n, K);
+    return (n + c - 1) / c;
+}
+inline size_t reorth_part_bytes(int64_t n, int K, int m) {
+    const int64_t c = reorth_chunks(n, K);
+    return (size_t)(c > REORTH_FOLD ? 1 : 2) * K * m * c * 16;
+}
+// The rest of a reorthogonalised step after passA: alpha_j, w -= alpha_j q_j,
+// Gram-Schmidt twice against q_1 .. q_j (Q, slots `slot` apart) and the
+// partial sums of |w|^2.
+hipError_t launch_reorth(const LzDims &z, const double *dotpart, const double2 *Q, int64_t slot, double2 *w,
+                         double *hpart, double2 *h, double *alpha, const double *beta, int j, double *nrmpart,
+                         hipStream_t st);
 hipError_t launch_passC(int prec, const LzDims &z, const double *nrmpart, const double2 *w,
                         double2 *q_next, void *Xt, int64_t xt_nst, const double *alpha,
                         double *beta, int j, hipStream_t st);

@@ -38,3 +38,29 @@ def test_quadrature_at_wave_edges(dev, m, scale):
             want = float((v[0] ** 2 * np.abs(lam)).sum())
             norm = max(np.abs(lam).max(), 1e-300)
             assert abs(F[k, j - 1] / scale - want) <= 48 * m * np.finfo(float).eps * norm, (k, j)
+
+
+@pytest.mark.parametrize("dims,a,b,K,m", [
+    ((2, 2, 3, 4), (0,), (1,), 3, 2),                  # n = 4: one chunk, mostly empty lanes
+    ((3, 3, 7, 6), (0, 2), (1,), 5, 9),                # n = 63: one element short of a wave
+    ((5, 13, 4, 5), (0,), (1,), 600, 12),              # n = 65, 600 probes: 128-element chunks
+    ((2, 2, 2, 5, 9, 3, 8), (0, 3, 4), (1, 2, 5), 4, 40),   # n = 1080: 17 chunks, added by their readers
+    ((2, 3, 7, 3, 19, 3), (1, 2, 4), (0, 3), 2, 33),   # n = 2394: 38 chunks, added by a kernel
+])
+def test_reorthogonalised_recurrence_at_chunk_edges(dev, dims, a, b, K, m):
+    # alpha, beta and the basis they come from: against a recurrence in 64
+    # bits that orthogonalises twice, from the explicit operator.  Both sides
+    # are backward stable with an orthonormal basis, so the coefficients agree
+    # to a modest multiple of eps times the operator's norm: 1e-11 of the
+    # largest, as the parity tests of the explicit form.
+    import torch
+    import tnslq_inputs as ti
+    from oracle import slq
+    psi = ti.haar_state_dims(list(dims), 5)
+    g = T.tnslq_logneg_dims(torch.from_numpy(psi).to(dev), list(dims), list(a), list(b), K, m, reorth=True,
+                            precision="fp64", seed=2)
+    Ko = min(K, 6)   # the oracle's first probes are the same ones
+    o = slq.slq_logneg_dims(psi, list(dims), list(a), list(b), Ko, m, seed=2, reorth=True)
+    big = np.abs(o["alpha"]).max()
+    assert np.abs(g["alpha"][:Ko] - o["alpha"]).max() <= 1e-11 * big
+    assert np.abs(g["beta"][:Ko, 1:] - o["beta"][:, 1:]).max() <= 1e-11 * big
