@@ -250,7 +250,11 @@ int plan_rest(Plan &pl, int dtype, int prec, int K, int lanczos) {
         pl.nst_e = brick_stages(prec, pl.dE);
         const int64_t tl = (up128(n) / 128) * (up128(K) / 128);
         pl.S = 1;
-        while (tl * pl.S < 2048 && pl.nst_rho % (2 * pl.S) == 0 && pl.nst_rho / (2 * pl.S) >= 8) pl.S *= 2;
+        if (thin_product(prec, n, K, 1))
+            // 16-row tiles: about 2048 waves, two per SIMD, each at least eight bricks
+            pl.S = (int)std::max<int64_t>(1, std::min<int64_t>(2048 / ((n + 15) / 16), pl.nst_rho / 8));
+        else
+            while (tl * pl.S < 2048 && pl.nst_rho % (2 * pl.S) == 0 && pl.nst_rho / (2 * pl.S) >= 8) pl.S *= 2;
     }
     if (pl.stream) {
         pl.kc = K;

@@ -383,10 +383,22 @@ struct LaneVec {
     }
 };
 
-// 1 / sqrt(x) for a normal x: the hardware's estimate and one third-order step
-__device__ inline double rsqrt_step(double x) {
-    const double y = __builtin_amdgcn_rsq(x), h = fma(-x * y, y, 1.0);
-    return fma(y * h, fma(0.375, h, 0.5), y);
+// r = sqrt(x) and y = 1 / r for a normal x, each to the last bit but for rare
+// ties: the hardware's estimate of 1 / sqrt(x) and one third-order step, the
+// root with a residual correction, and a Newton step to that root's reciprocal.
+__device__ inline double root_and_reciprocal(double x, double &y) {
+    y = __builtin_amdgcn_rsq(x);
+    const double h = fma(-x * y, y, 1.0);
+    y = fma(y * h, fma(0.375, h, 0.5), y);
+    double r = x * y;
+    r = fma(0.5 * y, fma(-r, r, x), r);
+    y = fma(y, fma(-r, y, 1.0), y);
+    return r;
+}
+// a / r from y = 1 / r, rounded as a division
+__device__ inline double quotient(double a, double r, double y) {
+    const double q = a * y;
+    return fma(fma(-q, r, a), y, q);
 }
 
 template <int R>
@@ -412,7 +424,7 @@ __device__ void tridiag_ql_first_row(int n, int lane, LaneVec<R> &d, LaneVec<R> 
             const double dl = d.get(l), el = e.get(l);
             double dn = d.get(mm), zn = z.get(mm);   // entries i + 1
             double g = (d.get(l + 1) - dl) / (2.0 * el);
-            g = dn - dl + el / (g + copysign(sqrt(fma(g, g, 1.0)), g));
+            g = dn - dl + el / (g + copysign(hypot(g, 1.0), g));
             double s = 1.0, c = 1.0, p = 0.0;
             bool early = false;
             int i = mm - 1;
@@ -423,19 +435,18 @@ __device__ void tridiag_ql_first_row(int n, int lane, LaneVec<R> &d, LaneVec<R> 
                     early = true;
                     break;
                 }
-                const double y = rsqrt_step(r2);
-                double r = r2 * y;
-                r = fma(0.5 * y, fma(-r, r, r2), r);
+                double y;
+                const double r = root_and_reciprocal(r2, y);
                 e.set(lane, i + 1, r);
-                s = f * y;
-                c = g * y;
+                s = quotient(f, r, y);
+                c = quotient(g, r, y);
                 g = dn - p;
-                const double t = fma(di - g, s, 2.0 * c * bb);
+                const double t = fma(bb, 2.0 * c, s * (di - g));
+                d.set(lane, i + 1, fma(s, t, g));
                 p = s * t;
-                d.set(lane, i + 1, g + p);
                 g = fma(c, t, -bb);
-                z.set(lane, i + 1, fma(s, zi, c * zn));
-                zn = fma(c, zi, -s * zn);
+                z.set(lane, i + 1, fma(c, zn, s * zi));
+                zn = fma(c, zi, -(s * zn));
                 dn = di;
             }
             if (early) {
@@ -465,8 +476,8 @@ __device__ inline double quad_f(int fn, double x) {
 // One wave per (probe, step).  What bounds it is the chain of one problem's
 // rotations (about 0.85 m^2 of them, each 20 dependent FP64 operations), not
 // the number of problems; with one thread per problem the 32 threads of a
-// block also waited for each other's branches.  945 us before, 299 now,
-// for 32 probes and 40 steps (280 and 88 for 16 probes and 20 steps).
+// block also waited for each other's branches.  945 us before, 317 now,
+// for 32 probes and 40 steps (280 and 96 for 16 probes and 20 steps).
 template <int R>
 __device__ inline void quadrature_wave(const double *__restrict__ ak, const double *__restrict__ bk, int jj, int fn,
                                        double *sh) {
@@ -490,14 +501,17 @@ __device__ inline void quadrature_wave(const double *__restrict__ ak, const doub
     }
     tridiag_ql_first_row<R>(jj, lane, d, e, z);
 #pragma unroll
-    for (int r = 0; r < R; ++r) sh[lane + 64 * r] = z.v[r] * z.v[r] * quad_f(fn, ldexp(d.v[r], x));
+    for (int r = 0; r < R; ++r) {
+        sh[lane + 64 * r] = z.v[r] * z.v[r];
+        sh[TNSLQ_MAX_STEPS + lane + 64 * r] = quad_f(fn, ldexp(d.v[r], x));
+    }
 }
 
 __global__ void __launch_bounds__(64) k_quadrature(const double *__restrict__ alpha,
                                                    const double *__restrict__ beta,
                                                    const int *__restrict__ steps, int64_t K, int m, int jlo, int nj,
                                                    int fn, double *__restrict__ F) {
-    __shared__ double sh[TNSLQ_MAX_STEPS];
+    __shared__ double sh[2 * TNSLQ_MAX_STEPS];   // tau^2, f(theta)
     for (int64_t t = blockIdx.x; t < K * nj; t += gridDim.x) {
         const int64_t k = t % K;
         const int j = jlo + nj - 1 - (int)(t / K);   // the longest chains start first
@@ -511,7 +525,7 @@ __global__ void __launch_bounds__(64) k_quadrature(const double *__restrict__ al
         __syncthreads();
         if (threadIdx.x == 0) {
             double f = 0.0;
-            for (int i = 0; i < jj; ++i) f += sh[i];
+            for (int i = 0; i < jj; ++i) f = fma(sh[i], sh[TNSLQ_MAX_STEPS + i], f);
             F[k * m + (j - 1)] = f;
         }
         __syncthreads();

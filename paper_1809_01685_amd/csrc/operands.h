@@ -185,8 +185,18 @@ struct GemmDesc {
     int64_t ldc, cbs, c_split;
 };
 
+// Whether an M x N product in S splits runs in 16-row tiles against all its
+// columns (k_thin_product) instead of 128 x 128 tiles: FP32 and FP64 up to 64
+// columns, where a 128-column tile is at least half padding (at 65 to 128
+// columns the large tile's reuse of A through LDS is worth the padding).
+// Its splits need not divide the bricks.
+__host__ inline bool thin_product(int prec, int64_t M, int64_t N, int S) {
+    return (prec == TNSLQ_FP32 || prec == TNSLQ_FP64) && N <= 64 && S >= 1 && (M + 127) / 128 * 2 * S <= 0xffffff;
+}
+
 hipError_t launch_gemm(int prec, const GemmDesc &g, hipStream_t st);
 hipError_t launch_gemm_valu(int prec, const GemmDesc &g, hipStream_t st);
+hipError_t launch_gemm_thin(int prec, const GemmDesc &g, hipStream_t st);
 bool gemm_mfma_supported(int prec, const GemmDesc &g);
 hipError_t launch_gemm_mfma(int prec, const GemmDesc &g, hipStream_t st);
 
