@@ -205,6 +205,21 @@ NetBufs net_bufs(const Plan &pl) {
     return b;
 }
 
+// Where the kernels of a run stamp their starts (operands.h): the run itself;
+// per step, for each probe chunk the first contraction, the second and the
+// merge of Y, then the rest of the Lanczos step, and its end where something
+// other than the next step's first contraction follows.
+struct Stamps {
+    int nchunk;
+    size_t count(int m) const { return 1 + (size_t)m * (2 + 3 * nchunk) + 1; }
+    size_t step(int j) const { return 1 + (size_t)(j - 1) * (2 + 3 * nchunk); }
+    size_t c1(int j, int ch) const { return step(j) + 3 * ch; }
+    size_t c2(int j, int ch) const { return step(j) + 3 * ch + 1; }
+    size_t merge(int j, int ch) const { return step(j) + 3 * ch + 2; }
+    size_t lanczos(int j) const { return step(j) + 3 * nchunk; }
+    size_t end(int j) const { return step(j) + 3 * nchunk + 1; }
+};
+
 // Chunking, splits and the workspace carve-up of a plan whose roles, sizes
 // and operator form are set.
 int plan_rest(Plan &pl, int dtype, int prec, int K, int lanczos) {
@@ -345,15 +360,20 @@ int plan_rest(Plan &pl, int dtype, int prec, int K, int lanczos) {
         pl.nQ = pl.reorth ? pl.m + 1 : 3;
         pl.off_Q = take((size_t)pl.nQ * K * n * 16);
         pl.off_w = take((size_t)K * n * 16);
+        // what a call reads back, in one run from off_alpha to end_out: the
+        // coefficients and quadrature values, then the small results
         pl.off_alpha = take((size_t)K * pl.m * 8);
         pl.off_beta = take((size_t)K * (pl.m + 1) * 8);
         pl.off_F = take((size_t)K * pl.m * 8);
-        pl.off_G = take((size_t)K * 8);
         pl.off_stats = take((size_t)pl.m * 4 * 8);
+        pl.off_G = take((size_t)K * 8);
+        pl.off_fit = take((size_t)2 * K * 8 + 8 * 8);
+        pl.off_steps = take((size_t)K * 4);
+        // (the stamps' place does not depend on the chunking)
+        pl.off_stamp = take(Stamps{K}.count(pl.m) * 8);
+        pl.end_out = pl.off_stamp + Stamps{(K + pl.kc - 1) / pl.kc}.count(pl.m) * 8;
         pl.off_red = take((size_t)2 * K * pl.nblk * 8);
         pl.off_h = take(pl.reorth ? reorth_part_bytes(n, K, pl.m) + (size_t)K * pl.m * 16 : 16);
-        pl.off_steps = take((size_t)K * 4);
-        pl.off_fit = take((size_t)2 * K * 8 + 8 * 8);
         pl.off_feat = take(64 * 4);
         pl.off_mlp = take(mlp_ws_bytes(1) + 64);
         pl.off_chk = take(STATE_CHECK_BYTES);
@@ -1061,17 +1081,9 @@ struct Ctx {
     double *finf, *fsig, *fitout;
     float *feat;
     void *mlpws;
-    std::vector<hipEvent_t> ev;
+    Stamps at{1};
+    uint64_t *stamps = nullptr;
     int n_launch = 0;
-    ~Ctx() {
-        for (auto e : ev) (void)hipEventDestroy(e);
-    }
-    hipEvent_t event() {
-        hipEvent_t e;
-        if (hipEventCreate(&e) != hipSuccess) return nullptr;
-        ev.push_back(e);
-        return e;
-    }
 };
 
 void bind(Ctx &c, void *ws, hipStream_t st) {
@@ -1120,6 +1132,8 @@ void bind(Ctx &c, void *ws, hipStream_t st) {
     c.finf = (double *)(c.ws + pl.off_fit);
     c.fsig = c.finf + pl.K;
     c.fitout = c.fsig + pl.K;
+    c.at = Stamps{(pl.K + pl.kc - 1) / pl.kc};
+    c.stamps = (uint64_t *)(c.ws + pl.off_stamp);
     c.feat = (float *)(c.ws + pl.off_feat);
     c.mlpws = c.ws + pl.off_mlp;
     // the explicit form contracts the vectors over the whole index (a, b): its
@@ -1343,33 +1357,32 @@ int do_layout(Ctx &c, const void *psi) {
 //   Ym[k][a dB + b]        = sum_s Yt[s][(k, b)][a]
 // Both passes read their vectors and write their outputs contiguously, the
 // column MAC's plain form.
-int stream_contract(Ctx &c, const double2 *xq, hipEvent_t e1, hipEvent_t e2) {
+int stream_contract(Ctx &c, const double2 *xq, uint64_t *t1, uint64_t *t2) {
     const Plan &pl = c.pl;
     if (pl.fused) {
         // both contractions in one read of psi; the Lanczos pass (or the
         // matvec's reduction) sums the blocks' partials
-        if (e1) TNSLQ_HIP(hipEventRecord(e1, c.st));
+        if (t1) TNSLQ_HIP(launch_stamp(t1, c.st));
         TNSLQ_HIP(launch_pt_fused(c.P1s, xq, pl.dA, pl.dB, pl.K, pl.dE, FUSED_BLOCKS, (double2 *)c.Ypart, c.st));
-        if (e2) TNSLQ_HIP(hipEventRecord(e2, c.st));
         c.n_launch++;
         return TNSLQ_OK;
     }
     const int64_t ncol = pl.dE * pl.dB;
     const int nv = pl.K * (int)pl.dB;
-    TNSLQ_HIP(launch_vectors_by_b(xq, pl.K, pl.dA, pl.nB, c.Xq, c.st));
+    TNSLQ_HIP(launch_vectors_by_b(xq, pl.K, pl.dA, pl.nB, c.Xq, c.st, t1));
     TNSLQ_HIP(launch_colmac(pl.dtype, 1, plain_colmac(c.P1s, pl.dA, ncol, c.Xq, nv, c.Up, pl.S1s), c.st));
     TNSLQ_HIP(launch_sum_transpose_ups(c.Up, pl.S1s, pl.K, pl.nB, pl.nE, c.U2, c.st));
-    if (e1) TNSLQ_HIP(hipEventRecord(e1, c.st));
     double2 *Yt = (double2 *)c.Ypart;
-    TNSLQ_HIP(launch_colmac(pl.dtype, 0, plain_colmac(c.P2s, ncol, pl.dA, c.U2, nv, Yt, pl.S2s), c.st));
+    ColmacDesc g2 = plain_colmac(c.P2s, ncol, pl.dA, c.U2, nv, Yt, pl.S2s);
+    g2.start = t2;
+    TNSLQ_HIP(launch_colmac(pl.dtype, 0, g2, c.st));
     TNSLQ_HIP(launch_sum_transpose_y(Yt, pl.S2s, pl.K, pl.dA, pl.nB, c.Ym, c.st));
-    if (e2) TNSLQ_HIP(hipEventRecord(e2, c.st));
     c.n_launch++;
     return TNSLQ_OK;
 }
 
 // Both contractions for probes [k0, k0 + kcur): Xt -> Ups -> Ypart.
-int contract_chunk(Ctx &c, int k0, int kcur, hipEvent_t e1, hipEvent_t e2) {
+int contract_chunk(Ctx &c, int k0, int kcur, uint64_t *t1, uint64_t *t2) {
     const Plan &pl = c.pl;
     // contraction 1: Ups[(k, b)][(c, b')] = sum_a' conj psi[a', b, c] Xt[(k, b')][a'];
     // output (i, j) = ((b, c), (k, b')) -> row k d_B + b, index c d_B + b'
@@ -1414,24 +1427,24 @@ int contract_chunk(Ctx &c, int k0, int kcur, hipEvent_t e1, hipEvent_t e2) {
     g2.ldc = pl.dB;
     g2.cbs = pl.dAB;
     g2.c_split = (int64_t)pl.kc * pl.dAB;
+    g1.start = t1;
+    g2.start = t2;
     TNSLQ_HIP(launch_gemm(pl.prec, g1, c.st));
     if (pl.S1 > 1)
         TNSLQ_HIP(launch_partials_to_bricks(pl.prec, c.U1part, pl.S1, g1.c_split, u1n, pl.nB, pl.nE, c.Ups, pl.nst2,
                                             c.st));
-    if (e1) TNSLQ_HIP(hipEventRecord(e1, c.st));
     TNSLQ_HIP(launch_gemm(pl.prec, g2, c.st));
-    if (e2) TNSLQ_HIP(hipEventRecord(e2, c.st));
     c.n_launch++;
     return TNSLQ_OK;
 }
 
 // Intermediary (iii): Y[k][i] = sum_l rho^{T_B}[i][l] Xt[k][l] for all K
 // probes, split-K partials at s K n + k n + i.
-int explicit_matvec(Ctx &c, hipEvent_t e1, hipEvent_t e2) {
+int explicit_matvec(Ctx &c, uint64_t *t1) {
     const Plan &pl = c.pl;
     const int64_t n = pl.dAB;
-    if (e1) TNSLQ_HIP(hipEventRecord(e1, c.st));
     GemmDesc g{};
+    g.start = t1;
     g.A = c.rho;
     g.B = c.Xt;
     g.C = c.Ypart;
@@ -1447,7 +1460,6 @@ int explicit_matvec(Ctx &c, hipEvent_t e1, hipEvent_t e2) {
     g.cbs = n;
     g.c_split = (int64_t)pl.K * n;
     TNSLQ_HIP(launch_gemm(pl.prec, g, c.st));
-    if (e2) TNSLQ_HIP(hipEventRecord(e2, c.st));
     c.n_launch++;
     return TNSLQ_OK;
 }
@@ -1461,7 +1473,7 @@ int explicit_matvec(Ctx &c, hipEvent_t e1, hipEvent_t e2) {
 //   Z3[k][a][(m', v)]       = sum_(u', m) P[a][(u', m)] Z2p[k][(u', m)][(m', v)]
 //   Y[k][a][b]              = sum_(m', v) Z3[k][a][(m', v)] conj Q[b][(m', v)]
 // i.e. Y[a][b] = sum_{a', b', e} psi[a][b'][e] conj psi[a'][b][e] X[a'][b'].
-int mps_matvec(Ctx &c, const double2 *x, int kcur, hipEvent_t e1, hipEvent_t e2) {
+int mps_matvec(Ctx &c, const double2 *x, int kcur, uint64_t *t1, uint64_t *t2) {
     const Plan &pl = c.pl;
     const MpsFactors &f = c.mf;
     const int64_t n = pl.dAB, UpM = f.Up * f.M, MV = f.M * f.V;
@@ -1472,11 +1484,11 @@ int mps_matvec(Ctx &c, const double2 *x, int kcur, hipEvent_t e1, hipEvent_t e2)
             // Z2 written straight into the exchanged order Z2p
             TNSLQ_HIP(launch_zgemm_xc(Z1, Q, Z2p, (int)UpM, (int)MV, kB, kB, MV, kcur, UpM * kB, 0, UpM * MV, f.M,
                                       f.V, c.st));
-            if (e1) TNSLQ_HIP(hipEventRecord(e1, c.st));
+            TNSLQ_HIP(launch_stamp(t2, c.st));
         } else {
             TNSLQ_HIP(launch_zgemm(0, 0, Z1, Q, Z2, (int)UpM, (int)MV, kB, kB, MV, MV, kcur, UpM * kB, 0, UpM * MV,
                                    c.st));
-            if (e1) TNSLQ_HIP(hipEventRecord(e1, c.st));
+            TNSLQ_HIP(launch_stamp(t2, c.st));
             TNSLQ_HIP(launch_swap01(Z2, (int64_t)kcur * f.Up, f.M, f.M, f.V, Z2p, c.st));
         }
         TNSLQ_HIP(launch_zgemm(0, 0, P, Z2p, Z3, kA, (int)MV, (int)UpM, UpM, MV, MV, kcur, 0, UpM * MV, kA * MV,
@@ -1487,6 +1499,7 @@ int mps_matvec(Ctx &c, const double2 *x, int kcur, hipEvent_t e1, hipEvent_t e2)
         return TNSLQ_OK;
     };
     int rc;
+    TNSLQ_HIP(launch_stamp(t1, c.st));
     if (pl.prec == TNSLQ_FP32) {
         TNSLQ_HIP(launch_to_c64(x, (int64_t)kcur * n, c.X32, c.st));
         rc = chain((const float2 *)c.P32, (const float2 *)c.Q32, (const float2 *)c.X32, (float2 *)c.Z1,
@@ -1495,7 +1508,6 @@ int mps_matvec(Ctx &c, const double2 *x, int kcur, hipEvent_t e1, hipEvent_t e2)
         rc = chain((const double2 *)f.P, f.Q, x, c.Z1, c.Z2, c.Z2p, c.Z3, (double2 *)c.Ypart);
     }
     if (rc) return rc;
-    if (e2) TNSLQ_HIP(hipEventRecord(e2, c.st));
     c.n_launch++;
     return TNSLQ_OK;
 }
@@ -1511,7 +1523,7 @@ int mps_matvec(Ctx &c, const double2 *x, int kcur, hipEvent_t e1, hipEvent_t e2)
 //   Y[k][a][b]             = sum_{n', v'} T5[k][a][(n', v')] conj R_B[b][(n', v')]
 // (the last in reduction splits at Ypart, as for the factors).  Each product
 // is batched over the chunk; the regroupings are axis permutations.
-int net_matvec(Ctx &c, const double2 *x, int kcur, hipEvent_t e1, hipEvent_t e2) {
+int net_matvec(Ctx &c, const double2 *x, int kcur, uint64_t *t1, uint64_t *t2) {
     const Plan &pl = c.pl;
     const int64_t n = pl.dAB, U = pl.nU, M = pl.nM, N = pl.nN, V = pl.nV, UM = U * M, NV = N * V, MN = M * N,
                   UV = U * V, big = UM * NV;
@@ -1522,7 +1534,7 @@ int net_matvec(Ctx &c, const double2 *x, int kcur, hipEvent_t e1, hipEvent_t e2)
                      auto *Y) -> int {
         TNSLQ_HIP(launch_zgemm(2, 0, RA, X, T1, (int)UM, kB, kA, UM, kB, kB, kcur, 0, n, UM * kB, c.st));
         TNSLQ_HIP(launch_zgemm(0, 0, T1, RB, Ta, (int)UM, (int)NV, kB, kB, NV, NV, kcur, UM * kB, 0, big, c.st));
-        if (e1) TNSLQ_HIP(hipEventRecord(e1, c.st));
+        TNSLQ_HIP(launch_stamp(t2, c.st));
         auto *T3 = Ta;   // [m][n'][u'][v]
         if (pl.ngap) {
             const int64_t d[4] = {U, M, N, V};
@@ -1557,6 +1569,7 @@ int net_matvec(Ctx &c, const double2 *x, int kcur, hipEvent_t e1, hipEvent_t e2)
         return TNSLQ_OK;
     };
     int rc;
+    TNSLQ_HIP(launch_stamp(t1, c.st));
     if (pl.prec == TNSLQ_FP32) {
         TNSLQ_HIP(launch_to_c64(x, (int64_t)kcur * n, c.X32, c.st));
         rc = chain((const float2 *)c.P32, (const float2 *)c.Q32, (const float2 *)(base + nb.ew32),
@@ -1567,25 +1580,11 @@ int net_matvec(Ctx &c, const double2 *x, int kcur, hipEvent_t e1, hipEvent_t e2)
                    (const double2 *)(base + nb.ezp), x, c.Z1, c.Z2, c.Z2p, c.Z3, (double2 *)c.Ypart);
     }
     if (rc) return rc;
-    if (e2) TNSLQ_HIP(hipEventRecord(e2, c.st));
     c.n_launch++;
     return TNSLQ_OK;
 }
 
-// Events of one Lanczos step: mv0, then per probe chunk (after contraction 1,
-// after contraction 2, after the merge), then mv1 (matvec done), lz1.
-struct StepEvents {
-    std::vector<hipEvent_t> e;
-    int nchunk = 0;
-    hipEvent_t mv0() const { return e[0]; }
-    hipEvent_t c1(int ch) const { return e[1 + 3 * ch]; }
-    hipEvent_t c2(int ch) const { return e[2 + 3 * ch]; }
-    hipEvent_t pa(int ch) const { return e[3 + 3 * ch]; }
-    hipEvent_t mv1() const { return e[1 + 3 * nchunk]; }
-    hipEvent_t lz1() const { return e[2 + 3 * nchunk]; }
-};
-
-int lanczos_step(Ctx &c, int j, StepEvents *se) {
+int lanczos_step(Ctx &c, int j) {
     const Plan &pl = c.pl;
     const int64_t n = pl.dAB;
     const int64_t slot = (int64_t)pl.K * n;
@@ -1595,34 +1594,32 @@ int lanczos_step(Ctx &c, int j, StepEvents *se) {
     double2 *q_next = c.Q + slot_of(j) * slot;
     const int accfp64 = pl.prec == TNSLQ_FP64 || pl.stream;
     int rc;
-    TNSLQ_HIP(hipEventRecord(se->mv0(), c.st));
     for (int k0 = 0, ch = 0; k0 < pl.K; k0 += pl.kc, ++ch) {
         const int kcur = std::min(pl.kc, pl.K - k0);
+        uint64_t *t1 = c.stamps + c.at.c1(j, ch), *t2 = c.stamps + c.at.c2(j, ch);
         if (pl.mpsf) {
-            if ((rc = (pl.mnet ? net_matvec : mps_matvec)(c, q_cur + (int64_t)k0 * n, kcur, se->c1(ch), se->c2(ch))))
-                return rc;
+            if ((rc = (pl.mnet ? net_matvec : mps_matvec)(c, q_cur + (int64_t)k0 * n, kcur, t1, t2))) return rc;
         } else if (pl.expl) {
-            if ((rc = explicit_matvec(c, se->c1(ch), se->c2(ch)))) return rc;
+            if ((rc = explicit_matvec(c, t1))) return rc;
         } else if (pl.stream) {
-            if ((rc = stream_contract(c, q_cur, se->c1(ch), se->c2(ch)))) return rc;
-        } else if ((rc = contract_chunk(c, k0, kcur, se->c1(ch), se->c2(ch)))) {
+            if ((rc = stream_contract(c, q_cur, t1, t2))) return rc;
+        } else if ((rc = contract_chunk(c, k0, kcur, t1, t2))) {
             return rc;
         }
         // the streaming passes leave Y already summed over their splits
         TNSLQ_HIP(launch_passA(accfp64, c.z, pl.stream && !pl.fused ? (const void *)c.Ym : c.Ypart,
                                pl.stream && !pl.fused ? 1 : pl.S,
                                (int64_t)pl.kc * n, k0, kcur, q_prev, q_cur, c.w, c.alpha, c.beta, j, c.dotpart,
-                               c.st));
-        TNSLQ_HIP(hipEventRecord(se->pa(ch), c.st));
+                               c.st, c.stamps + c.at.merge(j, ch)));
     }
-    TNSLQ_HIP(hipEventRecord(se->mv1(), c.st));
+    uint64_t *t3 = c.stamps + c.at.lanczos(j);
     if (pl.reorth)
-        TNSLQ_HIP(launch_reorth(c.z, c.dotpart, c.Q, slot, c.w, c.hpart, c.h, c.alpha, c.beta, j, c.nrmpart, c.st));
+        TNSLQ_HIP(launch_reorth(c.z, c.dotpart, c.Q, slot, c.w, c.hpart, c.h, c.alpha, c.beta, j, c.nrmpart, c.st,
+                                t3));
     else
-        TNSLQ_HIP(launch_passB(c.z, c.dotpart, q_cur, c.w, c.alpha, c.beta, j, c.nrmpart, c.st));
+        TNSLQ_HIP(launch_passB(c.z, c.dotpart, q_cur, c.w, c.alpha, c.beta, j, c.nrmpart, c.st, t3));
     TNSLQ_HIP(launch_passC(pl.prec, c.z, c.nrmpart, c.w, q_next, pl.stream ? nullptr : c.Xt, pl.nst1, c.alpha,
                            c.beta, j, c.st));
-    TNSLQ_HIP(hipEventRecord(se->lz1(), c.st));
     return TNSLQ_OK;
 }
 
@@ -1630,27 +1627,50 @@ int slq_setup(Ctx &c, const void *psi, uint64_t seed, uint64_t offset) {
     const Plan &pl = c.pl;
     int rc;
     if ((rc = do_layout(c, psi))) return rc;
-    TNSLQ_HIP(launch_zero(c.alpha, (size_t)pl.K * pl.m * 8, c.st));
-    TNSLQ_HIP(launch_zero(c.beta, (size_t)pl.K * (pl.m + 1) * 8, c.st));
-    TNSLQ_HIP(launch_zero(c.F, (size_t)pl.K * pl.m * 8, c.st));
     TNSLQ_HIP(launch_probe_init(pl.prec, c.z, seed, offset, pl.swapped, c.Q, pl.stream ? nullptr : c.Xt, pl.nst1,
                                 c.alpha, c.beta, c.st));
     return TNSLQ_OK;
 }
 
-// Quadrature for steps [jlo, jhi] and the statistics of step `jstat`.
-int quad_stats(Ctx &c, int jdone, int jlo, int jhi, int jstat, double *G) {
+// Quadrature for steps [jlo, jhi] and the statistics of step `jstat` (with G)
+// and, where above 0, step `jprev`.
+int quad_stats(Ctx &c, int jdone, int jlo, int jhi, int jstat, int jprev, double *G) {
     const Plan &pl = c.pl;
-    TNSLQ_HIP(launch_steps(c.alpha, c.beta, pl.K, pl.m, jdone, c.steps, c.st));
+    TNSLQ_HIP(launch_steps(c.alpha, c.beta, pl.K, pl.m, jdone, c.steps, c.st, c.stamps + c.at.end(jdone)));
     TNSLQ_HIP(launch_quadrature(c.alpha, c.beta, c.steps, pl.K, pl.m, jlo, jhi, TNSLQ_F_ABS, c.F, c.st));
-    TNSLQ_HIP(launch_stats(c.beta, c.F, pl.K, pl.m, jstat, G, c.stats, c.st));
+    TNSLQ_HIP(launch_stats(c.beta, c.F, pl.K, pl.m, jstat, jprev, G, c.stats, c.st));
     return TNSLQ_OK;
 }
 
-float elapsed(hipEvent_t a, hipEvent_t b) {
-    float ms = 0.f;
-    if (a && b && hipEventElapsedTime(&ms, a, b) == hipSuccess) return ms;
-    return 0.f;
+// Milliseconds per tick of the device clock that kernels stamp.
+double tick_ms() {
+    int dev = 0, khz = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, dev) != hipSuccess || khz <= 0)
+        return 0.0;
+    return 1.0 / khz;
+}
+double elapsed(const uint64_t *t, size_t from, size_t to) {
+    return t[from] && t[to] > t[from] ? (double)(t[to] - t[from]) : 0.0;
+}
+
+// The phases' times of steps 1..jdone added to res, from the run's stamps t.
+// A step ends where the next one's first contraction starts, or where the
+// quadrature after it did.
+void add_times(const Ctx &c, const uint64_t *t, int jdone, tnslq_result *res) {
+    const Stamps &at = c.at;
+    const double ms = tick_ms();
+    for (int j = 1; j <= jdone; ++j) {
+        const size_t end = t[at.end(j)] || j == jdone ? at.end(j) : at.c1(j + 1, 0);
+        res->t_matvec_ms += ms * elapsed(t, at.c1(j, 0), at.lanczos(j));
+        for (int ch = 0; ch < at.nchunk; ++ch) {
+            // one kernel for both contractions: all in the second
+            const size_t mid = t[at.c2(j, ch)] ? at.c2(j, ch) : at.c1(j, ch);
+            res->t_contract1_ms += ms * elapsed(t, at.c1(j, ch), mid);
+            res->t_contract2_ms += ms * elapsed(t, mid, at.merge(j, ch));
+        }
+        res->t_lanczos_ms += ms * elapsed(t, at.lanczos(j), end);
+    }
 }
 
 void zero_result(tnslq_result *res) {
@@ -1676,8 +1696,9 @@ int trivial(const tnslq_options *opt, tnslq_result *res, double *G, double *alph
 // The estimate needs a normalised state (Tr rho_AB = 1, Eq. 1); psi is
 // checked, not silently renormalised: its non-finite amplitudes and its
 // squared norm are read back once before the Lanczos steps.  Synchronises.
-int check_state(int dtype, const void *psi, int64_t D, double *scratch, hipStream_t st) {
-    TNSLQ_HIP(launch_state_check(dtype, psi, D, scratch, st));
+// The kernels go in front of the regrouping and the values are read behind it,
+// so that the stream has work while the host waits.
+int check_state(int dtype, const double *scratch, hipStream_t st) {
     double h[2];
     TNSLQ_HIP(hipMemcpyAsync(h, scratch + 2 * STATE_CHECK_BLOCKS, sizeof h, hipMemcpyDeviceToHost, st));
     TNSLQ_HIP(hipStreamSynchronize(st));
@@ -1718,8 +1739,6 @@ struct Timer {
 // Shared body of tnslq_logneg and tnslq_logneg_surrogate.
 struct Run {
     Ctx c;
-    std::vector<StepEvents> se;
-    hipEvent_t e_start = nullptr, e_layout = nullptr;
     int jdone = 0;
     int rule = TNSLQ_STOP_DIFF;
     double lanczos_err = 0.0;   // of the last stop check
@@ -1748,25 +1767,15 @@ int run_start(Run &r, const tnslq_options *opt, const void *psi, void *ws, size_
         return fail(TNSLQ_E_WORKSPACE, "workspace %zu bytes, need %zu", ws_bytes, r.c.pl.total);
     bind(r.c, ws, (hipStream_t)stream);
     r.rule = opt->stop_rule;
-    r.e_start = r.c.event();
-    r.e_layout = r.c.event();
-    r.se.resize(opt->n_steps + 1);
-    const int nchunk = (r.c.pl.K + r.c.pl.kc - 1) / r.c.pl.kc;
-    for (auto &s : r.se) {
-        s.nchunk = nchunk;
-        s.e.resize(3 + 3 * nchunk);
-        for (auto &e : s.e)
-            if (!(e = r.c.event())) return fail(TNSLQ_E_DEVICE, "hipEventCreate failed");
-    }
-    TNSLQ_HIP(hipEventRecord(r.e_start, r.c.st));
-    if (!r.c.pl.mpsf && (rc = check_state(r.c.pl.dtype, psi, r.c.pl.D, (double *)(r.c.ws + r.c.pl.off_chk), r.c.st)))
-        return rc;
+    double *chk = (double *)(r.c.ws + r.c.pl.off_chk);
+    TNSLQ_HIP(launch_zero(r.c.alpha, r.c.pl.end_out - r.c.pl.off_alpha, r.c.st));
+    TNSLQ_HIP(launch_stamp(r.c.stamps, r.c.st));
+    if (!r.c.pl.mpsf) TNSLQ_HIP(launch_state_check(r.c.pl.dtype, psi, r.c.pl.D, chk, r.c.st));
     roctxRangePush("tnslq layout");
     rc = slq_setup(r.c, psi, opt->seed, opt->probe_offset);
     roctxRangePop();
     if (rc) return rc;
-    TNSLQ_HIP(hipEventRecord(r.e_layout, r.c.st));
-    return TNSLQ_OK;
+    return r.c.pl.mpsf ? TNSLQ_OK : check_state(r.c.pl.dtype, chk, r.c.st);
 }
 
 // Fitted estimate of every probe after step j (exponential fit, Sec. III):
@@ -1774,7 +1783,7 @@ int run_start(Run &r, const tnslq_options *opt, const void *psi, void *ws, size_
 int fit_step(Run &r, int j, double *G) {
     Ctx &c = r.c;
     const int lo = std::max(2, j - TNSLQ_FIT_WINDOW + 1);
-    TNSLQ_HIP(launch_steps(c.alpha, c.beta, c.pl.K, c.pl.m, j, c.steps, c.st));
+    TNSLQ_HIP(launch_steps(c.alpha, c.beta, c.pl.K, c.pl.m, j, c.steps, c.st, c.stamps + c.at.end(j)));
     TNSLQ_HIP(launch_quadrature(c.alpha, c.beta, c.steps, c.pl.K, c.pl.m, lo, j, TNSLQ_F_ABS, c.F, c.st));
     TNSLQ_HIP(launch_fit(c.alpha, c.beta, c.F, c.pl.K, c.pl.m, j, c.finf, c.fsig, G, c.fitout, c.st));
     return TNSLQ_OK;
@@ -1789,7 +1798,7 @@ int run_steps(Run &r, int jmax, double stop_tol, bool lanczos_only = false) {
     r.met = false;
     for (int j = r.jdone + 1; j <= jmax; ++j) {
         roctxRangePush("tnslq lanczos step");
-        rc = lanczos_step(r.c, j, &r.se[j]);
+        rc = lanczos_step(r.c, j);
         roctxRangePop();
         if (rc) return rc;
         r.jdone = j;
@@ -1806,15 +1815,11 @@ int run_steps(Run &r, int jmax, double stop_tol, bool lanczos_only = false) {
                 break;
             }
         } else if (r.rule == TNSLQ_STOP_DIFF && j >= 6) {
-            if ((rc = quad_stats(r.c, j, j - 5, j, j - 5, nullptr))) return rc;
-            TNSLQ_HIP(launch_stats(r.c.beta, r.c.F, r.c.pl.K, r.c.pl.m, j, nullptr, r.c.stats, r.c.st));
-            double s[8];
-            TNSLQ_HIP(hipMemcpyAsync(s, r.c.stats + (size_t)(j - 6) * 4, 4 * sizeof(double), hipMemcpyDeviceToHost,
-                                     r.c.st));
-            TNSLQ_HIP(hipMemcpyAsync(s + 4, r.c.stats + (size_t)(j - 1) * 4, 4 * sizeof(double),
-                                     hipMemcpyDeviceToHost, r.c.st));
+            if ((rc = quad_stats(r.c, j, j - 5, j, j, j - 5, nullptr))) return rc;
+            double s[24];   // the statistics of steps j - 5 .. j
+            TNSLQ_HIP(hipMemcpyAsync(s, r.c.stats + (size_t)(j - 6) * 4, sizeof s, hipMemcpyDeviceToHost, r.c.st));
             TNSLQ_HIP(hipStreamSynchronize(r.c.st));
-            const double e_now = s[6], de = s[7], e_old = s[2];
+            const double e_now = s[22], de = s[23], e_old = s[2];
             const double dl = e_now - e_old;
             const double err = std::sqrt((std::isnan(de) ? 0.0 : de * de) + dl * dl);
             if (std::isfinite(e_now) && err <= stop_tol * std::max(std::fabs(e_now), 1.0)) {
@@ -1826,8 +1831,10 @@ int run_steps(Run &r, int jmax, double stop_tol, bool lanczos_only = false) {
     return TNSLQ_OK;
 }
 
+// The results of a run; have_quadrature: quad_stats has run for every step up
+// to the last, with its G.
 int run_finish(Run &r, tnslq_result *res, double *G, double *alpha, double *beta, double *F, int *steps,
-               const Timer &tm) {
+               const Timer &tm, bool have_quadrature = false) {
     Ctx &c = r.c;
     const Plan &pl = c.pl;
     int rc;
@@ -1837,27 +1844,40 @@ int run_finish(Run &r, tnslq_result *res, double *G, double *alpha, double *beta
     // trajectory that has not settled can be far off), with the fit's
     // Lanczos error as the measure of how far it is from converged.
     const bool plain = !fit || (r.target && !r.met);
-    // quadrature of every step and the plain statistics of each step (G at the
-    // last step unless the fit supplies it)
-    if ((rc = quad_stats(c, r.jdone, 1, r.jdone, r.jdone, plain ? c.G : nullptr))) return rc;
+    // quadrature of every step and the plain statistics of the last (G there
+    // unless the fit supplies it) and of the one five steps earlier
+    const int jprev = !fit && r.jdone >= 6 ? r.jdone - 5 : 0;
+    if (!(plain && have_quadrature) &&
+        (rc = quad_stats(c, r.jdone, 1, r.jdone, r.jdone, jprev, plain ? c.G : nullptr)))
+        return rc;
     if (fit && (rc = fit_step(r, r.jdone, plain ? nullptr : c.G))) return rc;
-    double s[4], o[6], e_old = std::nan("");
-    TNSLQ_HIP(hipMemcpyAsync(s, c.stats + (size_t)(r.jdone - 1) * 4, sizeof s, hipMemcpyDeviceToHost, c.st));
-    if (fit) TNSLQ_HIP(hipMemcpyAsync(o, c.fitout, sizeof o, hipMemcpyDeviceToHost, c.st));
-    if (!fit && r.jdone >= 6) {
-        TNSLQ_HIP(launch_stats(c.beta, c.F, pl.K, pl.m, r.jdone - 5, nullptr, c.stats, c.st));
-        TNSLQ_HIP(hipMemcpyAsync(&e_old, c.stats + (size_t)(r.jdone - 6) * 4 + 2, sizeof(double),
-                                 hipMemcpyDeviceToHost, c.st));
-    }
-    std::vector<int> hsteps(pl.K);
-    TNSLQ_HIP(hipMemcpyAsync(hsteps.data(), c.steps, sizeof(int) * pl.K, hipMemcpyDeviceToHost, c.st));
-    if (G) TNSLQ_HIP(hipMemcpyAsync(G, c.G, sizeof(double) * pl.K, hipMemcpyDeviceToHost, c.st));
-    if (alpha) TNSLQ_HIP(hipMemcpyAsync(alpha, c.alpha, sizeof(double) * pl.K * pl.m, hipMemcpyDeviceToHost, c.st));
-    if (beta)
-        TNSLQ_HIP(hipMemcpyAsync(beta, c.beta, sizeof(double) * pl.K * (pl.m + 1), hipMemcpyDeviceToHost, c.st));
-    if (F) TNSLQ_HIP(hipMemcpyAsync(F, c.F, sizeof(double) * pl.K * pl.m, hipMemcpyDeviceToHost, c.st));
+    // one copy of the small results, with the arrays in front of them where
+    // all are asked for and small
+    const bool all = alpha && beta && F && pl.end_out - pl.off_alpha <= (size_t(1) << 20);
+    const size_t from = all ? pl.off_alpha : pl.off_stats;
+    std::vector<char> host(pl.end_out - from);
+    auto at_off = [&](size_t off) { return host.data() + (off - from); };
+    TNSLQ_HIP(hipMemcpyAsync(host.data(), c.ws + from, host.size(), hipMemcpyDeviceToHost, c.st));
+    auto array = [&](double *out, size_t off, size_t count) -> hipError_t {
+        return out && !all ? hipMemcpyAsync(out, c.ws + off, count * 8, hipMemcpyDeviceToHost, c.st) : hipSuccess;
+    };
+    const size_t na = (size_t)pl.K * pl.m, nb = (size_t)pl.K * (pl.m + 1);
+    TNSLQ_HIP(array(alpha, pl.off_alpha, na));
+    TNSLQ_HIP(array(beta, pl.off_beta, nb));
+    TNSLQ_HIP(array(F, pl.off_F, na));
     TNSLQ_HIP(hipStreamSynchronize(c.st));
-    if (steps) std::copy(hsteps.begin(), hsteps.end(), steps);
+    if (all) {
+        memcpy(alpha, at_off(pl.off_alpha), na * 8);
+        memcpy(beta, at_off(pl.off_beta), nb * 8);
+        memcpy(F, at_off(pl.off_F), na * 8);
+    }
+    const double *stats = (const double *)at_off(pl.off_stats), *s = stats + (size_t)(r.jdone - 1) * 4;
+    const double *o = (const double *)at_off(pl.off_fit) + 2 * (size_t)pl.K;
+    const double e_old = jprev ? stats[(size_t)(jprev - 1) * 4 + 2] : std::nan("");
+    const int *hsteps = (const int *)at_off(pl.off_steps);
+    const uint64_t *t = (const uint64_t *)at_off(pl.off_stamp);
+    if (G) memcpy(G, at_off(pl.off_G), sizeof(double) * pl.K);
+    if (steps) std::copy(hsteps, hsteps + pl.K, steps);
     zero_result(res);
     if (!plain) {
         const double ln2 = std::log(2.0);
@@ -1877,7 +1897,7 @@ int run_finish(Run &r, tnslq_result *res, double *G, double *alpha, double *beta
             res->lanczos_err = r.jdone >= 6 ? std::fabs(s[2] - e_old) : std::nan("");
     }
     res->steps_done = r.jdone;
-    res->steps_min = *std::min_element(hsteps.begin(), hsteps.end());
+    res->steps_min = *std::min_element(hsteps, hsteps + pl.K);
     res->swapped_ab = pl.swapped;
     res->streamed = pl.stream ? (pl.fused ? 2 : 1) : 0;
     res->explicit_operator = pl.expl;
@@ -1885,16 +1905,8 @@ int run_finish(Run &r, tnslq_result *res, double *G, double *alpha, double *beta
     res->n_probes_used = pl.K;
     res->n_matvecs = r.jdone;
     res->n_contract_launches = c.n_launch;
-    res->t_layout_ms = elapsed(r.e_start, r.e_layout);
-    for (int j = 1; j <= r.jdone; ++j) {
-        const StepEvents &e = r.se[j];
-        res->t_matvec_ms += elapsed(e.mv0(), e.mv1());
-        for (int ch = 0; ch < e.nchunk; ++ch) {
-            res->t_contract1_ms += elapsed(ch == 0 ? e.mv0() : e.pa(ch - 1), e.c1(ch));
-            res->t_contract2_ms += elapsed(e.c1(ch), e.c2(ch));
-        }
-        res->t_lanczos_ms += elapsed(e.mv1(), e.lz1());
-    }
+    res->t_layout_ms = tick_ms() * elapsed(t, 0, c.at.c1(1, 0));
+    add_times(c, t, r.jdone, res);
     res->t_total_ms = tm.ms();
     if (!std::isfinite(res->logneg))
         return fail(TNSLQ_E_NONFINITE, "estimate is not finite (trace norm %g)", res->trace_norm);
@@ -1913,7 +1925,7 @@ struct SPlan {
     int K = 1, m = 1, reorth = 0;
     int S1 = 1, S2 = 1, nblk = 1, nQ = 3;
     size_t off_P1 = 0, off_P2 = 0, off_Zp = 0, off_Z = 0, off_Yp = 0, off_Q = 0, off_w = 0, off_alpha = 0, off_beta = 0;
-    size_t off_F = 0, off_G = 0, off_stats = 0, off_red = 0, off_h = 0, off_steps = 0, off_chk = 0, total = 0;
+    size_t off_F = 0, off_G = 0, off_stats = 0, off_red = 0, off_h = 0, off_steps = 0, off_chk = 0, off_stamp = 0, total = 0;
 };
 
 int check_subsystem(int L, const int *s, int n_s) {
@@ -1988,6 +2000,7 @@ int make_splan(int dtype, int L, const int *s, int n_s, const tnslq_options *opt
     sp.off_alpha = take((size_t)K * m * 8);
     sp.off_beta = take((size_t)K * (m + 1) * 8);
     sp.off_F = take((size_t)K * m * 8);
+    sp.off_stamp = take(Stamps{1}.count(m) * 8);
     sp.off_G = take((size_t)K * 8);
     sp.off_stats = take((size_t)m * 4 * 8);
     sp.off_red = take((size_t)2 * K * sp.nblk * 8);
@@ -2030,64 +2043,47 @@ int spectral_run(const SPlan &sp, const void *psi, const tnslq_options *opt, uin
     int *steps = (int *)(base + sp.off_steps);
     const LzDims z{sp.d, 1, sp.d, sp.K, sp.m, sp.nblk};
     const int64_t n = sp.d, slot = (int64_t)sp.K * n;
-    std::vector<hipEvent_t> ev;
-    struct Guard {
-        std::vector<hipEvent_t> &e;
-        ~Guard() {
-            for (auto x : e) (void)hipEventDestroy(x);
-        }
-    } guard{ev};
-    auto event = [&]() {
-        hipEvent_t e = nullptr;
-        if (hipEventCreate(&e) == hipSuccess) ev.push_back(e);
-        return e;
-    };
-    hipEvent_t e0 = event(), e1 = event();
-    std::vector<hipEvent_t> mv0(sp.m + 1), mv1(sp.m + 1), lz1(sp.m + 1);
-    for (int j = 1; j <= sp.m; ++j) {
-        mv0[j] = event();
-        mv1[j] = event();
-        lz1[j] = event();
-    }
-    if ((int)ev.size() != 2 + 3 * sp.m) return fail(TNSLQ_E_DEVICE, "hipEventCreate failed");
-    int rc0;
-    if ((rc0 = check_state(sp.dtype, psi, sp.D, (double *)(base + sp.off_chk), st))) return rc0;
-    TNSLQ_HIP(hipEventRecord(e0, st));
+    double *chk = (double *)(base + sp.off_chk);
+    uint64_t *stamps = (uint64_t *)(base + sp.off_stamp);
+    const Stamps at{1};
+    TNSLQ_HIP(launch_zero(alpha, sp.off_stamp + at.count(sp.m) * 8 - sp.off_alpha, st));
+    TNSLQ_HIP(launch_state_check(sp.dtype, psi, sp.D, chk, st));
+    TNSLQ_HIP(launch_stamp(stamps, st));
     const PermDesc p1 = perm_two(sp.L, sp.side, sp.n_side, sp.rest, sp.n_rest);
     const PermDesc p2 = perm_two(sp.L, sp.rest, sp.n_rest, sp.side, sp.n_side);
     TNSLQ_HIP(launch_regroup(sp.dtype, psi, P1, sp.d, sp.dR, p1, st));
     TNSLQ_HIP(launch_regroup(sp.dtype, psi, P2, sp.dR, sp.d, p2, st));
-    TNSLQ_HIP(launch_zero(alpha, (size_t)sp.K * sp.m * 8, st));
-    TNSLQ_HIP(launch_zero(beta, (size_t)sp.K * (sp.m + 1) * 8, st));
-    TNSLQ_HIP(launch_zero(F, (size_t)sp.K * sp.m * 8, st));
     TNSLQ_HIP(launch_probe_init(TNSLQ_FP64, z, opt->seed, offset, 0, Q, nullptr, 0, alpha, beta, st));
-    TNSLQ_HIP(hipEventRecord(e1, st));
+    int rc0;
+    if ((rc0 = check_state(sp.dtype, chk, st))) return rc0;
     auto slot_of = [&](int jj) { return sp.reorth ? jj : jj % 3; };
     for (int j = 1; j <= sp.m; ++j) {
         double2 *q_cur = Q + slot_of(j - 1) * slot;
         double2 *q_prev = j > 1 ? Q + slot_of(j - 2) * slot : q_cur;
         double2 *q_next = Q + slot_of(j) * slot;
-        TNSLQ_HIP(hipEventRecord(mv0[j], st));
         // Z = Psi^dagger q over P1 (d x d_R); Y = Psi Z over P2 = Psi^T (d_R x d)
-        TNSLQ_HIP(launch_colmac(sp.dtype, 1, plain_colmac(P1, sp.d, sp.dR, q_cur, sp.K, Zp, sp.S1), st));
+        ColmacDesc g1 = plain_colmac(P1, sp.d, sp.dR, q_cur, sp.K, Zp, sp.S1);
+        g1.start = stamps + at.c1(j, 0);
+        TNSLQ_HIP(launch_colmac(sp.dtype, 1, g1, st));
         TNSLQ_HIP(launch_sum_splits(Zp, sp.S1, (int64_t)sp.K * sp.dR, Z, st));
         TNSLQ_HIP(launch_colmac(sp.dtype, 0, plain_colmac(P2, sp.dR, sp.d, Z, sp.K, Yp, sp.S2), st));
-        TNSLQ_HIP(hipEventRecord(mv1[j], st));
-        TNSLQ_HIP(launch_passA(1, z, Yp, sp.S2, slot, 0, sp.K, q_prev, q_cur, w, alpha, beta, j, dotpart, st));
+        TNSLQ_HIP(launch_passA(1, z, Yp, sp.S2, slot, 0, sp.K, q_prev, q_cur, w, alpha, beta, j, dotpart, st,
+                               stamps + at.lanczos(j)));
         if (sp.reorth)
             TNSLQ_HIP(launch_reorth(z, dotpart, Q, slot, w, hpart, h, alpha, beta, j, nrmpart, st));
         else
             TNSLQ_HIP(launch_passB(z, dotpart, q_cur, w, alpha, beta, j, nrmpart, st));
         TNSLQ_HIP(launch_passC(TNSLQ_FP64, z, nrmpart, w, q_next, nullptr, 0, alpha, beta, j, st));
-        TNSLQ_HIP(hipEventRecord(lz1[j], st));
     }
-    TNSLQ_HIP(launch_steps(alpha, beta, sp.K, sp.m, sp.m, steps, st));
+    TNSLQ_HIP(launch_steps(alpha, beta, sp.K, sp.m, sp.m, steps, st, stamps + at.end(sp.m)));
     TNSLQ_HIP(launch_quadrature(alpha, beta, steps, sp.K, sp.m, 1, sp.m, sp.fn, F, st));
-    TNSLQ_HIP(launch_stats(beta, F, sp.K, sp.m, sp.m, G, stats, st));
+    TNSLQ_HIP(launch_stats(beta, F, sp.K, sp.m, sp.m, 0, G, stats, st));
     double sv[4];
     std::vector<int> hsteps(sp.K);
+    std::vector<uint64_t> t(at.count(sp.m));
     TNSLQ_HIP(hipMemcpyAsync(sv, stats + (size_t)(sp.m - 1) * 4, sizeof sv, hipMemcpyDeviceToHost, st));
     TNSLQ_HIP(hipMemcpyAsync(hsteps.data(), steps, sizeof(int) * sp.K, hipMemcpyDeviceToHost, st));
+    TNSLQ_HIP(hipMemcpyAsync(t.data(), stamps, t.size() * 8, hipMemcpyDeviceToHost, st));
     if (Gh) TNSLQ_HIP(hipMemcpyAsync(Gh, G, sizeof(double) * sp.K, hipMemcpyDeviceToHost, st));
     if (alh) TNSLQ_HIP(hipMemcpyAsync(alh, alpha, sizeof(double) * sp.K * sp.m, hipMemcpyDeviceToHost, st));
     if (beh) TNSLQ_HIP(hipMemcpyAsync(beh, beta, sizeof(double) * sp.K * (sp.m + 1), hipMemcpyDeviceToHost, st));
@@ -2101,10 +2097,11 @@ int spectral_run(const SPlan &sp, const void *psi, const tnslq_options *opt, uin
     res->steps_min = *std::min_element(hsteps.begin(), hsteps.end());
     res->complement = sp.complement;
     res->n_qubits_side = sp.n_side;
-    res->t_layout_ms = elapsed(e0, e1);
+    const double ms = tick_ms();
+    res->t_layout_ms = ms * elapsed(t.data(), 0, at.c1(1, 0));
     for (int j = 1; j <= sp.m; ++j) {
-        res->t_matvec_ms += elapsed(mv0[j], mv1[j]);
-        res->t_lanczos_ms += elapsed(mv1[j], lz1[j]);
+        res->t_matvec_ms += ms * elapsed(t.data(), at.c1(j, 0), at.lanczos(j));
+        res->t_lanczos_ms += ms * elapsed(t.data(), at.lanczos(j), j < sp.m ? at.c1(j + 1, 0) : at.end(j));
     }
     res->t_total_ms = tm.ms();
     if (!std::isfinite(res->value)) return fail(TNSLQ_E_NONFINITE, "estimate is not finite");
@@ -2271,15 +2268,16 @@ int run_probe_loop(Run &r, const tnslq_options *opt, tnslq_result *res, double *
     std::vector<double> Gall, Sall, g(K), sg(K);
     std::vector<int> hsteps(K);
     int steps_min = pl.m, jmax = 0, nmv = 0;
-    double tmv = 0.0, tc1 = 0.0, tc2 = 0.0, tlz = 0.0;
+    tnslq_result times;
+    zero_result(&times);
+    std::vector<uint64_t> t(c.at.count(pl.m));
+    double t_layout = 0.0;
     double T = 0.0, se = std::nan(""), epsl = 0.0, E = std::nan(""), de = INFINITY;
     int rc;
     for (int b = 0;; ++b) {
         if (b > 0) {
             // the next block: fresh probes on the same regrouped psi
-            TNSLQ_HIP(launch_zero(c.alpha, (size_t)K * pl.m * 8, c.st));
-            TNSLQ_HIP(launch_zero(c.beta, (size_t)K * (pl.m + 1) * 8, c.st));
-            TNSLQ_HIP(launch_zero(c.F, (size_t)K * pl.m * 8, c.st));
+            TNSLQ_HIP(launch_zero(c.alpha, pl.end_out - pl.off_alpha, c.st));
             TNSLQ_HIP(launch_probe_init(pl.prec, c.z, opt->seed, opt->probe_offset + (uint64_t)b * K, pl.swapped,
                                         c.Q, pl.stream ? nullptr : c.Xt, pl.nst1, c.alpha, c.beta, c.st));
             r.jdone = 0;
@@ -2289,16 +2287,10 @@ int run_probe_loop(Run &r, const tnslq_options *opt, tnslq_result *res, double *
         TNSLQ_HIP(hipMemcpyAsync(g.data(), c.G, sizeof(double) * K, hipMemcpyDeviceToHost, c.st));
         TNSLQ_HIP(hipMemcpyAsync(sg.data(), c.fsig, sizeof(double) * K, hipMemcpyDeviceToHost, c.st));
         TNSLQ_HIP(hipMemcpyAsync(hsteps.data(), c.steps, sizeof(int) * K, hipMemcpyDeviceToHost, c.st));
+        TNSLQ_HIP(hipMemcpyAsync(t.data(), c.stamps, t.size() * 8, hipMemcpyDeviceToHost, c.st));
         TNSLQ_HIP(hipStreamSynchronize(c.st));
-        for (int j = 1; j <= r.jdone; ++j) {
-            const StepEvents &e = r.se[j];
-            tmv += elapsed(e.mv0(), e.mv1());
-            for (int ch = 0; ch < e.nchunk; ++ch) {
-                tc1 += elapsed(ch == 0 ? e.mv0() : e.pa(ch - 1), e.c1(ch));
-                tc2 += elapsed(e.c1(ch), e.c2(ch));
-            }
-            tlz += elapsed(e.mv1(), e.lz1());
-        }
+        if (b == 0) t_layout = tick_ms() * elapsed(t.data(), 0, c.at.c1(1, 0));
+        add_times(c, t.data(), r.jdone, &times);
         nmv += r.jdone;
         jmax = std::max(jmax, r.jdone);
         for (int k = 0; k < K; ++k) {
@@ -2325,7 +2317,7 @@ int run_probe_loop(Run &r, const tnslq_options *opt, tnslq_result *res, double *
         if (std::isfinite(E) && std::isfinite(de) && de <= opt->stop_tol * std::max(std::fabs(E), 1.0)) break;
         if ((int64_t)(b + 2) * K > opt->max_probes) break;
     }
-    zero_result(res);
+    *res = times;
     res->trace_norm = T;
     res->trace_norm_se = se;
     res->logneg = E;
@@ -2340,11 +2332,7 @@ int run_probe_loop(Run &r, const tnslq_options *opt, tnslq_result *res, double *
     res->n_probes_used = (int)Gall.size();
     res->n_matvecs = nmv;
     res->n_contract_launches = c.n_launch;
-    res->t_layout_ms = elapsed(r.e_start, r.e_layout);
-    res->t_matvec_ms = tmv;
-    res->t_contract1_ms = tc1;
-    res->t_contract2_ms = tc2;
-    res->t_lanczos_ms = tlz;
+    res->t_layout_ms = t_layout;
     if (G_host) std::copy(Gall.begin(), Gall.end(), G_host);
     res->t_total_ms = tm.ms();
     if (!std::isfinite(res->logneg))
@@ -2836,7 +2824,7 @@ int tnslq_logneg_surrogate(const void *psi_dev, int dtype, const tnslq_partition
     if ((rc = run_steps(r, early_steps, 0.0))) return rc;
     Ctx &c = r.c;
     const Plan &pl = c.pl;
-    if ((rc = quad_stats(c, r.jdone, r.jdone, r.jdone, r.jdone, nullptr))) return rc;
+    if ((rc = quad_stats(c, r.jdone, 1, r.jdone, r.jdone, r.jdone >= 6 ? r.jdone - 5 : 0, c.G))) return rc;
     // features in the caller's roles (log2 d_A, log2 d_B as given)
     const double dA = double(int64_t(1) << part->n_a), dB = double(int64_t(1) << part->n_b);
     TNSLQ_HIP(launch_features(c.alpha, c.beta, pl.K, pl.m, early_steps, double(pl.dAB), dA, dB, double(pl.dE), c.feat,
@@ -2855,7 +2843,7 @@ int tnslq_logneg_surrogate(const void *psi_dev, int dtype, const tnslq_partition
     info[1] = sigma;
     info[2] = e_early;
     if (std::isfinite(mu) && std::isfinite(sigma) && sigma <= tol * std::max(std::fabs(mu), 1.0)) {
-        if ((rc = run_finish(r, res, nullptr, nullptr, nullptr, nullptr, nullptr, tm))) return rc;
+        if ((rc = run_finish(r, res, nullptr, nullptr, nullptr, nullptr, nullptr, tm, true))) return rc;
         res->logneg = mu;
         res->logneg_se = sigma;
         info[3] = 0.0;

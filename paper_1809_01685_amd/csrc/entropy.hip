@@ -146,6 +146,7 @@ __device__ inline void load_pair(const void *M, int64_t e, double2 &a, double2 &
 // read serving two columns.
 template <int DTYPE, bool CONJ, int KG, bool WIDE>
 __global__ void __launch_bounds__(CM_THREADS) k_colmac(ColmacDesc g) {
+    stamp(g.start);
     constexpr int U = 8;                      // rows whose loads are issued together
     constexpr int CM_CH = WIDE ? 64 : 256;    // rows of vector entries staged per chunk
     __shared__ double2 vs[KG][CM_CH];
@@ -246,6 +247,7 @@ __global__ void __launch_bounds__(CM_THREADS) k_colmac(ColmacDesc g) {
 // per SIMD with 8 vectors.
 template <int DTYPE, bool CONJ, int KG>
 __global__ void __launch_bounds__(CM_THREADS) k_colmac_plain(ColmacDesc g) {
+    stamp(g.start);
     constexpr int U = 8, CH = 64;
     __shared__ double2 vs[KG][CH];
     const int t = threadIdx.x;
@@ -322,6 +324,7 @@ __global__ void __launch_bounds__(CM_THREADS) k_colmac_plain(ColmacDesc g) {
 // column l % 16, in register r.
 template <int DTYPE, bool CONJ, int NVG>
 __global__ void __launch_bounds__(CM_THREADS) k_colmac_mfma(ColmacDesc g) {
+    stamp(g.start);
     typedef __attribute__((ext_vector_type(4))) double f64x4;
     constexpr int KG = 8 * NVG, CH = 64;        // vectors per group, vector rows staged per chunk
     constexpr int NQ = 2 / NVG;                 // 32-column runs per wave
@@ -433,7 +436,8 @@ __global__ void __launch_bounds__(256) k_sum_transpose_ups(const double2 *__rest
 // The streaming partial-transpose matvec's first pass takes its vectors over
 // a': Lanczos vectors xq[k][a dB + b] -> Xq[(k, b)][a], K dA dB elements.
 __global__ void __launch_bounds__(256) k_vectors_by_b(const double2 *__restrict__ xq, int64_t total, int64_t dA,
-                                                      int nB, double2 *__restrict__ Xq) {
+                                                      int nB, double2 *__restrict__ Xq, uint64_t *start) {
+    stamp(start);
     const int64_t dB = int64_t(1) << nB, n = dA * dB;
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += stride) {
@@ -462,11 +466,12 @@ __global__ void __launch_bounds__(256) k_sum_transpose_y(const double2 *__restri
 
 }  // namespace
 
-hipError_t launch_vectors_by_b(const double2 *xq, int K, int64_t dA, int nB, double2 *Xq, hipStream_t st) {
+hipError_t launch_vectors_by_b(const double2 *xq, int K, int64_t dA, int nB, double2 *Xq, hipStream_t st,
+                               uint64_t *start) {
     const int64_t total = (int64_t)K * dA * (int64_t(1) << nB);
     int64_t g = (total + 255) / 256;
     if (g > 8192) g = 8192;
-    hipLaunchKernelGGL(k_vectors_by_b, dim3((unsigned)g), dim3(256), 0, st, xq, total, dA, nB, Xq);
+    hipLaunchKernelGGL(k_vectors_by_b, dim3((unsigned)g), dim3(256), 0, st, xq, total, dA, nB, Xq, start);
     return hipGetLastError();
 }
 

@@ -202,6 +202,7 @@ __device__ inline TileAt tile_of(const GemmDesc &g) {
 
 template <int PREC>
 __global__ void __launch_bounds__(NT, 1) k_cgemm_nt_mfma(GemmDesc g) {
+    stamp(g.start);
     using Acc = typename MP<PREC>::acc;
     extern __shared__ __attribute__((aligned(16))) char lds[];
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
@@ -269,6 +270,7 @@ __device__ __forceinline__ void unroll_from(F &f) {
 }
 
 __global__ void __launch_bounds__(NT, 1) k_cgemm_bf16x3(GemmDesc g) {
+    stamp(g.start);
     __shared__ __attribute__((aligned(16))) char lA0[PHB], lA1[PHB], lA2[PHB], lA3[PHB];
     __shared__ __attribute__((aligned(16))) char lB0[PHB], lB1[PHB], lB2[PHB], lB3[PHB];
     const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
@@ -501,6 +503,7 @@ constexpr int X6_FLUSH = 2;
 static_assert(X6_TM == 2 && X6_TN == 2 && X6_NT == 512, "32 x 32 per wave");
 
 __global__ void __launch_bounds__(X6_NT, 1) k_cgemm_bf16x6(GemmDesc g) {
+    stamp(g.start);
     constexpr int NPL = 6;
     constexpr int ABRICK = NPL * TILEB;        // A's brick, all planes: 48 KiB
     constexpr int BHALF = TILEB / 2;           // 64 rows of one plane of B: 4 KiB

@@ -20,6 +20,7 @@ constexpr int THIN_WAVES = 4;
 
 template <int PREC, int NTC>
 __global__ void __launch_bounds__(64 * THIN_WAVES) k_thin_product(GemmDesc g) {
+    stamp(g.start);
     using Acc = typename MP<PREC>::acc;
     constexpr int NPL = MP<PREC>::NPL, BRICKB = NPL * TILEB;
     constexpr int FLUSH = PREC == TNSLQ_FP32 ? 4 : 1 << 30;   // bricks per restart (64 terms)

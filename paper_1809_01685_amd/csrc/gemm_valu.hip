@@ -66,6 +66,7 @@ constexpr int BM = 64, BN = 64, BK = 16;
 
 template <int PREC>
 __global__ void __launch_bounds__(256) k_cgemm_nt_valu(GemmDesc g) {
+    stamp(g.start);
     using T = typename Pol<PREC>::T;
     __shared__ Elem<PREC> As[BK][BM + 1];
     __shared__ Elem<PREC> Bs[BK][BN + 1];

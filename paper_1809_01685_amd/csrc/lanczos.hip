@@ -88,8 +88,9 @@ __global__ void __launch_bounds__(256) k_passA(const AccT *__restrict__ part, in
                                                const double2 *__restrict__ q_cur, double2 *__restrict__ w,
                                                const double *__restrict__ alpha,
                                                const double *__restrict__ beta, int m, int j, int nblk,
-                                               double *__restrict__ dotpart) {
+                                               double *__restrict__ dotpart, uint64_t *start) {
     __shared__ double sh[16];
+    stamp(start);
     const int kl = blockIdx.y, k = k0 + kl;
     const double *ak = alpha + (int64_t)k * m;
     const double *bk = beta + (int64_t)k * (m + 1);
@@ -124,8 +125,10 @@ __global__ void __launch_bounds__(256) k_passA(const AccT *__restrict__ part, in
 __global__ void __launch_bounds__(256) k_passB(const double *__restrict__ dotpart, int64_t n,
                                                const double2 *__restrict__ q_cur, double2 *__restrict__ w,
                                                double *__restrict__ alpha, const double *__restrict__ beta,
-                                               int m, int j, int nblk, double *__restrict__ nrmpart) {
+                                               int m, int j, int nblk, double *__restrict__ nrmpart,
+                                               uint64_t *start) {
     __shared__ double sh[16];
+    stamp(start);
     const int k = blockIdx.y;
     const double *ak = alpha + (int64_t)k * m;
     const double *bk = beta + (int64_t)k * (m + 1);
@@ -231,9 +234,10 @@ __global__ void __launch_bounds__(256) k_passB_dots(const double *__restrict__ d
                                                     const double2 *__restrict__ Q, int64_t slot,
                                                     double2 *__restrict__ w, double *__restrict__ alpha,
                                                     const double *__restrict__ beta, int m, int j, int nchunk,
-                                                    double2 *__restrict__ hpart) {
+                                                    double2 *__restrict__ hpart, uint64_t *start) {
     __shared__ double sh[16];
     __shared__ double2 ws[256];
+    stamp(start);
     const int k = blockIdx.y;
     const bool live = first_break(alpha + (int64_t)k * m, beta + (int64_t)k * (m + 1), j - 1) == 0;
     double a = sum_partials(dotpart + (int64_t)k * nblk, nblk, sh);
@@ -354,7 +358,8 @@ __global__ void __launch_bounds__(256) k_passC(const double *__restrict__ nrmpar
 }
 
 __global__ void __launch_bounds__(64) k_steps(const double *__restrict__ alpha, const double *__restrict__ beta, int m,
-                                              int jdone, int *__restrict__ steps) {
+                                              int jdone, int *__restrict__ steps, uint64_t *start) {
+    if (start && *start == 0) stamp(start);   // the step's first check is its end
     const int k = blockIdx.x;
     const int s = first_break(alpha + (int64_t)k * m, beta + (int64_t)k * (m + 1), jdone);
     if (threadIdx.x == 0) steps[k] = s ? s : jdone;
@@ -533,11 +538,16 @@ __global__ void __launch_bounds__(64) k_quadrature(const double *__restrict__ al
 }
 
 // G_k = beta_1^2 F_j; mean, SE = sqrt(Var / K) (sample variance), E = log2 mean,
-// dE = SE / (mean ln 2).  stats[(j-1)*4 + {0,1,2,3}].
+// dE = SE / (mean ln 2).  stats[(j-1)*4 + {0,1,2,3}].  A second block, where
+// there is one, takes step j2 (without its G).
 __global__ void __launch_bounds__(256) k_stats(const double *__restrict__ beta, const double *__restrict__ F,
-                                               int K, int m, int j, double *__restrict__ G,
+                                               int K, int m, int j, int j2, double *__restrict__ G,
                                                double *__restrict__ stats) {
     __shared__ double sh[16];
+    if (blockIdx.x == 1) {
+        j = j2;
+        G = nullptr;
+    }
     double s = 0.0;
     for (int k = threadIdx.x; k < K; k += blockDim.x) {
         const double b1 = beta[(int64_t)k * (m + 1)];
@@ -802,28 +812,28 @@ __global__ void k_features(const double *__restrict__ alpha, const double *__res
 
 hipError_t launch_passA(int accfp64, const LzDims &z, const void *part, int S, int64_t split_stride, int k0,
                         int kc, const double2 *q_prev, const double2 *q_cur, double2 *w, const double *alpha,
-                        const double *beta, int j, double *dotpart, hipStream_t st) {
+                        const double *beta, int j, double *dotpart, hipStream_t st, uint64_t *start) {
     dim3 grid(z.nblk, kc), block(256);
     if (accfp64)
         hipLaunchKernelGGL((k_passA<double2>), grid, block, 0, st, (const double2 *)part, S, split_stride, k0,
-                           z.n, q_prev, q_cur, w, alpha, beta, z.m, j, z.nblk, dotpart);
+                           z.n, q_prev, q_cur, w, alpha, beta, z.m, j, z.nblk, dotpart, start);
     else
         hipLaunchKernelGGL((k_passA<float2>), grid, block, 0, st, (const float2 *)part, S, split_stride, k0,
-                           z.n, q_prev, q_cur, w, alpha, beta, z.m, j, z.nblk, dotpart);
+                           z.n, q_prev, q_cur, w, alpha, beta, z.m, j, z.nblk, dotpart, start);
     return hipGetLastError();
 }
 
 hipError_t launch_passB(const LzDims &z, const double *dotpart, const double2 *q_cur, double2 *w,
-                        double *alpha, const double *beta, int j, double *nrmpart, hipStream_t st) {
+                        double *alpha, const double *beta, int j, double *nrmpart, hipStream_t st, uint64_t *start) {
     dim3 grid(z.nblk, z.K), block(256);
     hipLaunchKernelGGL(k_passB, grid, block, 0, st, dotpart, z.n, q_cur, w, alpha, beta, z.m, j, z.nblk,
-                       nrmpart);
+                       nrmpart, start);
     return hipGetLastError();
 }
 
 hipError_t launch_reorth(const LzDims &z, const double *dotpart, const double2 *Q, int64_t slot, double2 *w,
                          double *hpart, double2 *h, double *alpha, const double *beta, int j, double *nrmpart,
-                         hipStream_t st) {
+                         hipStream_t st, uint64_t *start) {
     const int bt = reorth_chunk(z.n, z.K);
     const int64_t chunks = reorth_chunks(z.n, z.K);
     if (chunks > 0x7fffffff) return hipErrorInvalidConfiguration;
@@ -831,7 +841,8 @@ hipError_t launch_reorth(const LzDims &z, const double *dotpart, const double2 *
     const bool fold = nc <= REORTH_FOLD;
     double2 *p0 = (double2 *)hpart, *p1 = fold ? p0 + (size_t)z.K * j * nc : p0;
     const dim3 grid(nc, z.K), block(bt), rgrid((j + 3) / 4, z.K);
-    hipLaunchKernelGGL(k_passB_dots, grid, block, 0, st, dotpart, z.nblk, z.n, Q, slot, w, alpha, beta, z.m, j, nc, p0);
+    hipLaunchKernelGGL(k_passB_dots, grid, block, 0, st, dotpart, z.nblk, z.n, Q, slot, w, alpha, beta, z.m, j, nc, p0,
+                       start);
     if (!fold) hipLaunchKernelGGL(k_reorth_reduce, rgrid, dim3(256), 0, st, (const double2 *)p0, j, nc, h);
     hipLaunchKernelGGL(k_reorth_update_dots, grid, block, 0, st, Q, j, slot, z.n, (const double2 *)h,
                        (const double2 *)p0, w, nc, p1);
@@ -858,8 +869,8 @@ hipError_t launch_passC(int prec, const LzDims &z, const double *nrmpart, const 
 }
 
 hipError_t launch_steps(const double *alpha, const double *beta, int K, int m, int jdone, int *steps,
-                        hipStream_t st) {
-    hipLaunchKernelGGL(k_steps, dim3(K), dim3(64), 0, st, alpha, beta, m, jdone, steps);
+                        hipStream_t st, uint64_t *start) {
+    hipLaunchKernelGGL(k_steps, dim3(K), dim3(64), 0, st, alpha, beta, m, jdone, steps, start);
     return hipGetLastError();
 }
 
@@ -872,9 +883,9 @@ hipError_t launch_quadrature(const double *alpha, const double *beta, const int 
     return hipGetLastError();
 }
 
-hipError_t launch_stats(const double *beta, const double *F, int K, int m, int j, double *G, double *stats,
+hipError_t launch_stats(const double *beta, const double *F, int K, int m, int j, int j2, double *G, double *stats,
                         hipStream_t st) {
-    hipLaunchKernelGGL(k_stats, dim3(1), dim3(256), 0, st, beta, F, K, m, j, G, stats);
+    hipLaunchKernelGGL(k_stats, dim3(j2 > 0 ? 2 : 1), dim3(256), 0, st, beta, F, K, m, j, j2, G, stats);
     return hipGetLastError();
 }
 

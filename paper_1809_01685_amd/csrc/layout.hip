@@ -303,6 +303,8 @@ __global__ void k_zero(uint4 *__restrict__ p, int64_t n16, unsigned char *__rest
     if (i < tail) tailp[i] = 0;
 }
 
+__global__ void k_stamp(uint64_t *p) { stamp(p); }
+
 // ||psi||^2 and the number of non-finite amplitudes: per-block partial sums
 // (grid-stride, FP64), then one thread adds the blocks in order.
 template <typename T>
@@ -355,6 +357,11 @@ hipError_t launch_state_check(int dtype, const void *psi, int64_t D, double *scr
     else
         hipLaunchKernelGGL(k_state_partial<float2>, dim3(nb), dim3(256), 0, st, (const float2 *)psi, D, scratch);
     hipLaunchKernelGGL(k_state_sum, dim3(1), dim3(64), 0, st, (const double *)scratch, nb, out);
+    return hipGetLastError();
+}
+
+hipError_t launch_stamp(uint64_t *p, hipStream_t st) {
+    hipLaunchKernelGGL(k_stamp, dim3(1), dim3(1), 0, st, p);
     return hipGetLastError();
 }
 

@@ -163,6 +163,15 @@ __host__ __device__ inline int64_t brick_index(int prec, int64_t nst, int64_t r,
     return (((r / BRICK_ROWS) * nst + st) * planes_of(prec) * BRICK_ROWS + rr) * epr + u * epu + ll % epu;
 }
 
+// ------------------------------------------------------------ times
+// The device's constant-rate clock, written by the first thread of a kernel's
+// first block as it starts (p null: not asked for).  The phases of an estimate
+// are timed by these instead of events around them: an event costs a launch's
+// time on the stream, and small estimates are launches.
+__device__ inline void stamp(uint64_t *p) {
+    if (p && (blockIdx.x | blockIdx.y | blockIdx.z | threadIdx.x) == 0) *p = wall_clock64();
+}
+
 // ------------------------------------------------------------ GEMM
 // C = A * B^T over complex brick operands: A is M x Kr, B is N x Kr, both with
 // nst bricks along the reduction index and A, B pointing at their first block
@@ -183,6 +192,7 @@ struct GemmDesc {
     int cnb_log2, cni_log2;
     int64_t crs, c_nst;
     int64_t ldc, cbs, c_split;
+    uint64_t *start;   // where the kernel stamps its start, or null
 };
 
 // Whether an M x N product in S splits runs in 16-row tiles against all its

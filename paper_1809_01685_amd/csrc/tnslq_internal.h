@@ -75,6 +75,7 @@ struct Plan {
     size_t off_P32 = 0, off_Q32 = 0, off_X32 = 0;   // complex64 copies (FP32 factorised operator)
     size_t off_Q = 0, off_w = 0, off_alpha = 0, off_beta = 0, off_F = 0, off_G = 0;
     size_t off_stats = 0, off_red = 0, off_h = 0, off_steps = 0, off_fit = 0, off_feat = 0, off_mlp = 0;
+    size_t off_stamp = 0, end_out = 0;   // start stamps; end of the region read back (from off_alpha)
     size_t off_chk = 0;              // the state check's partial sums
     size_t total = 0;
     int nQ = 3;                      // Lanczos vector slots
@@ -83,6 +84,8 @@ struct Plan {
 // ------------------------------------------------------------ layout
 // Zero `bytes` bytes at p (16-byte aligned) with a fill kernel on st.
 hipError_t launch_zero(void *p, size_t bytes, hipStream_t st);
+// A kernel that only stamps its start (operands.h).
+hipError_t launch_stamp(uint64_t *p, hipStream_t st);
 
 // ||psi||^2 and the count of non-finite amplitudes of the D-element state, at
 // scratch[2 STATE_CHECK_BLOCKS] and scratch[2 STATE_CHECK_BLOCKS + 1]
@@ -128,9 +131,10 @@ hipError_t launch_probe_init(int prec, const LzDims &z, uint64_t seed, uint64_t 
 hipError_t launch_passA(int accfp64, const LzDims &z, const void *part, int S, int64_t split_stride,
                         int k0, int kc, const double2 *q_prev, const double2 *q_cur, double2 *w,
                         const double *alpha, const double *beta, int j, double *dotpart,
-                        hipStream_t st);
+                        hipStream_t st, uint64_t *start = nullptr);
 hipError_t launch_passB(const LzDims &z, const double *dotpart, const double2 *q_cur, double2 *w,
-                        double *alpha, const double *beta, int j, double *nrmpart, hipStream_t st);
+                        double *alpha, const double *beta, int j, double *nrmpart, hipStream_t st,
+                        uint64_t *start = nullptr);
 // Elements per block of the reorthogonalisation's dot products (one per
 // thread): 256, or down to 64 to give every CU two blocks; the blocks per
 // probe; and the bytes of their partial sums against up to m vectors.  Up to
@@ -156,7 +160,7 @@ inline size_t reorth_part_bytes(int64_t n, int K, int m) {
 // partial sums of |w|^2.
 hipError_t launch_reorth(const LzDims &z, const double *dotpart, const double2 *Q, int64_t slot, double2 *w,
                          double *hpart, double2 *h, double *alpha, const double *beta, int j, double *nrmpart,
-                         hipStream_t st);
+                         hipStream_t st, uint64_t *start = nullptr);
 hipError_t launch_passC(int prec, const LzDims &z, const double *nrmpart, const double2 *w,
                         double2 *q_next, void *Xt, int64_t xt_nst, const double *alpha,
                         double *beta, int j, hipStream_t st);
@@ -164,8 +168,9 @@ hipError_t launch_passC(int prec, const LzDims &z, const double *nrmpart, const 
 hipError_t launch_quadrature(const double *alpha, const double *beta, const int *steps, int K,
                              int m, int jlo, int jhi, int fn, double *F, hipStream_t st);
 hipError_t launch_steps(const double *alpha, const double *beta, int K, int m, int jdone,
-                        int *steps, hipStream_t st);
-hipError_t launch_stats(const double *beta, const double *F, int K, int m, int j, double *G,
+                        int *steps, hipStream_t st, uint64_t *start = nullptr);
+// Statistics of step j (and, with j2 > 0, of step j2 without its G).
+hipError_t launch_stats(const double *beta, const double *F, int K, int m, int j, int j2, double *G,
                         double *stats, hipStream_t st);
 // Exponential-fit estimate of every probe after step j (FIT_MIN_POINTS <= j <= m)
 // into finf, fsig (K each), G = beta_1^2 finf (may be NULL) and the block
@@ -211,6 +216,7 @@ struct ColmacDesc {
     int64_t osplit, os1, os2, osc;
     int S;
     int64_t rows_per_split;   // set by the launcher
+    uint64_t *start = nullptr;   // where the kernel stamps its start
 };
 hipError_t launch_colmac(int dtype, int conj, ColmacDesc g, hipStream_t st);
 hipError_t launch_sum_splits(const double2 *part, int S, int64_t n, double2 *Z, hipStream_t st);
@@ -220,7 +226,8 @@ hipError_t launch_sum_transpose_ups(const double2 *Up, int S, int K, int nB, int
 // Xq[(k, b)][a] = xq[k][a dB + b] (K probes, dB = 2^nB), the first streaming
 // pass's vectors; and Y[k][a dB + b] = sum_s Yt[s][(k, b)][a], the sum of the
 // second pass's split partials.
-hipError_t launch_vectors_by_b(const double2 *xq, int K, int64_t dA, int nB, double2 *Xq, hipStream_t st);
+hipError_t launch_vectors_by_b(const double2 *xq, int K, int64_t dA, int nB, double2 *Xq, hipStream_t st,
+                               uint64_t *start = nullptr);
 hipError_t launch_sum_transpose_y(const double2 *Yt, int S, int K, int64_t dA, int nB, double2 *Y, hipStream_t st);
 // Caller vectors into FP64 layout order Xs[k][a dB + b].
 hipError_t launch_load_vectors_plain(const double2 *X, int64_t dA, int64_t dB, int K, int swapped, double2 *Xs,
