@@ -479,6 +479,14 @@ PermDesc perm_for(const Plan &pl, const int *g0, int n0, const int *g1, int n1, 
     return pd;
 }
 
+// Where psi's lowest bit lies in the rows-by-2^kbits operand that pd regroups
+// it into: -1 in the reduction index, else its place in the row index.
+int low_bit_row(const PermDesc &pd, int kbits) {
+    for (int t = kbits; t < pd.L; ++t)
+        if (pd.map[t] == 0) return t - kbits;
+    return -1;
+}
+
 // Output bit t <- input bit, for psi regrouped with group `hi` most
 // significant and group `lo` least significant.
 PermDesc perm_two(int L, const int *hi, int n_hi, const int *lo, int n_lo) {
@@ -1154,8 +1162,9 @@ int form_rho(const Plan &pl, int prec, const void *psi, void *Pabe, void *Pabc, 
         TNSLQ_HIP(launch_permute_mixed(prec, pl.dtype, psi, Pabc, pl.md, 1, st));
     } else {
         const PermDesc abe = perm_for(pl, pl.qa, pl.nA, pl.qb, pl.nB, pl.qe, pl.nE);
-        TNSLQ_HIP(launch_permute(prec, pl.dtype, psi, Pabe, n, dE, abe, 0, st));
-        TNSLQ_HIP(launch_permute(prec, pl.dtype, psi, Pabc, n, dE, abe, 1, st));
+        const int rs = low_bit_row(abe, pl.nE);
+        TNSLQ_HIP(launch_permute(prec, pl.dtype, psi, Pabe, n, dE, abe, 0, rs, st));
+        TNSLQ_HIP(launch_permute(prec, pl.dtype, psi, Pabc, n, dE, abe, 1, rs, st));
     }
     GemmDesc g{};
     g.A = Pabe;
@@ -1338,8 +1347,10 @@ int do_layout(Ctx &c, const void *psi) {
     }
     PermDesc aeb = perm_for(pl, pl.qa, pl.nA, pl.qe, pl.nE, pl.qb, pl.nB);
     PermDesc bea = perm_for(pl, pl.qb, pl.nB, pl.qe, pl.nE, pl.qa, pl.nA);
-    TNSLQ_HIP(launch_permute(pl.prec, pl.dtype, psi, c.Paeb, pl.dA, pl.dE * pl.dB, aeb, 0, c.st));
-    TNSLQ_HIP(launch_permute(pl.prec, pl.dtype, psi, c.Pbea, pl.dB * pl.dE, pl.dA, bea, 1, c.st));
+    TNSLQ_HIP(launch_permute(pl.prec, pl.dtype, psi, c.Paeb, pl.dA, pl.dE * pl.dB, aeb, 0,
+                             low_bit_row(aeb, pl.nE + pl.nB), c.st));
+    TNSLQ_HIP(launch_permute(pl.prec, pl.dtype, psi, c.Pbea, pl.dB * pl.dE, pl.dA, bea, 1,
+                             low_bit_row(bea, pl.nA), c.st));
     const int64_t epr = brick_epr(pl.prec);
     if (pl.dA % epr)
         TNSLQ_HIP(launch_zero(c.Xt, brick_bytes(pl.prec, (int64_t)pl.K * pl.dB, pl.dA), c.st));

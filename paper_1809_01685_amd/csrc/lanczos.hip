@@ -7,8 +7,11 @@
 // reproducible run to run; no floating-point atomics are used.
 #include <float.h>
 
+#include <algorithm>
+
 #include "tnslq_internal.h"
 #include "wave.h"
+#include "xt_tile.h"
 
 namespace tnslq {
 namespace {
@@ -339,20 +342,14 @@ __global__ void __launch_bounds__(256) k_passC(const double *__restrict__ nrmpar
     amax = fmax(amax, fabs(ak[j - 1]));
     if (j >= 2) bmax = fmax(bmax, bk[j - 1]);
     const bool cont = live && !(b <= BREAKDOWN_TOL * (amax + bmax));
-    const int64_t base = (int64_t)k * n;
-    const int64_t gstride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += gstride) {
-        double2 v = w[base + e];
-        double2 q = cont ? make_double2(v.x / b, v.y / b) : make_double2(0.0, 0.0);
-        q_next[base + e] = q;
-        // Xt entry (row (k, b'), reduction index a') reads w at a' * dB + b'
-        if (Xt) {
-            const int64_t bb = e / dA, aa = e % dA;
-            double2 u = w[base + aa * dB + bb];
-            double2 qt = cont ? make_double2(u.x / b, u.y / b) : make_double2(0.0, 0.0);
-            store_planes<PREC>(Xt, brick_ps(PREC), brick_index(PREC, xt_nst, (int64_t)k * dB + bb, aa), qt.x,
-                               qt.y);
-        }
+    const double2 *wk = w + (int64_t)k * n;
+    double2 *qk = q_next + (int64_t)k * n;
+    auto unit = [&](double2 v) { return cont ? make_double2(v.x / b, v.y / b) : make_double2(0.0, 0.0); };
+    if (Xt) {
+        vector_to_xt<PREC>(wk, Xt, xt_nst, k, dA, dB, unit, [&](int64_t e, double2 q) { qk[e] = q; });
+    } else {
+        const int64_t gstride = (int64_t)gridDim.x * blockDim.x;
+        for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += gstride) qk[e] = unit(wk[e]);
     }
     if (blockIdx.x == 0 && threadIdx.x == 0) bk[j] = b;
 }
@@ -854,7 +851,8 @@ hipError_t launch_reorth(const LzDims &z, const double *dotpart, const double2 *
 
 hipError_t launch_passC(int prec, const LzDims &z, const double *nrmpart, const double2 *w, double2 *q_next,
                         void *Xt, int64_t xt_nst, const double *alpha, double *beta, int j, hipStream_t st) {
-    dim3 grid(z.nblk, z.K), block(256);
+    // whole tiles per block where the pass transposes into Xt
+    dim3 grid((unsigned)(Xt ? std::min<int64_t>(xt_tiles(z.dA, z.dB), 1024) : z.nblk), z.K), block(256);
 #define TNSLQ_PC(P)                                                                                         \
     hipLaunchKernelGGL((k_passC<P>), grid, block, 0, st, nrmpart, z.n, z.dA, z.dB, w, q_next, Xt, xt_nst, \
                        alpha, beta, z.m, j, z.nblk)

@@ -6,6 +6,8 @@
 #include <algorithm>
 
 #include "tnslq_internal.h"
+#include "wave.h"
+#include "xt_tile.h"
 
 namespace tnslq {
 namespace {
@@ -23,31 +25,56 @@ __device__ inline double2 load_psi(const void *psi, int64_t i) {
 
 // Brick operand of R x Kr entries from psi: entry (r, l) = psi[in(r Kr + l)]
 // (conjugated if asked), where bit t of the regrouped index is bit map[t] of
-// in, and zeros in the padding.  Threads step over the plane-0 entries of the
-// bricks in memory order, so consecutive threads write consecutive elements of
-// every plane.
+// in, and zeros in the padding (Kr a power of two).  A thread gathers the
+// terms of one 16-byte unit and stores whole units, one per plane.  Bound by
+// the gather: consecutive threads take the units of a row, then the rows, when
+// psi runs along the reduction index, and the rows of a brick in steps of
+// 2^rs, then the next, when it runs along those (rs >= 0: of the row index
+// (b, c) the b, c having rs bits).
+// 2-byte stores in plane order took 3.12 ms for 28 qubits in split BF16
+// per operand (1.7 TB/s read and written), this 2.05 (2.6).
 template <int PREC, int DTYPE>
 __global__ void __launch_bounds__(256) k_permute(const void *__restrict__ psi, void *__restrict__ out, int64_t R,
-                                                 int64_t Kr, int64_t nst, PermDesc pd, int conj) {
-    constexpr int EPR = brick_epr(PREC), EPU = EPR / 4, NPL = planes_of(PREC);
-    constexpr int64_t PER_BRICK = (int64_t)BRICK_ROWS * EPR;
-    const int64_t total = brick_rows(R) * nst * EPR;
+                                                 int64_t Kr, int64_t nst, PermDesc pd, int conj, int rs) {
+    constexpr int EPR = brick_epr(PREC), EPU = brick_epu(PREC), NPL = planes_of(PREC);
+    const int64_t total = brick_rows(R) * nst * 4;
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+    int64_t dl[EPU];   // psi index of the unit's terms against its first
+#pragma unroll
+    for (int t = 0; t < EPU; ++t) {
+        dl[t] = 0;
+#pragma unroll
+        for (int k = 0; (1 << k) < EPU; ++k)
+            if ((t >> k) & 1 && k < pd.L) dl[t] |= int64_t(1) << pd.map[k];
+    }
     for (int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; x < total; x += stride) {
-        const int64_t b = x / PER_BRICK, w = x % PER_BRICK;
-        const int64_t rr = w / EPR, pos = w % EPR;
-        // stored unit pos / EPU holds logical unit (pos / EPU) ^ swizzle(rr)
-        const int64_t ll = (((pos / EPU) ^ brick_swizzle(rr)) * EPU) + pos % EPU;
-        const int64_t r = (b / nst) * BRICK_ROWS + rr, l = (b % nst) * EPR + ll;
-        double2 v = make_double2(0.0, 0.0);
-        if (r < R && l < Kr) {
+        const int64_t b = x >> 9;
+        const int w = (int)(x & 511);
+        int rr, u;   // row of the brick, logical unit
+        if (rs < 0) {
+            rr = w >> 2;
+            u = w & 3;
+        } else {
+            const int j = w & 127;
+            rr = ((j << rs) | (j >> (7 - rs))) & 127;
+            u = w >> 7;
+        }
+        const int64_t r = (b / nst) * BRICK_ROWS + rr, l = (b % nst) * EPR + u * EPU;
+        double2 v[EPU];
+#pragma unroll
+        for (int t = 0; t < EPU; ++t) v[t] = make_double2(0.0, 0.0);
+        if (r < R) {
             const int64_t o = r * Kr + l;
             int64_t in = 0;
             for (int t = 0; t < pd.L; ++t) in |= ((o >> t) & 1) << pd.map[t];
-            v = load_psi<DTYPE>(psi, in);
-            if (conj) v.y = -v.y;
+#pragma unroll
+            for (int t = 0; t < EPU; ++t)
+                if (l + t < Kr) {
+                    v[t] = load_psi<DTYPE>(psi, in + dl[t]);
+                    if (conj) v[t].y = -v[t].y;
+                }
         }
-        store_planes<PREC>(out, brick_ps(PREC), (b * NPL * BRICK_ROWS + rr) * EPR + pos, v.x, v.y);
+        store_unit<PREC>(out, (b * NPL * BRICK_ROWS + rr) * EPR + (u ^ brick_swizzle(rr)) * EPU, v);
     }
 }
 
@@ -116,6 +143,22 @@ __device__ inline double2 probe_value(uint64_t seed, uint64_t offset, int k, int
     return make_double2(re, im);
 }
 
+// Xt's entries of row (k, b), reduction index a, from value(a, b), a unit of
+// consecutive a per thread (all of them where d_A is below a unit).
+template <int PREC, typename F>
+__device__ inline void fill_xt(void *Xt, int64_t xt_nst, int64_t k, int64_t dA, int64_t dB, F value) {
+    constexpr int EPU = brick_epu(PREC);
+    const int64_t ua = (dA + EPU - 1) / EPU, units = ua * dB;
+    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; x < units; x += stride) {
+        const int64_t b = x / ua, a0 = (x % ua) * EPU;
+        double2 v[EPU];
+#pragma unroll
+        for (int t = 0; t < EPU; ++t) v[t] = a0 + t < dA ? value(a0 + t, b) : make_double2(0.0, 0.0);
+        store_unit<PREC>(Xt, brick_index(PREC, xt_nst, k * dB + b, a0), v);
+    }
+}
+
 // q_1 = phi / beta_1 with beta_1 = ||phi|| = sqrt(d_A d_B) (unit-modulus
 // entries), in [k][a][b] order, and its transposed low-precision copy Xt.
 template <int PREC>
@@ -127,19 +170,15 @@ __global__ void __launch_bounds__(256) k_probe_init(uint64_t seed, uint64_t offs
     const int64_t n = dA * dB;
     const double b1 = sqrt((double)n);
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += stride) {
-        // q in [a][b] order, b fastest
-        const int64_t a = e / dB, b = e % dB;
-        double2 v = probe_value(seed, offset, k, a, b, dA, dB, swapped);
-        q[(int64_t)k * n + e] = make_double2(v.x / b1, v.y / b1);
-        // Xt row (k, b'), reduction index a' (when the caller contracts through Xt)
-        if (Xt) {
-            const int64_t b2 = e / dA, a2 = e % dA;
-            double2 u = probe_value(seed, offset, k, a2, b2, dA, dB, swapped);
-            store_planes<PREC>(Xt, brick_ps(PREC), brick_index(PREC, xt_nst, (int64_t)k * dB + b2, a2), u.x / b1,
-                               u.y / b1);
-        }
-    }
+    auto value = [&](int64_t a, int64_t b) {
+        const double2 v = probe_value(seed, offset, k, a, b, dA, dB, swapped);
+        return make_double2(v.x / b1, v.y / b1);
+    };
+    // q in [a][b] order, b fastest
+    for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += stride)
+        q[(int64_t)k * n + e] = value(e / dB, e % dB);
+    // Xt row (k, b'), reduction index a' (when the caller contracts through Xt)
+    if (Xt) fill_xt<PREC>(Xt, xt_nst, k, dA, dB, value);
     if (blockIdx.x == 0 && threadIdx.x == 0) beta[(int64_t)k * (m + 1)] = b1;
 }
 
@@ -159,19 +198,14 @@ __global__ void __launch_bounds__(256) k_load_vectors(const double2 *__restrict_
                                                       int64_t dB, int swapped, void *__restrict__ Xt,
                                                       int64_t xt_nst) {
     const int k = blockIdx.y;
-    const int64_t n = dA * dB;
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += stride) {
-        const int64_t b = e / dA, a = e % dA;   // Xt position [b][a]
-        double2 v;
-        if (swapped) {
-            v = X[(int64_t)k * n + b * dA + a];  // caller (a_o, b_o) = (b, a)
-            v.y = -v.y;
-        } else {
-            v = X[(int64_t)k * n + a * dB + b];
-        }
-        store_planes<PREC>(Xt, brick_ps(PREC), brick_index(PREC, xt_nst, (int64_t)k * dB + b, a), v.x, v.y);
-    }
+    const double2 *Xk = X + (int64_t)k * dA * dB;
+    if (swapped)   // caller (a_o, b_o) = (b, a)
+        fill_xt<PREC>(Xt, xt_nst, k, dA, dB, [&](int64_t a, int64_t b) {
+            const double2 v = Xk[b * dA + a];
+            return make_double2(v.x, -v.y);
+        });
+    else
+        vector_to_xt<PREC>(Xk, Xt, xt_nst, k, dA, dB, [](double2 v) { return v; }, [](int64_t, double2) {});
 }
 
 // Caller vectors X[k][a_o][b_o] -> FP64 vectors in layout order, Xs[k][a dB + b]
@@ -306,19 +340,27 @@ __global__ void k_zero(uint4 *__restrict__ p, int64_t n16, unsigned char *__rest
 __global__ void k_stamp(uint64_t *p) { stamp(p); }
 
 // ||psi||^2 and the number of non-finite amplitudes: per-block partial sums
-// (grid-stride, FP64), then one thread adds the blocks in order.
+// (grid-stride, FP64), then one wave adds the blocks.
 template <typename T>
 __global__ void __launch_bounds__(256) k_state_partial(const T *__restrict__ psi, int64_t D,
                                                        double *__restrict__ part) {
     __shared__ double sh[2][256];
     double s = 0.0, bad = 0.0;
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < D; i += stride) {
-        const double re = psi[i].x, im = psi[i].y;
-        if (isfinite(re) && isfinite(im))
-            s += re * re + im * im;
-        else
-            bad += 1.0;
+    // four loads in flight per thread (one at a time left HBM at 3.6 TB/s)
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < D; i += 4 * stride) {
+        T v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) v[u] = psi[i + u * stride < D ? i + u * stride : i];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const double re = v[u].x, im = v[u].y;
+            if (i + u * stride >= D) continue;
+            if (isfinite(re) && isfinite(im))
+                s += re * re + im * im;
+            else
+                bad += 1.0;
+        }
     }
     sh[0][threadIdx.x] = s;
     sh[1][threadIdx.x] = bad;
@@ -336,15 +378,20 @@ __global__ void __launch_bounds__(256) k_state_partial(const T *__restrict__ psi
     }
 }
 
-__global__ void k_state_sum(const double *__restrict__ part, int nb, double *__restrict__ out) {
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
+// The blocks' sums, one wave: a lane takes every 64th block in order, then the
+// lanes (a single thread waited for memory 1024 times, 85 us).
+__global__ void __launch_bounds__(64) k_state_sum(const double *__restrict__ part, int nb, double *__restrict__ out) {
     double s = 0.0, bad = 0.0;
-    for (int b = 0; b < nb; ++b) {
+    for (int b = threadIdx.x; b < nb; b += 64) {
         s += part[2 * b];
         bad += part[2 * b + 1];
     }
-    out[0] = s;
-    out[1] = bad;
+    s = wave_total(s);
+    bad = wave_total(bad);
+    if (threadIdx.x == 0) {
+        out[0] = s;
+        out[1] = bad;
+    }
 }
 
 }  // namespace
@@ -377,11 +424,12 @@ hipError_t launch_zero(void *p, size_t bytes, hipStream_t st) {
 }
 
 hipError_t launch_permute(int prec, int dtype, const void *psi, void *out, int64_t R, int64_t Kr,
-                          const PermDesc &pd, int conj, hipStream_t st) {
+                          const PermDesc &pd, int conj, int rs, hipStream_t st) {
     const int64_t nst = brick_stages(prec, Kr);
-    dim3 grid(grid_for(brick_rows(R) * nst * brick_epr(prec), 256 * 4, 65535 * 8)), block(256);
+    rs = rs < 7 ? rs : 7;
+    dim3 grid(grid_for(brick_rows(R) * nst * 4, 256 * 2, 65535 * 8)), block(256);
 #define TNSLQ_PERM(P, T) \
-    hipLaunchKernelGGL((k_permute<P, T>), grid, block, 0, st, psi, out, R, Kr, nst, pd, conj)
+    hipLaunchKernelGGL((k_permute<P, T>), grid, block, 0, st, psi, out, R, Kr, nst, pd, conj, rs)
     if (dtype == TNSLQ_C128) {
         switch (prec) {
             case TNSLQ_FP64: TNSLQ_PERM(TNSLQ_FP64, TNSLQ_C128); break;

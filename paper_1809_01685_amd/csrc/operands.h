@@ -163,6 +163,42 @@ __host__ __device__ inline int64_t brick_index(int prec, int64_t nst, int64_t r,
     return (((r / BRICK_ROWS) * nst + st) * planes_of(prec) * BRICK_ROWS + rr) * epr + u * epu + ll % epu;
 }
 
+// The 16-byte units (one per plane) of brick_epu consecutive reduction terms
+// v of one row, stored at element index idx (plane 0) of the unit's first
+// term: what store_planes writes term by term, in whole units.
+__host__ __device__ constexpr int brick_epu(int prec) { return 16 / piece_bytes(prec); }
+template <int PREC>
+__device__ inline void store_unit(void *base, int64_t idx, const double2 (&v)[brick_epu(PREC)]) {
+    constexpr int EPU = brick_epu(PREC);
+    constexpr int64_t PS = brick_ps(PREC);
+    if constexpr (PREC == TNSLQ_FP64) {
+        double *p = (double *)base + idx;
+        *(double2 *)p = make_double2(v[0].x, v[1].x);
+        *(double2 *)(p + PS) = make_double2(v[0].y, v[1].y);
+    } else if constexpr (PREC == TNSLQ_FP32) {
+        float *p = (float *)base + idx;
+        *(float4 *)p = make_float4((float)v[0].x, (float)v[1].x, (float)v[2].x, (float)v[3].x);
+        *(float4 *)(p + PS) = make_float4((float)v[0].y, (float)v[1].y, (float)v[2].y, (float)v[3].y);
+    } else {
+        constexpr int NP = pieces_of(PREC), NC = planes_of(PREC) / NP;   // re, im (and their sum)
+        uint16_t *p = (uint16_t *)base + idx;
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+            uint32_t w[NP][EPU / 2];
+#pragma unroll
+            for (int t = 0; t < EPU; ++t) {
+                uint16_t h[NP];
+                split_bf16_d<NP>(c == 0 ? v[t].x : (c == 1 ? v[t].y : v[t].x + v[t].y), h);
+#pragma unroll
+                for (int q = 0; q < NP; ++q) w[q][t / 2] = t % 2 ? w[q][t / 2] | (uint32_t)h[q] << 16 : h[q];
+            }
+#pragma unroll
+            for (int q = 0; q < NP; ++q)
+                *(uint4 *)(p + (c * NP + q) * PS) = make_uint4(w[q][0], w[q][1], w[q][2], w[q][3]);
+        }
+    }
+}
+
 // ------------------------------------------------------------ times
 // The device's constant-rate clock, written by the first thread of a kernel's
 // first block as it starts (p null: not asked for).  The phases of an estimate

@@ -99,9 +99,11 @@ struct PermDesc {
     int map[TNSLQ_MAX_QUBITS];   // output bit t <- input bit map[t]
 };
 // Regroup psi into an R x Kr brick operand (output flat index r * Kr + l),
-// writing every brick entry including the zero padding.
+// writing every brick entry including the zero padding.  rs: -1 when psi's
+// low bits run along the reduction index, else the number of row bits below
+// those they run along.
 hipError_t launch_permute(int prec, int dtype, const void *psi, void *out, int64_t R, int64_t Kr,
-                          const PermDesc &pd, int conj, hipStream_t st);
+                          const PermDesc &pd, int conj, int rs, hipStream_t st);
 
 // Explicit rho^{T_B} (intermediary (iii) of Sec. V) from the dense product
 // C[i][j] = rho_AB[i][j] (n x n, row-major, accumulator type: FP64 when
