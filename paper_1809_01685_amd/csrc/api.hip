@@ -239,16 +239,21 @@ int plan_rest(Plan &pl, int dtype, int prec, int K, int lanczos) {
         pl.kc = std::min(K, (pl.kc + q - 1) / q * q);
     }
     // split-K of the second contraction: enough blocks to fill the chip,
-    // at least 8 bricks per split
-    const int64_t tiles = ((pl.dA + 127) / 128) * ((pl.kc * pl.dB + 127) / 128);
+    // at least 8 bricks per split.  FP64: tiles of 64 columns, and 1024 blocks
+    // (four per CU, one at a time): its partials take 16 bytes an entry, and
+    // with 2048 the 22-qubit block matvec wrote and read 671 MB of them.
+    const bool f64 = prec == TNSLQ_FP64;
+    const int64_t tcols = f64 ? 64 : 128, want = f64 ? 1024 : 2048;
+    const int64_t tiles = ((pl.dA + 127) / 128) * ((pl.kc * pl.dB + tcols - 1) / tcols);
     pl.S = 1;
-    while (tiles * pl.S < 2048 && pl.nst2 % (2 * pl.S) == 0 && pl.nst2 / (2 * pl.S) >= 8) pl.S *= 2;
+    while (tiles * pl.S < want && pl.nst2 % (2 * pl.S) == 0 && pl.nst2 / (2 * pl.S) >= 8) pl.S *= 2;
     // the first contraction too, when its output (d_B d_E x kc d_B) has few
     // tiles: partial sums in the accumulator type, merged into Ups afterwards
-    const int64_t tiles1 = ((pl.dB * pl.dE + 127) / 128) * ((pl.kc * pl.dB + 127) / 128);
+    // (FP64: below 512 tiles, two per CU, the merge costs less than idle CUs)
+    const int64_t tiles1 = ((pl.dB * pl.dE + 127) / 128) * ((pl.kc * pl.dB + tcols - 1) / tcols);
     pl.S1 = 1;
-    if (tiles1 < 1024)
-        while (tiles1 * pl.S1 < 2048 && pl.nst1 % (2 * pl.S1) == 0 && pl.nst1 / (2 * pl.S1) >= 8) pl.S1 *= 2;
+    if (tiles1 < (f64 ? 512 : 1024))
+        while (tiles1 * pl.S1 < (f64 ? 512 : 2048) && pl.nst1 % (2 * pl.S1) == 0 && pl.nst1 / (2 * pl.S1) >= 8) pl.S1 *= 2;
     const int64_t n = pl.dAB;
     pl.nblk = reduction_blocks(n, K);
     // HBM regime: with K d_B <= STREAM_MAX_VECTORS vectors the contractions do
@@ -263,13 +268,13 @@ int plan_rest(Plan &pl, int dtype, int prec, int K, int lanczos) {
         pl.S1 = 1;
         pl.nst1 = pl.nst_rho = brick_stages(prec, n);
         pl.nst_e = brick_stages(prec, pl.dE);
-        const int64_t tl = (up128(n) / 128) * (up128(K) / 128);
+        const int64_t tl = (up128(n) / 128) * ((K + tcols - 1) / tcols);
         pl.S = 1;
-        if (thin_product(prec, n, K, 1))
+        if (K <= 64 && thin_product(prec, n, K, 1, pl.nst_rho))
             // 16-row tiles: about 2048 waves, two per SIMD, each at least eight bricks
             pl.S = (int)std::max<int64_t>(1, std::min<int64_t>(2048 / ((n + 15) / 16), pl.nst_rho / 8));
         else
-            while (tl * pl.S < 2048 && pl.nst_rho % (2 * pl.S) == 0 && pl.nst_rho / (2 * pl.S) >= 8) pl.S *= 2;
+            while (tl * pl.S < want && pl.nst_rho % (2 * pl.S) == 0 && pl.nst_rho / (2 * pl.S) >= 8) pl.S *= 2;
     }
     if (pl.stream) {
         pl.kc = K;

@@ -1,44 +1,36 @@
 // Complex "NT" contraction C = A * B^T on the matrix cores (gfx950), for the
 // two contractions of Sec. V Eq. 4, in these arithmetics:
 //   BF16X3  operands split as hi + lo BF16 pieces, three products of pieces
-//           per real product (hi*hi + hi*lo + lo*hi), three real products per
-//           complex product (see k_cgemm_bf16x3), v_mfma_f32_16x16x32_bf16,
-//           FP32 accumulation;
+//           per real product (hi*hi + hi*lo + lo*hi), v_mfma_f32_16x16x32_bf16,
+//           FP32 accumulation (k_cgemm_bf16x3);
 //   BF16X6  hi + mid + lo pieces, the six products of pieces (p, q) with
 //           p + q < 3, FP32 accumulation restarted every 64 terms
 //           (k_cgemm_bf16x6, 128 x 64 output tiles);
-//   FP32    v_mfma_f32_16x16x4_f32 with FP32 accumulation, the matrix-core
-//           sums flushed every 64 reduction terms into a second accumulator
-//           so that no FP32 running sum grows past 64 terms;
-//   FP64    v_mfma_f64_16x16x4_f64.
+//   FP32    FP32 operands, split into three exact BF16 pieces on their way to
+//           LDS, the same six products, FP32 accumulation in two levels
+//           (k_cgemm_fp32);
+//   FP64    v_mfma_f64_16x16x4_f64 (k_cgemm_fp64, 128 x 64 output tiles).
 //
-// Complex products in BF16X6, FP32 and FP64 use four real MFMA chains:
+// A complex product takes three real ones (Gauss's form) but in BF16X6, which
+// uses four:
 //   Re C += Re A Re B + (-Im A) Im B,   Im C += Re A Im B + Im A Re B,
 // the sign of Im A applied by flipping sign bits in registers.
 //
-// Tiling (wave64): a block of 8 waves computes a 128 x 128 complex output
-// tile, each wave 64 x 32 (4 x 2 MFMA tiles of 16 x 16), two waves per SIMD
-// so that one wave's LDS waits overlap the other's matrix instructions.  A
-// reduction step stages one brick of each operand (128 rows x 64 bytes per
-// plane: 32 BF16, 16 FP32 or 8 FP64 reduction terms) in LDS: thread t copies
-// bytes [16 t, 16 t + 16) of every plane, so each load instruction of the
-// block reads 8 KiB of contiguous memory and lands at the same offset in LDS.
-// Double buffered, one barrier per step.  For BF16 (k_cgemm_bf16x3,
-// k_cgemm_bf16x6) the copy goes straight from global memory into LDS
+// Tiling (wave64): a block of 8 waves computes a 128 x 128 (or 128 x 64)
+// complex output tile, each wave 64 x 32 (32 x 32) in MFMA tiles of 16 x 16,
+// two waves per SIMD so that one wave's LDS waits overlap the other's matrix
+// instructions.  A brick of an operand is 128 rows x 64 bytes per plane (32
+// BF16, 16 FP32 or 8 FP64 reduction terms); thread t copies bytes [16 t, 16 t
+// + 16) of a plane, so each load instruction of the block reads 8 KiB of
+// contiguous memory.  All but FP32 copy straight from global memory into LDS
 // (global_load_lds_dwordx4: 16 bytes per lane, each wave 1 KiB of a plane
-// tile); k_cgemm_bf16x3 stages one pair of planes at a time and reads the next
-// pair's fragments while its matrix instructions run on the current ones; see
-// the comment at that kernel.  FP32 and FP64 stage through
-// registers: step i+1 (loaded one step earlier) is written to the other
-// buffer and step i+2 is loaded into registers.  Bricks store the four
-// 16-byte units of a row XOR-swizzled by ((row >> 1) ^ (row >> 2)) & 3, so
-// the fragment reads of 8 or 16
-// consecutive rows hit distinct banks.  Rows past the edge of C come from the
-// bricks' row padding and their results are dropped; the reduction padding
-// holds zeros.  Each lane's 16-byte fragment
-// feeds one BF16 MFMA (8 terms), four FP32 MFMAs or two FP64 MFMAs; A and B
-// fragments pair the same reduction terms, so the order in which the terms of
-// a unit enter the sum does not matter.
+// tile).  Bricks store the four 16-byte units of a row XOR-swizzled by
+// ((row >> 1) ^ (row >> 2)) & 3, so the fragment reads of 8 or 16 consecutive
+// rows hit distinct banks.  Rows past the edge of C come from the bricks' row
+// padding and their results are dropped; the reduction padding holds zeros.
+// Each lane's 16-byte fragment feeds one BF16 MFMA (8 terms) or two FP64 MFMAs;
+// A and B fragments pair the same reduction terms, so the order in which the
+// terms of a unit enter the sum does not matter.
 //
 // Block order: the hardware deals blocks to the eight XCDs round robin, so
 // block b is renumbered to give XCD b % 8 a contiguous range of output tiles,
@@ -57,121 +49,6 @@ constexpr int WAVES_M = 2, WAVES_N = 4;
 constexpr int TM = BM / (16 * WAVES_M), TN = BN / (16 * WAVES_N);
 constexpr int NT = 64 * WAVES_M * WAVES_N;
 static_assert(BM * ROWB / 16 == NT, "one 16-byte unit of every brick plane per thread");
-
-template <int PREC> constexpr int stage_bytes() { return 2 * MP<PREC>::NPL * TILEB; }
-template <int PREC> constexpr int lds_bytes() { return 2 * stage_bytes<PREC>(); }
-
-// Main reduction loop over bricks [sbeg, send) for the block's output tile at
-// (i0, j0), accumulating into (outr, outi).
-template <int PREC>
-__device__ __forceinline__ void mainloop(const GemmDesc &g, char *lds, int64_t i0, int64_t j0, int64_t sbeg,
-                                         int64_t send, typename MP<PREC>::acc (&outr)[TM][TN],
-                                         typename MP<PREC>::acc (&outi)[TM][TN]) {
-    using P = MP<PREC>;
-    using Acc = typename P::acc;
-    constexpr int NPL = P::NPL;
-    constexpr int STAGEB = stage_bytes<PREC>();
-    constexpr int BRICKB = NPL * TILEB;   // one brick, all planes
-    // FP32 keeps a second accumulator: the matrix-core sums restart every
-    // FLUSH stages (64 terms) and are added into (outr, outi).
-    constexpr bool TWO_LEVEL = PREC == TNSLQ_FP32;
-    constexpr int FLUSH = 4;
-    const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
-    const int wm = wid / WAVES_N, wn = wid % WAVES_N;
-    const size_t blk = brick_block_bytes(PREC, g.nst);
-    const char *ga = (const char *)g.A + (size_t)(i0 / BM) * blk + 16 * tid;
-    const char *gb = (const char *)g.B + (size_t)(j0 / BN) * blk + 16 * tid;
-
-    // global -> register staging: one 16-byte unit of A and of B per plane
-    uint4 ra[NPL], rb[NPL];
-    auto gload = [&](int64_t st) __attribute__((always_inline)) {
-        const char *pa = ga + st * BRICKB, *pb = gb + st * BRICKB;
-#pragma unroll
-        for (int p = 0; p < NPL; ++p) {
-            const uint4 va = *(const uint4 *)(pa + p * TILEB);
-            const uint4 vb = *(const uint4 *)(pb + p * TILEB);
-            ra[p] = va;
-            rb[p] = vb;
-        }
-    };
-    auto lstore = [&](int buf) __attribute__((always_inline)) {
-        char *As = lds + buf * STAGEB + 16 * tid, *Bs = As + NPL * TILEB;
-#pragma unroll
-        for (int p = 0; p < NPL; ++p) {
-            *(uint4 *)(As + p * TILEB) = ra[p];
-            *(uint4 *)(Bs + p * TILEB) = rb[p];
-        }
-    };
-
-    Acc accr[TM][TN], acci[TM][TN];
-    auto zero = [&]() __attribute__((always_inline)) {
-#pragma unroll
-        for (int a = 0; a < TM; ++a)
-#pragma unroll
-            for (int b = 0; b < TN; ++b) {
-                accr[a][b] = Acc{0, 0, 0, 0};
-                acci[a][b] = Acc{0, 0, 0, 0};
-            }
-    };
-    auto flush = [&]() __attribute__((always_inline)) {
-#pragma unroll
-        for (int a = 0; a < TM; ++a)
-#pragma unroll
-            for (int b = 0; b < TN; ++b) {
-                outr[a][b] += accr[a][b];
-                outi[a][b] += acci[a][b];
-            }
-    };
-    zero();
-
-    const int frow = lane & 15, fk = lane >> 4;   // fragment row within a 16-row tile, k-unit
-    gload(sbeg);
-    lstore(0);
-    if (sbeg + 1 < send) gload(sbeg + 1);
-    __syncthreads();
-    int buf = 0, nstage = 0;
-    for (int64_t st = sbeg; st < send; ++st, buf ^= 1) {
-        const char *As = lds + buf * STAGEB, *Bs = As + NPL * TILEB;
-        uint4 fa[TM][NPL], fb[TN][NPL];
-#pragma unroll
-        for (int x = 0; x < TM; ++x) {
-            const int oa = loff(wm * TM * 16 + x * 16 + frow, fk);
-#pragma unroll
-            for (int p = 0; p < NPL; ++p) fa[x][p] = *(const uint4 *)(As + p * TILEB + oa);
-        }
-#pragma unroll
-        for (int x = 0; x < TN; ++x) {
-            const int ob = loff(wn * TN * 16 + x * 16 + frow, fk);
-#pragma unroll
-            for (int p = 0; p < NPL; ++p) fb[x][p] = *(const uint4 *)(Bs + p * TILEB + ob);
-        }
-        if (st + 1 < send) {
-            lstore(buf ^ 1);
-            if (st + 2 < send) gload(st + 2);
-        }
-        stage_mfma<PREC, TM, TN>(fa, fb, accr, acci);
-        if constexpr (TWO_LEVEL) {
-            if (++nstage == FLUSH) {
-                flush();
-                zero();
-                nstage = 0;
-            }
-        }
-        __builtin_amdgcn_sched_barrier(0);
-        __syncthreads();
-    }
-    if constexpr (TWO_LEVEL) {
-        if (nstage) flush();
-    } else {
-#pragma unroll
-        for (int a = 0; a < TM; ++a)
-#pragma unroll
-            for (int b = 0; b < TN; ++b) {
-                outr[a][b] = accr[a][b];
-                outi[a][b] = acci[a][b];
-            }
-    }
-}
 
 // Output tile (i0, j0) and reduction split s of block blockIdx.x: the
 // hardware deals blocks to the XCDs round robin, so block b is renumbered to
@@ -200,25 +77,392 @@ __device__ inline TileAt tile_of(const GemmDesc &g) {
     return r;
 }
 
-template <int PREC>
-__global__ void __launch_bounds__(NT, 1) k_cgemm_nt_mfma(GemmDesc g) {
+typedef __attribute__((address_space(3))) void lds_void_t;
+typedef __attribute__((address_space(1))) const void gbl_void_t;
+
+template <int U, int END, typename F>
+__device__ __forceinline__ void unroll_from(F &f) {
+    if constexpr (U < END) {
+        f(std::integral_constant<int, U>{});
+        unroll_from<U + 1, END>(f);
+    }
+}
+
+// ---------------------------------------------------------------------------
+// FP64: three real products per complex product, as for BF16X3 below
+//   T1 = sum Re A Re B,  T2 = sum Im A Im B,  T3 = sum (Re A + Im A)(Re B + Im B),
+//   Re C = T1 - T2,      Im C = T3 - T1 - T2,
+// a quarter fewer v_mfma_f64_16x16x4f64 than four; the sums Re + Im are formed
+// from the fragments in registers (8 additions per 24 matrix instructions).
+// T3's terms are larger, so its sum is restarted every four steps (32 terms)
+// and kept in a second accumulator: the error against 80-bit sums is 5.1e-16 of
+// the result where the four-product form's was 5.5e-16 (14 to 18 qubits).
+// FP64 is bound by the matrix cores alone (a fragment read feeds six matrix
+// instructions of 64 cycles), so the tile is chosen for the number of blocks:
+// 128 x 64 outputs, 8 waves of 32 x 32 (2 x 2 tiles, 96 accumulator registers;
+// 64 x 32 would take 192).  A step is one brick of A and half a brick of B
+// (24 KiB), copied straight into a ring of four LDS buffers, four steps ahead;
+// fragments of the next step are read between the current step's matrix
+// instructions; one barrier per step.  Buffers and register sets are chosen at
+// compile time (the loop body is four steps; a run of another length starts
+// inside it), as in k_cgemm_bf16x3.  A 22-qubit block matvec of 5 vectors took
+// 1573 us with 128 x 128 tiles of four products and 2048 splits' worth of
+// partial sums, 863 with this; 68 TFLOP/s (of 78.6 issued in four products).
+constexpr int D_BN = 64, D_WAVES_N = 2, D_TM = 2, D_TN = 2, D_BODY = 4;
+
+__global__ void __launch_bounds__(NT, 1) k_cgemm_fp64(GemmDesc g) {
     stamp(g.start);
-    using Acc = typename MP<PREC>::acc;
-    extern __shared__ __attribute__((aligned(16))) char lds[];
-    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+    constexpr int NPL = 2, ABRICK = NPL * TILEB, BHALF = TILEB / 2, BSTEP = NPL * BHALF;
+    __shared__ __attribute__((aligned(16))) char lA0[ABRICK], lA1[ABRICK], lA2[ABRICK], lA3[ABRICK];
+    __shared__ __attribute__((aligned(16))) char lB0[BSTEP], lB1[BSTEP], lB2[BSTEP], lB3[BSTEP];
+    const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+    const int wm = wid / D_WAVES_N, wn = wid % D_WAVES_N;
+    const TileAt tl = tile_of<D_BN>(g);
+    const int64_t p0 = tl.sbeg, pend = tl.send, plast = pend - 1;
+    const size_t blk = brick_block_bytes(TNSLQ_FP64, g.nst);
+    const char *gA = (const char *)g.A + (size_t)(tl.i0 / BM) * blk;
+    // B's rows j0 .. j0 + 63: the first or second half of every plane tile
+    const char *gB = (const char *)g.B + (size_t)(tl.j0 / BN) * blk + ((tl.j0 % BN) / D_BN) * BHALF;
+    const int w = __builtin_amdgcn_readfirstlane(wid);
+    const uint32_t l16 = 16u * (uint32_t)lane;
+    auto bufA = [&](auto bb) -> char * {
+        constexpr int B = decltype(bb)::value;
+        return B == 0 ? lA0 : (B == 1 ? lA1 : (B == 2 ? lA2 : lA3));
+    };
+    auto bufB = [&](auto bb) -> char * {
+        constexpr int B = decltype(bb)::value;
+        return B == 0 ? lB0 : (B == 1 ? lB1 : (B == 2 ? lB2 : lB3));
+    };
+    // copy step st (the last one again past the end): wave w takes KiB w of
+    // both planes of A, and quarter w % 4 of plane w / 4 of B
+    auto dma = [&](int64_t st, auto bb) __attribute__((always_inline)) {
+        const int64_t q = st <= plast ? st : plast;
+        const char *pa = gA + q * ABRICK, *pb = gB + q * ABRICK;
+        char *As = bufA(bb) + 1024 * w, *Bs = bufB(bb) + 1024 * w;
+#pragma unroll
+        for (int p = 0; p < NPL; ++p)
+            __builtin_amdgcn_global_load_lds((gbl_void_t *)(pa + p * TILEB + 1024 * w + l16),
+                                             (lds_void_t *)(As + p * TILEB), 16, 0, 0);
+        __builtin_amdgcn_global_load_lds((gbl_void_t *)(pb + (w >> 2) * TILEB + (w & 3) * 1024 + l16),
+                                         (lds_void_t *)Bs, 16, 0, 0);
+    };
+    const int frow = lane & 15, fk = lane >> 4;
+    int oa[D_TM], ob[D_TN];
+#pragma unroll
+    for (int x = 0; x < D_TM; ++x) oa[x] = loff(wm * D_TM * 16 + x * 16 + frow, fk);
+#pragma unroll
+    for (int x = 0; x < D_TN; ++x) ob[x] = loff(wn * D_TN * 16 + x * 16 + frow, fk);
+    uint4 fa[2][D_TM][NPL], fb[2][D_TN][NPL];
+    auto rd = [&](auto ss, auto bb) __attribute__((always_inline)) {
+        constexpr int S = decltype(ss)::value;
+        const char *As = bufA(bb), *Bs = bufB(bb);
+#pragma unroll
+        for (int x = 0; x < D_TM; ++x)
+#pragma unroll
+            for (int p = 0; p < NPL; ++p) fa[S][x][p] = *(const uint4 *)(As + p * TILEB + oa[x]);
+#pragma unroll
+        for (int x = 0; x < D_TN; ++x)
+#pragma unroll
+            for (int p = 0; p < NPL; ++p) fb[S][x][p] = *(const uint4 *)(Bs + p * BHALF + ob[x]);
+    };
+    f64x4 t[3][D_TM][D_TN];
+#pragma unroll
+    for (int q = 0; q < 3; ++q)
+#pragma unroll
+        for (int a = 0; a < D_TM; ++a)
+#pragma unroll
+            for (int b = 0; b < D_TN; ++b) t[q][a][b] = f64x4{0, 0, 0, 0};
+    // T3 of the finished bodies
+    f64x4 t3[D_TM][D_TN];
+#pragma unroll
+    for (int a = 0; a < D_TM; ++a)
+#pragma unroll
+        for (int b = 0; b < D_TN; ++b) t3[a][b] = f64x4{0, 0, 0, 0};
+    auto flush3 = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int a = 0; a < D_TM; ++a)
+#pragma unroll
+            for (int b = 0; b < D_TN; ++b) {
+                t3[a][b] += t[2][a][b];
+                t[2][a][b] = f64x4{0, 0, 0, 0};
+            }
+    };
+    int64_t base = 0;
+    auto step = [&](auto uu) __attribute__((always_inline)) {
+        constexpr int U = decltype(uu)::value, C = U % 2;
+        rd(std::integral_constant<int, C ^ 1>{}, std::integral_constant<int, (U + 1) % 4>{});
+        dma(base + U + 4, std::integral_constant<int, U>{});
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int q = 0; q < 3; ++q)
+#pragma unroll
+                for (int a = 0; a < D_TM; ++a)
+#pragma unroll
+                    for (int b = 0; b < D_TN; ++b) {
+                        const double ar = f64_at(fa[C][a][0], h), ai = f64_at(fa[C][a][1], h);
+                        const double br = f64_at(fb[C][b][0], h), bi = f64_at(fb[C][b][1], h);
+                        t[q][a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(
+                            q == 0 ? ar : (q == 1 ? ai : ar + ai), q == 0 ? br : (q == 1 ? bi : br + bi), t[q][a][b], 0, 0,
+                            0);
+                    }
+        // 2 MFMA, 8 x (LDS read, MFMA), 3 x (copy, MFMA), 11 MFMA
+        __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+        }
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+        }
+        __builtin_amdgcn_sched_group_barrier(0x008, 11, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_waitcnt(0x0076);   // vmcnt(6): step st + 2 landed; lgkmcnt(0)
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    // the run starts at body position U0, so that it ends with a whole body
+    auto start = [&](auto u0) __attribute__((always_inline)) {
+        constexpr int V = decltype(u0)::value;
+        dma(p0, std::integral_constant<int, V % 4>{});
+        dma(p0 + 1, std::integral_constant<int, (V + 1) % 4>{});
+        dma(p0 + 2, std::integral_constant<int, (V + 2) % 4>{});
+        dma(p0 + 3, std::integral_constant<int, (V + 3) % 4>{});
+        __builtin_amdgcn_s_waitcnt(0x0f79);   // vmcnt(9): step p0 landed
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+        rd(std::integral_constant<int, V % 2>{}, std::integral_constant<int, V % 4>{});
+        __builtin_amdgcn_s_waitcnt(0x0076);   // vmcnt(6): step p0 + 1 landed; lgkmcnt(0)
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+        base = p0 - V;
+        unroll_from<V, D_BODY>(step);
+        flush3();
+        base += D_BODY;
+    };
+    switch ((int)((D_BODY - (pend - p0) % D_BODY) % D_BODY)) {
+        case 1: start(std::integral_constant<int, 1>{}); break;
+        case 2: start(std::integral_constant<int, 2>{}); break;
+        case 3: start(std::integral_constant<int, 3>{}); break;
+        default: start(std::integral_constant<int, 0>{}); break;
+    }
+    for (; base < pend; base += D_BODY) {
+        unroll_from<0, D_BODY>(step);
+        flush3();
+    }
+    __builtin_amdgcn_s_waitcnt(0x0f70);   // the copies past the end, before LDS is given up
+
+    f64x4 accr[D_TM][D_TN], acci[D_TM][D_TN];
+#pragma unroll
+    for (int a = 0; a < D_TM; ++a)
+#pragma unroll
+        for (int b = 0; b < D_TN; ++b) {
+            accr[a][b] = t[0][a][b] - t[1][a][b];
+            acci[a][b] = t3[a][b] - t[0][a][b] - t[1][a][b];
+        }
+    store_tiles<TNSLQ_FP64, D_TM, D_TN>(g, tl.s, tl.i0 + wm * D_TM * 16, tl.j0 + wn * D_TN * 16, lane, accr, acci);
+}
+
+hipError_t launch_fp64(const GemmDesc &g, hipStream_t st) {
+    const int64_t nblocks = ((g.M + BM - 1) / BM) * ((g.N + D_BN - 1) / D_BN) * g.S;
+    if (nblocks < 1 || nblocks > 0x7fffffff) return hipErrorInvalidConfiguration;
+    hipLaunchKernelGGL(k_cgemm_fp64, dim3((unsigned)nblocks), dim3(NT), 0, st, g);
+    return hipGetLastError();
+}
+
+// ---------------------------------------------------------------------------
+// FP32 on the BF16 matrix cores: an FP32 value is the exact sum of three BF16
+// pieces (8 + 8 + 8 significant bits), a product of two values the six
+// products of pieces (p, q) with p + q < 3 up to 2^-26 of it, and BF16
+// instructions run at 16 times the rate of v_mfma_f32_16x16x4f32; with three
+// real products per complex product a term costs 18 BF16 instructions where
+// the FP32 unit took 16 times 4 (18 / 64 of the time).  The operands stay FP32 bricks: a
+// step of 32 terms (two bricks) is loaded into registers, split there (a
+// packed conversion, its widening and a subtraction per pair and piece) and
+// written to LDS as three BF16 planes, so that memory and L2 see 8 bytes per
+// value and not 18.
+// Sums: each of T1, T2, T3 is accumulated over FP32_CHUNK steps (256 terms) in
+// matrix-core accumulators that start from zero, the products of leading
+// pieces apart from the five small ones (an addition rounds at the size of the
+// sum, so adding those five to it rounds six times as often: 5.2e-7 instead of
+// 2.0e-7 at 22 qubits), then added into Re C and Im C; T1, T2 and T3 take
+// turns on one set of accumulators.  Error of a block matvec against 64 bits:
+// 1.1e-7 to 2.2e-7 of the result from 10 to 24 qubits, where the FP32 unit with
+// sums restarted every 64 terms had 2.0e-7 to 3.3e-7.
+// Block, waves and tiles as k_cgemm_bf16x3: 128 x 128 outputs, 8 waves of
+// 64 x 32; 48 matrix instructions per wave and step for 18 fragment reads.  Two
+// LDS buffers (96 KiB), one barrier per step: the step after next is loaded, the
+// next one split and written, then the current one's matrix instructions run.
+// 26 qubits (65536 x 8192 outputs over 1024 terms): 34.0 to 21.5 ms, 130 to 205
+// TFLOP/s.  Bound by the split and the loads ahead of each step's matrix
+// instructions: interleaving them needs registers (it spilled 220), and giving
+// the two waves of a SIMD alternate phases took 23.7 ms.
+constexpr int FP32_CHUNK = 8;   // steps of 32 terms per restart
+
+__global__ void __launch_bounds__(NT, 1) k_cgemm_fp32(GemmDesc g) {
+    stamp(g.start);
+    constexpr int FBRICK = 2 * TILEB;   // an FP32 brick: re, im
+    constexpr int BUF = 3 * TILEB;      // an operand's three BF16 planes of a step
+    __shared__ __attribute__((aligned(16))) char lds[2][2][BUF];
+    typedef __attribute__((ext_vector_type(2))) float f32x2;
+    typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
+    const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
     const int wm = wid / WAVES_N, wn = wid % WAVES_N;
     const TileAt tl = tile_of(g);
+    const size_t blk = brick_block_bytes(TNSLQ_FP32, g.nst);
+    const char *gA = (const char *)g.A + (size_t)(tl.i0 / BM) * blk + 16 * tid;
+    const char *gB = (const char *)g.B + (size_t)(tl.j0 / BN) * blk + 16 * tid;
+    const int nsteps = (int)((tl.send - tl.sbeg + 1) / 2);
+    // thread t holds unit t % 4 of row t / 4 of a brick plane: four terms, 8
+    // bytes of a BF16 row, in its first half (first brick) or second
+    const int srow = tid >> 2, su = (tid & 3) ^ brick_swizzle(srow);
+    const int so0 = loff(srow, su >> 1) + 8 * (su & 1), so1 = loff(srow, 2 + (su >> 1)) + 8 * (su & 1);
 
-    Acc accr[TM][TN], acci[TM][TN];
+    // (chunk of steps from c0, product q, step s of the chunk)
+    struct Cursor {
+        int c0, q, s;
+    };
+    auto advance = [&](Cursor &c) __attribute__((always_inline)) {
+        const int len = min(FP32_CHUNK, nsteps - c.c0);
+        if (++c.s == len) {
+            c.s = 0;
+            if (++c.q == 3) {
+                c.q = 0;
+                c.c0 += FP32_CHUNK;
+            }
+        }
+    };
+    // staged values: [operand][brick of the step]; a second set for T3
+    float4 v[2][2], v2[2][2];
+    auto load = [&](const Cursor &c) __attribute__((always_inline)) {
+        if (c.c0 >= nsteps) return;
+        const int64_t st = tl.sbeg + 2 * (int64_t)(c.c0 + c.s);
+        const int64_t o0 = st * FBRICK + (c.q == 1 ? TILEB : 0);
+        const bool two = st + 1 < tl.send;
+        v[0][0] = *(const float4 *)(gA + o0);
+        v[1][0] = *(const float4 *)(gB + o0);
+        // a last odd brick: the step's second half is zeros
+        v[0][1] = two ? *(const float4 *)(gA + o0 + FBRICK) : make_float4(0.f, 0.f, 0.f, 0.f);
+        v[1][1] = two ? *(const float4 *)(gB + o0 + FBRICK) : make_float4(0.f, 0.f, 0.f, 0.f);
+        if (c.q == 2) {
+            v2[0][0] = *(const float4 *)(gA + o0 + TILEB);
+            v2[1][0] = *(const float4 *)(gB + o0 + TILEB);
+            v2[0][1] = two ? *(const float4 *)(gA + o0 + FBRICK + TILEB) : make_float4(0.f, 0.f, 0.f, 0.f);
+            v2[1][1] = two ? *(const float4 *)(gB + o0 + FBRICK + TILEB) : make_float4(0.f, 0.f, 0.f, 0.f);
+        }
+    };
+    auto split2 = [&](float x, float y, uint32_t (&h)[3]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int p = 0; p < 3; ++p) {
+            const bf16x2 b = __builtin_convertvector((f32x2{x, y}), bf16x2);
+            h[p] = __builtin_bit_cast(uint32_t, b);
+            x -= __uint_as_float(h[p] << 16);
+            y -= __uint_as_float(h[p] & 0xffff0000u);
+        }
+    };
+    auto put = [&](int q, int buf) __attribute__((always_inline)) {
+#pragma unroll
+        for (int o = 0; o < 2; ++o)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                float4 x = v[o][h];
+                if (q == 2) {
+                    x.x += v2[o][h].x;
+                    x.y += v2[o][h].y;
+                    x.z += v2[o][h].z;
+                    x.w += v2[o][h].w;
+                }
+                uint32_t a[3], b[3];
+                split2(x.x, x.y, a);
+                split2(x.z, x.w, b);
+                char *d = lds[buf][o] + (h ? so1 : so0);
+#pragma unroll
+                for (int p = 0; p < 3; ++p) *(uint2 *)(d + p * TILEB) = make_uint2(a[p], b[p]);
+            }
+    };
+    const int frow = lane & 15, fk = lane >> 4;
+    int oa[TM], ob[TN];
+#pragma unroll
+    for (int x = 0; x < TM; ++x) oa[x] = loff(wm * TM * 16 + x * 16 + frow, fk);
+#pragma unroll
+    for (int x = 0; x < TN; ++x) ob[x] = loff(wn * TN * 16 + x * 16 + frow, fk);
+    f32x4 t[TM][TN], tlow[TM][TN], accr[TM][TN], acci[TM][TN];
 #pragma unroll
     for (int a = 0; a < TM; ++a)
 #pragma unroll
-        for (int b = 0; b < TN; ++b) {
-            accr[a][b] = Acc{0, 0, 0, 0};
-            acci[a][b] = Acc{0, 0, 0, 0};
+        for (int b = 0; b < TN; ++b) t[a][b] = tlow[a][b] = accr[a][b] = acci[a][b] = f32x4{0, 0, 0, 0};
+
+    Cursor cur{0, 0, 0}, nxt{0, 0, 0}, ld{0, 0, 0};
+    load(ld);
+    advance(ld);
+    put(0, 0);
+    load(ld);
+    nxt = ld;
+    advance(ld);
+    __syncthreads();
+    const int total = 3 * nsteps;
+    int buf = 0;
+    for (int i = 0; i < total; ++i, buf ^= 1) {
+        const char *As = lds[buf][0], *Bs = lds[buf][1];
+        uint4 fa[TM][3], fb[TN][3];
+#pragma unroll
+        for (int p = 0; p < 3; ++p) {
+#pragma unroll
+            for (int x = 0; x < TM; ++x) fa[x][p] = *(const uint4 *)(As + p * TILEB + oa[x]);
+#pragma unroll
+            for (int x = 0; x < TN; ++x) fb[x][p] = *(const uint4 *)(Bs + p * TILEB + ob[x]);
         }
-    mainloop<PREC>(g, lds, tl.i0, tl.j0, tl.sbeg, tl.send, accr, acci);
-    store_tiles<PREC, TM, TN>(g, tl.s, tl.i0 + wm * TM * 16, tl.j0 + wn * TN * 16, lane, accr, acci);
+        if (i + 1 < total) put(nxt.q, buf ^ 1);
+        nxt = ld;
+        load(ld);
+        advance(ld);
+#pragma unroll
+        for (int pq = 0; pq < 6; ++pq) {
+            // (0,0), (0,1), (1,0), (1,1), (0,2), (2,0): pieces in the order they are read
+            const int p = pq == 2 || pq == 3 ? 1 : (pq == 5 ? 2 : 0);
+            const int q = pq == 1 || pq == 3 ? 1 : (pq == 4 ? 2 : 0);
+#pragma unroll
+            for (int a = 0; a < TM; ++a)
+#pragma unroll
+                for (int b = 0; b < TN; ++b) {
+                    f32x4 &c = pq == 0 ? t[a][b] : tlow[a][b];
+                    c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(fa[a][p]), as_bf16x8(fb[b][q]), c, 0, 0, 0);
+                }
+        }
+        const int q = cur.q;
+        advance(cur);
+        if (cur.q != q || cur.s == 0) {
+            // the chunk's sum of product q
+#pragma unroll
+            for (int a = 0; a < TM; ++a)
+#pragma unroll
+                for (int b = 0; b < TN; ++b) {
+                    t[a][b] += tlow[a][b];
+                    if (q == 0) {
+                        accr[a][b] += t[a][b];
+                        acci[a][b] -= t[a][b];
+                    } else if (q == 1) {
+                        accr[a][b] -= t[a][b];
+                        acci[a][b] -= t[a][b];
+                    } else {
+                        acci[a][b] += t[a][b];
+                    }
+                    t[a][b] = tlow[a][b] = f32x4{0, 0, 0, 0};
+                }
+        }
+        __syncthreads();
+    }
+    store_tiles<TNSLQ_FP32, TM, TN>(g, tl.s, tl.i0 + wm * TM * 16, tl.j0 + wn * TN * 16, lane, accr, acci);
+}
+
+hipError_t launch_fp32(const GemmDesc &g, hipStream_t st) {
+    const int64_t nblocks = ((g.M + BM - 1) / BM) * ((g.N + BN - 1) / BN) * g.S;
+    if (nblocks < 1 || nblocks > 0x7fffffff) return hipErrorInvalidConfiguration;
+    hipLaunchKernelGGL(k_cgemm_fp32, dim3((unsigned)nblocks), dim3(NT), 0, st, g);
+    return hipGetLastError();
 }
 
 // ---------------------------------------------------------------------------
@@ -255,19 +499,8 @@ __global__ void __launch_bounds__(NT, 1) k_cgemm_nt_mfma(GemmDesc g) {
 // 244 / 244 ms per launch against 283 / 282, 14% rather than 25%, the rest
 // taken by the 1.5x bytes staged per step (with the copies left out the loop
 // took 189 ms) and the power they cost under the chip's power limit.
-typedef __attribute__((address_space(3))) void lds_void_t;
-typedef __attribute__((address_space(1))) const void gbl_void_t;
-
 constexpr int PHB = 2 * TILEB;    // one pair of planes of one operand: 16 KiB
 constexpr int X3_BODY = 12;       // phases per loop iteration: lcm(2 sets, 3 products, 4 buffers)
-
-template <int U, int END, typename F>
-__device__ __forceinline__ void unroll_from(F &f) {
-    if constexpr (U < END) {
-        f(std::integral_constant<int, U>{});
-        unroll_from<U + 1, END>(f);
-    }
-}
 
 __global__ void __launch_bounds__(NT, 1) k_cgemm_bf16x3(GemmDesc g) {
     stamp(g.start);
@@ -631,27 +864,8 @@ hipError_t launch_bf16x6(const GemmDesc &g, hipStream_t st) {
 }
 
 template <int PREC>
-hipError_t launch(const GemmDesc &g, hipStream_t st) {
-    if constexpr (PREC == TNSLQ_BF16X3) {
-        return launch_bf16x3(g, st);
-    } else {
-        static bool attr_set = false;
-        if (!attr_set) {
-            hipError_t e = hipFuncSetAttribute((const void *)k_cgemm_nt_mfma<PREC>,
-                                               hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes<PREC>());
-            if (e != hipSuccess) return e;
-            attr_set = true;
-        }
-        const int64_t nblocks = ((g.M + BM - 1) / BM) * ((g.N + BN - 1) / BN) * g.S;
-        if (nblocks < 1 || nblocks > 0x7fffffff) return hipErrorInvalidConfiguration;
-        hipLaunchKernelGGL(k_cgemm_nt_mfma<PREC>, dim3((unsigned)nblocks), dim3(NT), lds_bytes<PREC>(), st, g);
-        return hipGetLastError();
-    }
-}
-
-template <int PREC>
 bool supported(const GemmDesc &g) {
-    if (thin_product(PREC, g.M, g.N, g.S)) return ((uintptr_t)g.A % 16) == 0 && ((uintptr_t)g.B % 16) == 0;
+    if (thin_product(PREC, g.M, g.N, g.S, g.nst)) return ((uintptr_t)g.A % 16) == 0 && ((uintptr_t)g.B % 16) == 0;
     return g.S >= 1 && g.nst % g.S == 0 && ((uintptr_t)g.A % 16) == 0 && ((uintptr_t)g.B % 16) == 0;
 }
 
@@ -670,13 +884,13 @@ bool gemm_mfma_supported(int prec, const GemmDesc &g) {
 }
 
 hipError_t launch_gemm_mfma(int prec, const GemmDesc &g, hipStream_t st) {
-    if (thin_product(prec, g.M, g.N, g.S))
+    if (thin_product(prec, g.M, g.N, g.S, g.nst))
         return launch_gemm_thin(prec, g, st);
     switch (prec) {
-        case TNSLQ_BF16X3: return launch<TNSLQ_BF16X3>(g, st);
+        case TNSLQ_BF16X3: return launch_bf16x3(g, st);
         case TNSLQ_BF16X6: return launch_bf16x6(g, st);
-        case TNSLQ_FP32: return launch<TNSLQ_FP32>(g, st);
-        case TNSLQ_FP64: return launch<TNSLQ_FP64>(g, st);
+        case TNSLQ_FP32: return launch_fp32(g, st);
+        case TNSLQ_FP64: return launch_fp64(g, st);
         default: return hipErrorInvalidValue;
     }
 }

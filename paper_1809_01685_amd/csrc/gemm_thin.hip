@@ -1,5 +1,5 @@
 // Complex "NT" contraction C = A * B^T over brick operands with few columns
-// (N <= 64, FP32 and FP64): the explicit operator on a block of
+// (N <= 64, FP32 and FP64) or, in FP64, few terms: the explicit operator on a block of
 // probes, or few vectors on a small B.  A 128-column tile would be half to
 // seven eighths padding, and such a product is bound by reading A once: a wave
 // takes one tile of 16 rows against all NTC tiles of 16 columns and loads its
@@ -33,7 +33,9 @@ __global__ void __launch_bounds__(64 * THIN_WAVES) k_thin_product(GemmDesc g) {
     if (i0 >= g.M) return;
     const int64_t sbeg = g.nst * s / g.S, send = g.nst * (s + 1) / g.S;
     const char *ga = (const char *)g.A + (size_t)rb * brick_block_bytes(PREC, g.nst) + loff(16 * r8 + frow, fk);
-    const char *gb = (const char *)g.B;
+    // columns in groups of 64 (half a row block of B) along the grid's y
+    const int64_t cg = blockIdx.y;
+    const char *gb = (const char *)g.B + (size_t)(cg >> 1) * brick_block_bytes(PREC, g.nst) + (cg & 1) * (TILEB / 2);
     int ob[NTC];
 #pragma unroll
     for (int c = 0; c < NTC; ++c) ob[c] = loff(16 * c + frow, fk);
@@ -90,7 +92,7 @@ __global__ void __launch_bounds__(64 * THIN_WAVES) k_thin_product(GemmDesc g) {
                 acci[0][c][r] = (float)outi[c][r];
             }
     }
-    store_tiles<PREC, 1, NTC>(g, s, i0, 0, lane, accr, acci);
+    store_tiles<PREC, 1, NTC>(g, s, i0, 64 * cg, lane, accr, acci);
 }
 
 template <int PREC>
@@ -98,8 +100,8 @@ hipError_t launch_thin(const GemmDesc &g, hipStream_t st) {
     const int64_t waves = (g.M + BM - 1) / BM * 8 * g.S;
     const int64_t nblocks = (waves + THIN_WAVES - 1) / THIN_WAVES;
     if (nblocks < 1 || nblocks > 0xffffff) return hipErrorInvalidConfiguration;
-    const dim3 grid((unsigned)nblocks), block(64 * THIN_WAVES);
-    switch ((g.N + 15) / 16) {
+    const dim3 grid((unsigned)nblocks, (unsigned)((g.N + 63) / 64)), block(64 * THIN_WAVES);
+    switch (g.N <= 48 ? (g.N + 15) / 16 : 4) {
         case 1: hipLaunchKernelGGL((k_thin_product<PREC, 1>), grid, block, 0, st, g); break;
         case 2: hipLaunchKernelGGL((k_thin_product<PREC, 2>), grid, block, 0, st, g); break;
         case 3: hipLaunchKernelGGL((k_thin_product<PREC, 3>), grid, block, 0, st, g); break;

@@ -231,13 +231,17 @@ struct GemmDesc {
     uint64_t *start;   // where the kernel stamps its start, or null
 };
 
-// Whether an M x N product in S splits runs in 16-row tiles against all its
-// columns (k_thin_product) instead of 128 x 128 tiles: FP32 and FP64 up to 64
-// columns, where a 128-column tile is at least half padding (at 65 to 128
-// columns the large tile's reuse of A through LDS is worth the padding).
-// Its splits need not divide the bricks.
-__host__ inline bool thin_product(int prec, int64_t M, int64_t N, int S) {
-    return (prec == TNSLQ_FP32 || prec == TNSLQ_FP64) && N <= 64 && S >= 1 && (M + 127) / 128 * 2 * S <= 0xffffff;
+// Whether an M x N product over nst bricks in S splits runs in 16-row tiles
+// against up to 64 columns (k_thin_product) instead of 128-row tiles: FP32 and
+// FP64 up to 64 columns, where a 128-column tile is at least half padding (at
+// 65 to 128 columns the large tile's reuse of A through LDS is worth the
+// padding), and FP64 over at most four bricks (32 terms), where four real
+// products round less than three (10 qubits: 3.73e-16 of the result against
+// 4.18e-16) and the matrix cores are not the bound.  Its splits need not
+// divide the bricks.
+__host__ inline bool thin_product(int prec, int64_t M, int64_t N, int S, int64_t nst) {
+    if ((prec != TNSLQ_FP32 && prec != TNSLQ_FP64) || S < 1 || (M + 127) / 128 * 2 * S > 0xffffff) return false;
+    return N <= 64 || (prec == TNSLQ_FP64 && nst <= 4 * (int64_t)S && (N + 63) / 64 <= 65535);
 }
 
 hipError_t launch_gemm(int prec, const GemmDesc &g, hipStream_t st);

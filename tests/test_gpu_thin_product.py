@@ -19,6 +19,7 @@ pytestmark = pytest.mark.gpu
     (12, [5, 6, 7, 8, 9], [1, 2], 11),         # 44
     (13, [0, 1, 2, 3, 4, 5], [8, 9, 10], 8),   # 64: the last thin shape
     (13, [0, 1, 2, 3, 4, 5], [8, 9, 10], 9),   # 72: the first of 128-column tiles
+    (13, [0, 1, 2, 3], [9, 10, 11], 24),       # 192 columns over 16 terms (FP64: groups of 64 columns)
     (9, [0, 1], [2, 3, 4, 5], 5),              # roles exchanged, 20 columns
 ])
 def test_matvec_with_few_columns(dev, prec, tol, L, a, b, K):
