@@ -1495,7 +1495,7 @@ int mps_matvec(Ctx &c, const double2 *x, int kcur, uint64_t *t1, uint64_t *t2) {
     const int64_t n = pl.dAB, UpM = f.Up * f.M, MV = f.M * f.V;
     const int kA = (int)f.kA, kB = (int)f.kB;
     auto chain = [&](auto *P, auto *Q, auto *X, auto *Z1, auto *Z2, auto *Z2p, auto *Z3, auto *Y) -> int {
-        TNSLQ_HIP(launch_zgemm(2, 0, P, X, Z1, (int)UpM, kB, kA, UpM, kB, kB, kcur, 0, n, UpM * kB, c.st));
+        TNSLQ_HIP(launch_zgemm(2, 0, P, X, Z1, (int)UpM, kB, kA, UpM, kB, kB, kcur, 0, n, UpM * kB, c.st, 0, 1, 0, 3));
         if (UpM <= 65535 * 64) {
             // Z2 written straight into the exchanged order Z2p
             TNSLQ_HIP(launch_zgemm_xc(Z1, Q, Z2p, (int)UpM, (int)MV, kB, kB, MV, kcur, UpM * kB, 0, UpM * MV, f.M,
@@ -1503,15 +1503,15 @@ int mps_matvec(Ctx &c, const double2 *x, int kcur, uint64_t *t1, uint64_t *t2) {
             TNSLQ_HIP(launch_stamp(t2, c.st));
         } else {
             TNSLQ_HIP(launch_zgemm(0, 0, Z1, Q, Z2, (int)UpM, (int)MV, kB, kB, MV, MV, kcur, UpM * kB, 0, UpM * MV,
-                                   c.st));
+                                   c.st, 0, 1, 0, 3));
             TNSLQ_HIP(launch_stamp(t2, c.st));
             TNSLQ_HIP(launch_swap01(Z2, (int64_t)kcur * f.Up, f.M, f.M, f.V, Z2p, c.st));
         }
         TNSLQ_HIP(launch_zgemm(0, 0, P, Z2p, Z3, kA, (int)MV, (int)UpM, UpM, MV, MV, kcur, 0, UpM * MV, kA * MV,
-                               c.st));
+                               c.st, 0, 1, 0, 3));
         // split s of the reduction at Y + s kc n (passA sums the splits)
         TNSLQ_HIP(launch_zgemm(0, 2, Z3, Q, Y, kA, kB, (int)MV, MV, MV, kB, kcur, kA * MV, 0, n, c.st, 0, pl.S,
-                               (int64_t)pl.kc * n));
+                               (int64_t)pl.kc * n, 3));
         return TNSLQ_OK;
     };
     int rc;
@@ -1548,15 +1548,15 @@ int net_matvec(Ctx &c, const double2 *x, int kcur, uint64_t *t1, uint64_t *t2) {
     char *base = c.ws + pl.off_net;
     auto chain = [&](auto *RA, auto *RB, auto *EWp, auto *EZp, auto *X, auto *T1, auto *Ta, auto *Tb, auto *T5,
                      auto *Y) -> int {
-        TNSLQ_HIP(launch_zgemm(2, 0, RA, X, T1, (int)UM, kB, kA, UM, kB, kB, kcur, 0, n, UM * kB, c.st));
-        TNSLQ_HIP(launch_zgemm(0, 0, T1, RB, Ta, (int)UM, (int)NV, kB, kB, NV, NV, kcur, UM * kB, 0, big, c.st));
+        TNSLQ_HIP(launch_zgemm(2, 0, RA, X, T1, (int)UM, kB, kA, UM, kB, kB, kcur, 0, n, UM * kB, c.st, 0, 1, 0, 3));
+        TNSLQ_HIP(launch_zgemm(0, 0, T1, RB, Ta, (int)UM, (int)NV, kB, kB, NV, NV, kcur, UM * kB, 0, big, c.st, 0, 1, 0, 3));
         TNSLQ_HIP(launch_stamp(t2, c.st));
         auto *T3 = Ta;   // [m][n'][u'][v]
         if (pl.ngap) {
             const int64_t d[4] = {U, M, N, V};
             const int perm[4] = {1, 2, 0, 3};   // [m'][n][u'][v]
             TNSLQ_HIP(launch_permute4(Ta, d, perm, Tb, c.st, kcur));
-            TNSLQ_HIP(launch_zgemm(0, 0, EWp, Tb, Ta, (int)MN, (int)UV, (int)MN, MN, UV, UV, kcur, 0, big, big, c.st));
+            TNSLQ_HIP(launch_zgemm(0, 0, EWp, Tb, Ta, (int)MN, (int)UV, (int)MN, MN, UV, UV, kcur, 0, big, big, c.st, 0, 1, 0, 3));
         } else {
             const int64_t d[4] = {U, M, M, V};
             const int perm[4] = {2, 1, 0, 3};
@@ -1570,7 +1570,7 @@ int net_matvec(Ctx &c, const double2 *x, int kcur, uint64_t *t1, uint64_t *t2) {
             const int perm3[4] = {3, 2, 0, 1};   // [v][u'][m][n']
             TNSLQ_HIP(launch_permute4(T3, d3, perm3, other, c.st, kcur));
             TNSLQ_HIP(launch_zgemm(0, 0, EZp, other, T3, (int)UV, (int)MN, (int)UV, UV, MN, MN, kcur, 0, big, big,
-                                   c.st));   // T4[u][v'][m][n']
+                                   c.st, 0, 1, 0, 3));   // T4[u][v'][m][n']
             const int64_t d4[4] = {U, V, M, N};
             const int perm4[4] = {0, 2, 3, 1};
             TNSLQ_HIP(launch_permute4(T3, d4, perm4, other, c.st, kcur));
@@ -1579,9 +1579,9 @@ int net_matvec(Ctx &c, const double2 *x, int kcur, uint64_t *t1, uint64_t *t2) {
             const int perm3[4] = {2, 0, 1, 3};
             TNSLQ_HIP(launch_permute4(T3, d3, perm3, other, c.st, kcur));
         }
-        TNSLQ_HIP(launch_zgemm(0, 0, RA, T4p, T5, kA, (int)NV, (int)UM, UM, NV, NV, kcur, 0, big, kA * NV, c.st));
+        TNSLQ_HIP(launch_zgemm(0, 0, RA, T4p, T5, kA, (int)NV, (int)UM, UM, NV, NV, kcur, 0, big, kA * NV, c.st, 0, 1, 0, 3));
         TNSLQ_HIP(launch_zgemm(0, 2, T5, RB, Y, kA, kB, (int)NV, NV, NV, kB, kcur, kA * NV, 0, n, c.st, 0, pl.S,
-                               (int64_t)pl.kc * n));
+                               (int64_t)pl.kc * n, 3));
         return TNSLQ_OK;
     };
     int rc;

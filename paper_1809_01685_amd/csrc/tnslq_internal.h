@@ -288,14 +288,15 @@ hipError_t launch_scale_rsqrt(double2 *x, int64_t n, const double *s, hipStream_
 // stored, 1 = transpose, 2 = conjugate transpose (supported pairs: (0,0),
 // (1,0), (2,0), (0,2)); op(A) is M x K.  With ks > 1 the reduction is split
 // in ks ranges and split s writes its partial product to C[b] + s csk (not
-// with sub); batch * ks <= 65535.
+// with sub); batch * ks <= 65535.  form: real products per complex one, 4, or
+// 3 where the reduction is long enough (pairs (0,0), (2,0), (0,2)).
 hipError_t launch_zgemm(int opa, int opb, const double2 *A, const double2 *B, double2 *C, int M, int N, int K,
                         int64_t lda, int64_t ldb, int64_t ldc, int batch, int64_t sa, int64_t sb, int64_t sc,
-                        hipStream_t st, int sub = 0, int ks = 1, int64_t csk = 0);
+                        hipStream_t st, int sub = 0, int ks = 1, int64_t csk = 0, int form = 4);
 // The same in FP32 (complex64 operands, FP32 matrix instructions).
 hipError_t launch_zgemm(int opa, int opb, const float2 *A, const float2 *B, float2 *C, int M, int N, int K,
                         int64_t lda, int64_t ldb, int64_t ldc, int batch, int64_t sa, int64_t sb, int64_t sc,
-                        hipStream_t st, int sub = 0, int ks = 1, int64_t csk = 0);
+                        hipStream_t st, int sub = 0, int ks = 1, int64_t csk = 0, int form = 4);
 // out[i] = complex64(in[i]), n entries.
 // C[b] = A[b] B[b] (both as stored) written with an exchange: output (r, c),
 // r = (r1, r2) with r2 < xm and c = (c1, c2) with c2 < xv, lands at
