@@ -355,7 +355,7 @@ int plan_rest(Plan &pl, int dtype, int prec, int K, int lanczos) {
         if (!lanczos) pl.off_Xs = take((size_t)K * n * 16);
     } else {
         pl.off_Paeb = take(brick_bytes(prec, pl.dA, pl.dE * pl.dB));
-        pl.off_Pbea = take(brick_bytes(prec, pl.dB * pl.dE, pl.dA));
+        pl.off_Peba = take(brick_bytes(prec, pl.dB * pl.dE, pl.dA));
         pl.off_Xt = take(brick_bytes(prec, (int64_t)K * pl.dB, pl.dA));
         pl.off_Ups = take(brick_bytes(prec, (int64_t)pl.kc * pl.dB, pl.dE * pl.dB));
         pl.off_Ypart = take((size_t)pl.S * pl.kc * n * acc);
@@ -1079,7 +1079,7 @@ struct Ctx {
     char *ws;
     hipStream_t st;
     LzDims z;
-    void *Paeb, *Pbea, *Xt, *Ups, *Ypart, *U1part;
+    void *Paeb, *Peba, *Xt, *Ups, *Ypart, *U1part;
     void *P1s, *P2s;
     void *Pabe, *Pabc, *Cd, *rho;
     double2 *Up, *U2, *Xs, *Xq, *Ym;
@@ -1104,7 +1104,7 @@ void bind(Ctx &c, void *ws, hipStream_t st) {
     c.ws = (char *)ws;
     c.st = st;
     c.Paeb = c.ws + pl.off_Paeb;
-    c.Pbea = c.ws + pl.off_Pbea;
+    c.Peba = c.ws + pl.off_Peba;
     c.Xt = c.ws + pl.off_Xt;
     c.Ups = c.ws + pl.off_Ups;
     c.Ypart = c.ws + pl.off_Ypart;
@@ -1116,12 +1116,12 @@ void bind(Ctx &c, void *ws, hipStream_t st) {
     c.Xs = (double2 *)(c.ws + pl.off_Xs);
     c.Xq = (double2 *)(c.ws + pl.off_Xq);
     c.Ym = (double2 *)(c.ws + pl.off_Ym);
-    if (pl.stream) c.Paeb = c.Pbea = c.Xt = c.Ups = nullptr;
+    if (pl.stream) c.Paeb = c.Peba = c.Xt = c.Ups = nullptr;
     c.Pabe = pl.expl ? c.ws + pl.off_Pabe : nullptr;
     c.Pabc = pl.expl ? c.ws + pl.off_Pabc : nullptr;
     c.Cd = pl.expl ? c.ws + pl.off_Cd : nullptr;
     c.rho = pl.expl ? c.ws + pl.off_rho : nullptr;
-    if (pl.expl) c.Paeb = c.Pbea = c.Ups = nullptr;
+    if (pl.expl) c.Paeb = c.Peba = c.Ups = nullptr;
     c.Z1 = (double2 *)(c.ws + pl.off_Z1);
     c.Z2 = (double2 *)(c.ws + pl.off_Z2);
     c.Z2p = (double2 *)(c.ws + pl.off_Z2p);
@@ -1129,7 +1129,7 @@ void bind(Ctx &c, void *ws, hipStream_t st) {
     c.P32 = (float2 *)(c.ws + pl.off_P32);
     c.Q32 = (float2 *)(c.ws + pl.off_Q32);
     c.X32 = (float2 *)(c.ws + pl.off_X32);
-    if (pl.mpsf) c.Paeb = c.Pbea = c.Xt = c.Ups = nullptr;
+    if (pl.mpsf) c.Paeb = c.Peba = c.Xt = c.Ups = nullptr;
     c.Q = (double2 *)(c.ws + pl.off_Q);
     c.w = (double2 *)(c.ws + pl.off_w);
     c.alpha = (double *)(c.ws + pl.off_alpha);
@@ -1182,7 +1182,6 @@ int form_rho(const Plan &pl, int prec, const void *psi, void *Pabe, void *Pabc, 
     g.S = 1;
     g.out_mode = 1;   // C[i][j] at i n + j
     g.cnb_log2 = 0;
-    g.cni_log2 = 0;
     g.ldc = n;
     g.cbs = 1;
     g.c_split = 0;
@@ -1351,11 +1350,11 @@ int do_layout(Ctx &c, const void *psi) {
         return TNSLQ_OK;
     }
     PermDesc aeb = perm_for(pl, pl.qa, pl.nA, pl.qe, pl.nE, pl.qb, pl.nB);
-    PermDesc bea = perm_for(pl, pl.qb, pl.nB, pl.qe, pl.nE, pl.qa, pl.nA);
+    PermDesc eba = perm_for(pl, pl.qe, pl.nE, pl.qb, pl.nB, pl.qa, pl.nA);
     TNSLQ_HIP(launch_permute(pl.prec, pl.dtype, psi, c.Paeb, pl.dA, pl.dE * pl.dB, aeb, 0,
                              low_bit_row(aeb, pl.nE + pl.nB), c.st));
-    TNSLQ_HIP(launch_permute(pl.prec, pl.dtype, psi, c.Pbea, pl.dB * pl.dE, pl.dA, bea, 1,
-                             low_bit_row(bea, pl.nA), c.st));
+    TNSLQ_HIP(launch_permute(pl.prec, pl.dtype, psi, c.Peba, pl.dB * pl.dE, pl.dA, eba, 1,
+                             low_bit_row(eba, pl.nA), c.st));
     const int64_t epr = brick_epr(pl.prec);
     if (pl.dA % epr)
         TNSLQ_HIP(launch_zero(c.Xt, brick_bytes(pl.prec, (int64_t)pl.K * pl.dB, pl.dA), c.st));
@@ -1401,9 +1400,9 @@ int stream_contract(Ctx &c, const double2 *xq, uint64_t *t1, uint64_t *t2) {
 int contract_chunk(Ctx &c, int k0, int kcur, uint64_t *t1, uint64_t *t2) {
     const Plan &pl = c.pl;
     // contraction 1: Ups[(k, b)][(c, b')] = sum_a' conj psi[a', b, c] Xt[(k, b')][a'];
-    // output (i, j) = ((b, c), (k, b')) -> row k d_B + b, index c d_B + b'
+    // output (i, j) = ((c, b), (k, b')) -> row k d_B + b, index c d_B + b'
     GemmDesc g1{};
-    g1.A = c.Pbea;
+    g1.A = c.Peba;
     g1.B = (const char *)c.Xt + (size_t)((int64_t)k0 * pl.dB / BRICK_ROWS) * brick_block_bytes(pl.prec, pl.nst1);
     g1.C = c.Ups;
     g1.M = pl.dB * pl.dE;
@@ -1413,12 +1412,11 @@ int contract_chunk(Ctx &c, int k0, int kcur, uint64_t *t1, uint64_t *t2) {
     g1.S = 1;
     g1.out_mode = 0;
     g1.cnb_log2 = pl.nB;
-    g1.cni_log2 = pl.nE;
     g1.crs = pl.dB;
     g1.c_nst = pl.nst2;
     const int64_t u1n = (int64_t)kcur * pl.dB * pl.dE * pl.dB;
     if (pl.S1 > 1) {
-        // split along a': partials at s * split + k (d_B d_E d_B) + (b d_E + c) d_B + b'
+        // split along a': partials at s * split + k (d_B d_E d_B) + (c d_B + b) d_B + b'
         g1.C = c.U1part;
         g1.S = pl.S1;
         g1.out_mode = 1;
@@ -1439,7 +1437,6 @@ int contract_chunk(Ctx &c, int k0, int kcur, uint64_t *t1, uint64_t *t2) {
     g2.S = pl.S;
     g2.out_mode = 1;
     g2.cnb_log2 = pl.nB;
-    g2.cni_log2 = 0;
     g2.ldc = pl.dB;
     g2.cbs = pl.dAB;
     g2.c_split = (int64_t)pl.kc * pl.dAB;
@@ -1471,7 +1468,6 @@ int explicit_matvec(Ctx &c, uint64_t *t1) {
     g.S = pl.S;
     g.out_mode = 1;
     g.cnb_log2 = 0;
-    g.cni_log2 = 0;
     g.ldc = 1;
     g.cbs = n;
     g.c_split = (int64_t)pl.K * n;

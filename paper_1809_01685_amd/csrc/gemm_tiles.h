@@ -104,13 +104,14 @@ __device__ __forceinline__ void stage_mfma(const uint4 (&fa)[WTM][MP<PREC>::NPL]
 
 // Epilogue of a wave's WTM x WTN tiles of 16 x 16 whose first output row and
 // column are (wi0, wj0): output register r of lane l holds column l % 16 and
-// row 4 (l / 16) + r (FP32 accumulators) or row 4 r + l / 16 (FP64).
-template <int PREC, int WTM, int WTN>
+// row 4 (l / 16) + r (FP32 accumulators) or row 4 r + l / 16 (FP64); with SWAP
+// (operands of the instruction exchanged) row l % 16 and column 4 (l / 16) + r.
+template <int PREC, int WTM, int WTN, bool SWAP = false>
 __device__ __forceinline__ void store_tiles(const GemmDesc &g, int s, int64_t wi0, int64_t wj0, int lane,
                                             const typename MP<PREC>::acc (&accr)[WTM][WTN],
                                             const typename MP<PREC>::acc (&acci)[WTM][WTN]) {
     const int frow = lane & 15, fk = lane >> 4;
-    const int64_t cnb_mask = ((int64_t)1 << g.cnb_log2) - 1, cni_mask = ((int64_t)1 << g.cni_log2) - 1;
+    const int64_t cnb_mask = ((int64_t)1 << g.cnb_log2) - 1;
 #pragma unroll
     for (int a = 0; a < WTM; ++a)
 #pragma unroll
@@ -118,14 +119,14 @@ __device__ __forceinline__ void store_tiles(const GemmDesc &g, int s, int64_t wi
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const int orow = PREC == TNSLQ_FP64 ? 4 * r + fk : 4 * fk + r;
-                const int64_t i = wi0 + a * 16 + orow;
-                const int64_t j = wj0 + b * 16 + frow;
+                const int64_t i = wi0 + a * 16 + (SWAP ? frow : orow);
+                const int64_t j = wj0 + b * 16 + (SWAP ? orow : frow);
                 if (i >= g.M || j >= g.N) continue;
                 const int64_t jq = j >> g.cnb_log2, jr = j & cnb_mask;
                 const auto vr = accr[a][b][r], vi = acci[a][b][r];
                 if (g.out_mode == 0) {
-                    const int64_t row = jq * g.crs + (i >> g.cni_log2);
-                    const int64_t col = ((i & cni_mask) << g.cnb_log2) + jr;
+                    const int64_t row = jq * g.crs + (i & cnb_mask);
+                    const int64_t col = (i & ~cnb_mask) + jr;
                     const int64_t idx = brick_index(PREC, g.c_nst, row, col);
                     if constexpr (PREC == TNSLQ_FP64)
                         store_planes<PREC>(g.C, brick_ps(PREC), idx, vr, vi);

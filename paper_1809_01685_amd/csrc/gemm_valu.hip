@@ -141,8 +141,8 @@ __global__ void __launch_bounds__(256) k_cgemm_nt_valu(GemmDesc g) {
             if (j >= g.N) continue;
             const int64_t jq = j >> g.cnb_log2, jr = j & (((int64_t)1 << g.cnb_log2) - 1);
             if (g.out_mode == 0) {
-                const int64_t row = jq * g.crs + (i >> g.cni_log2);
-                const int64_t col = ((i & (((int64_t)1 << g.cni_log2) - 1)) << g.cnb_log2) + jr;
+                const int64_t row = jq * g.crs + (i & (((int64_t)1 << g.cnb_log2) - 1));
+                const int64_t col = (i >> g.cnb_log2 << g.cnb_log2) + jr;
                 const int64_t idx = brick_index(PREC, g.c_nst, row, col);
                 if constexpr (PREC == TNSLQ_FP64)
                     store_planes<PREC>(g.C, brick_ps(PREC), idx, tot_re[r][c], tot_im[r][c]);

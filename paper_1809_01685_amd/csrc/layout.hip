@@ -29,8 +29,8 @@ __device__ inline double2 load_psi(const void *psi, int64_t i) {
 // terms of one 16-byte unit and stores whole units, one per plane.  Bound by
 // the gather: consecutive threads take the units of a row, then the rows, when
 // psi runs along the reduction index, and the rows of a brick in steps of
-// 2^rs, then the next, when it runs along those (rs >= 0: of the row index
-// (b, c) the b, c having rs bits).
+// 2^rs, then the next, when it runs along those (rs >= 0: the row bits
+// below them).
 // 2-byte stores in plane order took 3.12 ms for 28 qubits in split BF16
 // per operand (1.7 TB/s read and written), this 2.05 (2.6).
 template <int PREC, int DTYPE>
@@ -258,8 +258,8 @@ __global__ void __launch_bounds__(256) k_reduce_partials(const AccT *__restrict_
 }
 
 // The first contraction split along its reduction: the S partial sums of
-// Ups[k][(b, c)][b'] (accumulator type, at s * split + k * M dB + (b dE + c) dB
-// + b' with M = dB dE) added in FP64 and stored into the Ups brick operand,
+// Ups[k][(c, b)][b'] (accumulator type, at s * split + k * M dB + (c dB + b) dB
+// + b' with M = dE dB) added in FP64 and stored into the Ups brick operand,
 // row k dB + b, reduction index c dB + b'.
 template <int PREC, typename AccT>
 __global__ void __launch_bounds__(256) k_partials_to_bricks(const AccT *__restrict__ part, int S, int64_t split,
@@ -275,7 +275,7 @@ __global__ void __launch_bounds__(256) k_partials_to_bricks(const AccT *__restri
             im += (double)v.y;
         }
         const int64_t bp = e & (dB - 1), i = (e >> nB) % (dB * dE), k = (e >> nB) / (dB * dE);
-        const int64_t b = i >> nE, c = i & (dE - 1);
+        const int64_t b = i & (dB - 1), c = i >> nB;
         store_planes<PREC>(ups, brick_ps(PREC), brick_index(PREC, ups_nst, k * dB + b, (c << nB) + bp), re, im);
     }
 }

@@ -27,19 +27,25 @@ __host__ __device__ constexpr int piece_bytes(int prec) {
 __host__ __device__ constexpr int planes_of(int prec) { return prec == TNSLQ_BF16X3 ? 6 : 2 * pieces_of(prec); }
 
 // ------------------------------------------------------------ BF16 helpers
-// Round-to-nearest-even FP32 -> BF16 bits (finite inputs; NaN stays NaN).
-__device__ inline uint16_t f32_to_bf16_rne(float x) {
-    uint32_t u = __float_as_uint(x);
-    if ((u & 0x7f800000u) == 0x7f800000u) return (uint16_t)((u >> 16) | ((u & 0xffffu) ? 0x40u : 0u));
-    u += 0x7fffu + ((u >> 16) & 1u);
-    return (uint16_t)(u >> 16);
-}
+// Round-to-nearest-even FP32 -> BF16 bits (the packed conversion instruction,
+// one for two values; written out in integers it was six instructions each,
+// most of the time of an epilogue that splits its outputs).
+__device__ inline uint16_t f32_to_bf16_rne(float x) { return __builtin_bit_cast(uint16_t, (__bf16)x); }
 __device__ inline float bf16_to_f32(uint16_t h) { return __uint_as_float(((uint32_t)h) << 16); }
+
+// re + im as its two rounded operands give it, whatever they were computed from.
+template <class T> __device__ inline T rounded_sum(T re, T im) {
+#pragma clang fp contract(off)
+    return re + im;
+}
 
 // Split an FP32 value into `np` BF16 pieces whose sum approximates it:
 // piece 0 = bf16(x), piece 1 = bf16(x - piece0), piece 2 = bf16(rest).
+// The pieces are those of the rounded value x: no product that made it is
+// drawn into the differences.
 template <int NP>
 __device__ inline void split_bf16(float x, uint16_t *out) {
+#pragma clang fp contract(off)
     float r = x;
 #pragma unroll
     for (int p = 0; p < NP; ++p) {
@@ -52,6 +58,7 @@ __device__ inline void split_bf16(float x, uint16_t *out) {
 // that the pieces capture the value to ~2^-8 per piece.
 template <int NP>
 __device__ inline void split_bf16_d(double x, uint16_t *out) {
+#pragma clang fp contract(off)
     double r = x;
 #pragma unroll
     for (int p = 0; p < NP; ++p) {
@@ -85,7 +92,7 @@ __device__ inline void store_planes(void *base, int64_t ps, int64_t idx, double 
 #pragma unroll
         for (int q = 0; q < NP; ++q) p[(NP + q) * ps + idx] = h[q];
         if constexpr (PREC == TNSLQ_BF16X3) {
-            split_bf16_d<NP>(re + im, h);
+            split_bf16_d<NP>(rounded_sum(re, im), h);
 #pragma unroll
             for (int q = 0; q < NP; ++q) p[(2 * NP + q) * ps + idx] = h[q];
         }
@@ -113,7 +120,7 @@ __device__ inline void store_planes_f(void *base, int64_t ps, int64_t idx, float
 #pragma unroll
         for (int q = 0; q < NP; ++q) p[(NP + q) * ps + idx] = h[q];
         if constexpr (PREC == TNSLQ_BF16X3) {
-            split_bf16<NP>(re + im, h);
+            split_bf16<NP>(rounded_sum(re, im), h);
 #pragma unroll
             for (int q = 0; q < NP; ++q) p[(2 * NP + q) * ps + idx] = h[q];
         }
@@ -188,7 +195,7 @@ __device__ inline void store_unit(void *base, int64_t idx, const double2 (&v)[br
 #pragma unroll
             for (int t = 0; t < EPU; ++t) {
                 uint16_t h[NP];
-                split_bf16_d<NP>(c == 0 ? v[t].x : (c == 1 ? v[t].y : v[t].x + v[t].y), h);
+                split_bf16_d<NP>(c == 0 ? v[t].x : (c == 1 ? v[t].y : rounded_sum(v[t].x, v[t].y)), h);
 #pragma unroll
                 for (int q = 0; q < NP; ++q) w[q][t / 2] = t % 2 ? w[q][t / 2] | (uint32_t)h[q] << 16 : h[q];
             }
@@ -212,10 +219,10 @@ __device__ inline void stamp(uint64_t *p) {
 // C = A * B^T over complex brick operands: A is M x Kr, B is N x Kr, both with
 // nst bricks along the reduction index and A, B pointing at their first block
 // of rows.  The reduction is split into S equal runs of bricks.  With
-// cnb = 2^cnb_log2 and cni = 2^cni_log2, output element (i, j) of split s goes
+// cnb = 2^cnb_log2, output element (i, j) of split s goes
 //   out_mode 0: into a brick operand with c_nst bricks along its reduction
-//               index, at row (j / cnb) * crs + i / cni and reduction index
-//               (i % cni) * cnb + j % cnb (S = 1);
+//               index, at row (j / cnb) * crs + i % cnb and reduction index
+//               (i / cnb) * cnb + j % cnb (S = 1);
 //   out_mode 1: to interleaved accumulator-type complex values at
 //               s * c_split + (j / cnb) * cbs + i * ldc + j % cnb.
 struct GemmDesc {
@@ -225,7 +232,7 @@ struct GemmDesc {
     int64_t M, N, Kr, nst;
     int S;
     int out_mode;
-    int cnb_log2, cni_log2;
+    int cnb_log2;
     int64_t crs, c_nst;
     int64_t ldc, cbs, c_split;
     uint64_t *start;   // where the kernel stamps its start, or null

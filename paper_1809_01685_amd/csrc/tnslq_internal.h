@@ -4,8 +4,10 @@
 // matrices of R rows by Kr reduction terms, stored in bricks (operands.h):
 //   P_aeb   psi regrouped as (A, E, B): d_A rows a, reduction index (c, b')
 //           (b' fastest) of the second contraction.
-//   P_bea   psi regrouped as (B, E, A) and conjugated: d_B d_E rows (b, c),
-//           reduction index a' of the first contraction.
+//   P_eba   psi regrouped as (E, B, A) and conjugated: d_E d_B rows (c, b),
+//           reduction index a' of the first contraction.  With b fastest a tile
+//           of 128 rows is one environment index (d_B >= 128), and its outputs
+//           are whole bricks of the intermediary.
 //   Xt      the current Lanczos vectors: rows (k, b'), reduction index a'.
 //   Ups     intermediary (i) of Sec. V: rows (k, b), reduction index (c, b'),
 //           the B operand of the second contraction.
@@ -67,7 +69,7 @@ struct Plan {
     int nblk = 1;                    // reduction blocks per probe vector
     int64_t nst1 = 1, nst2 = 1;      // bricks along the reduction index of contraction 1, 2
     // workspace carve-up (byte offsets)
-    size_t off_Paeb = 0, off_Pbea = 0, off_Xt = 0, off_Ups = 0, off_Ypart = 0, off_U1part = 0;
+    size_t off_Paeb = 0, off_Peba = 0, off_Xt = 0, off_Ups = 0, off_Ypart = 0, off_U1part = 0;
     size_t off_P1s = 0, off_P2s = 0, off_Up = 0, off_U2 = 0, off_Xs = 0;
     size_t off_Pabe = 0, off_Pabc = 0, off_Cd = 0, off_rho = 0;
     size_t off_Xq = 0, off_Ym = 0;
