@@ -637,6 +637,7 @@ __global__ void __launch_bounds__(NT, 1) k_cgemm_bf16x3(GemmDesc g) {
     }
     for (; base < pend; base += X3_BODY) unroll_from<0, X3_BODY>(phase);
 
+    __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0): no copy (the clamped ones past the end) outlives the block
     f32x4 accr[TM][TN], acci[TM][TN];
 #pragma unroll
     for (int a = 0; a < TM; ++a)
@@ -649,67 +650,42 @@ __global__ void __launch_bounds__(NT, 1) k_cgemm_bf16x3(GemmDesc g) {
         store_tiles<TNSLQ_BF16X3, TM, TN, true>(g, tl.s, tl.i0 + wm * TM * 16, tl.j0 + wn * TN * 16, lane, accr, acci);
         return;
     }
-    // Output as bricks (the first contraction's intermediary), through LDS.
-    // A lane holds four columns of one row per tile, direct stores would be
-    // 8-byte pieces.  Instead, one pair of planes at a time (re, im, re + im; hi
-    // and lo) goes into LDS as [plane][row][column] and leaves in 16-byte units:
-    // 8 consecutive columns j are 8 consecutive reduction terms of one brick
-    // row when cnb >= 8, and rows i of one environment index are rows of the
-    // same bricks.  65536 x 8192 outputs over 256 terms, where a tile's output
-    // weighs as much as its 24 phases: 4350 us with rows of 2-byte writes into LDS
-    // and roundings in integers, 3380 with these.  Staging rows of 288 bytes (128
-    // columns + 16 of padding) spread a wave's 8-byte writes over the banks;
-    // plane p's rows 32 m .. 32 m + 31 live in ring buffer 4 p + m (9 KiB of
-    // its 16).
-    __builtin_amdgcn_s_waitcnt(0x0070);   // every copy (the clamped ones past the end) landed
-    __syncthreads();
-    constexpr int SROW = 288;
-    auto sbase = [&](int pm) -> char * {
-        return pm == 0 ? lA0
-                       : (pm == 1 ? lA1
-                                  : (pm == 2 ? lA2
-                                             : (pm == 3 ? lA3 : (pm == 4 ? lB0 : (pm == 5 ? lB1 : (pm == 6 ? lB2 : lB3))))));
-    };
-    const int64_t cnb_mask = ((int64_t)1 << g.cnb_log2) - 1;
+    // Output as bricks (the first contraction's intermediary).  A lane holds
+    // four columns of one row per tile: 8 bytes of a plane.  Exchanging the
+    // odd 16 lanes of the first column tile with the even ones of the second
+    // gives every lane 8 consecutive columns, a 16-byte unit when cnb >= 8 (8
+    // consecutive reduction terms of one brick row), and the wave 16 rows of 32
+    // columns: rows i of one environment index are rows of the same brick, so
+    // a store is 1 KiB of consecutive bytes of a plane.  65536 x 8192 outputs
+    // over 256 terms, where a tile's output weighs as much as its 24 phases:
+    // 4350 us with rows of 2-byte writes into LDS and roundings in integers,
+    // 3380 through LDS in 8-byte writes, 3050 this way, without LDS or barriers.
+    static_assert(TN == 2, "32 columns: a brick row");
     constexpr int64_t PS = brick_ps(TNSLQ_BF16X3);
+    const int64_t cnb_mask = ((int64_t)1 << g.cnb_log2) - 1;
+    const int64_t j = tl.j0 + wn * TN * 16 + 16 * (fk & 1) + 8 * (fk >> 1);
+    const int64_t jrow = (j >> g.cnb_log2) * g.crs, jcol = j & cnb_mask;
 #pragma unroll
-    for (int q = 0; q < 3; ++q) {
+    for (int a = 0; a < TM; ++a) {
+        const int64_t i = tl.i0 + wm * TM * 16 + a * 16 + frow;
+        uint16_t *out = (uint16_t *)g.C + brick_index(TNSLQ_BF16X3, g.c_nst, jrow + (i & cnb_mask), (i & ~cnb_mask) + jcol);
 #pragma unroll
-        for (int a = 0; a < TM; ++a) {
-            const int il0 = wm * TM * 16 + a * 16;   // 32-row group (il0 >> 5) is uniform
-            char *s0 = sbase(il0 >> 5), *s1 = sbase(4 + (il0 >> 5));
+        for (int q = 0; q < 3; ++q) {
+            uint32_t h[TN][2][2];   // tile, piece, pair of columns
 #pragma unroll
             for (int b = 0; b < TN; ++b) {
-                // row il0 + frow, columns 4 fk .. + 3 of tile b
-                const int off = ((il0 & 31) + frow) * SROW + 2 * (wn * TN * 16 + b * 16 + 4 * fk);
-                uint16_t h[4][2];
+                const f32x4 re = accr[a][b], im = acci[a][b];
+                const f32x4 v = q == 0 ? re : (q == 1 ? im : re + im);
+                split_bf16_pair(v[0], v[1], h[b][0][0], h[b][1][0]);
+                split_bf16_pair(v[2], v[3], h[b][0][1], h[b][1][1]);
+            }
 #pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const float re = accr[a][b][r], im = acci[a][b][r];
-                    split_bf16<2>(q == 0 ? re : (q == 1 ? im : re + im), h[r]);
-                }
-                *(uint2 *)(s0 + off) = make_uint2(h[0][0] | (uint32_t)h[1][0] << 16, h[2][0] | (uint32_t)h[3][0] << 16);
-                *(uint2 *)(s1 + off) = make_uint2(h[0][1] | (uint32_t)h[1][1] << 16, h[2][1] | (uint32_t)h[3][1] << 16);
+            for (int p = 0; p < 2; ++p) {
+                const auto x = __builtin_amdgcn_permlane16_swap(h[0][p][0], h[1][p][0], false, false);
+                const auto y = __builtin_amdgcn_permlane16_swap(h[0][p][1], h[1][p][1], false, false);
+                if (i < g.M && j < g.N) *(uint4 *)(out + (2 * q + p) * PS) = make_uint4(x[0], y[0], x[1], y[1]);
             }
         }
-        __syncthreads();
-#pragma unroll
-        for (int x = 0; x < 4; ++x) {
-            // units of a 64-byte brick row, then rows, then bricks: a wave
-            // stores 1 KiB of consecutive bytes per plane
-            const int R = tid + NT * x, il = (R >> 2) & (BM - 1), jl = 8 * ((R & 3) + 4 * (R >> 9));
-            const int64_t i = tl.i0 + il, j = tl.j0 + jl;
-            if (i < g.M && j < g.N) {
-                const int64_t row = (j >> g.cnb_log2) * g.crs + (i & cnb_mask);
-                const int64_t col = (i & ~cnb_mask) + (j & cnb_mask);
-                const int64_t idx = brick_index(TNSLQ_BF16X3, g.c_nst, row, col);
-                const int off = (il & 31) * SROW + 2 * jl;
-#pragma unroll
-                for (int p = 0; p < 2; ++p)
-                    *(uint4 *)((uint16_t *)g.C + idx + (2 * q + p) * PS) = *(const uint4 *)(sbase(4 * p + (il >> 5)) + off);
-            }
-        }
-        __syncthreads();
     }
 }
 

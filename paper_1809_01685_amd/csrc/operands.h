@@ -54,6 +54,15 @@ __device__ inline void split_bf16(float x, uint16_t *out) {
         r = r - bf16_to_f32(h);
     }
 }
+// split_bf16<2> of two values, their pieces packed x first.
+__device__ inline void split_bf16_pair(float x, float y, uint32_t &hi, uint32_t &lo) {
+#pragma clang fp contract(off)
+    typedef __attribute__((ext_vector_type(2))) float f32x2;
+    typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
+    hi = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2){x, y}, bf16x2));
+    const float rx = x - __uint_as_float(hi << 16), ry = y - __uint_as_float(hi & 0xffff0000u);
+    lo = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2){rx, ry}, bf16x2));
+}
 // Split an FP64 value: the first piece is taken from the double directly so
 // that the pieces capture the value to ~2^-8 per piece.
 template <int NP>
