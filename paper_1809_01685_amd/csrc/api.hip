@@ -1081,6 +1081,7 @@ struct Ctx {
     LzDims z;
     void *Paeb, *Peba, *Xt, *Ups, *Ypart, *U1part;
     void *P1s, *P2s;
+    double *chk = nullptr;           // streaming: where do_layout leaves the state's norm, or null
     void *Pabe, *Pabc, *Cd, *rho;
     double2 *Up, *U2, *Xs, *Xq, *Ym;
     const MpsPlan *mp = nullptr;     // factorised MPS operator: its factor construction
@@ -1335,7 +1336,7 @@ int do_layout(Ctx &c, const void *psi) {
         // (E, A, B), B fastest: environment slab c is a contiguous d_A x d_B
         // matrix (the panel layout with 512 columns is row-major)
         const PermDesc eab = perm_for(pl, pl.qe, pl.nE, pl.qa, pl.nA, pl.qb, pl.nB);
-        TNSLQ_HIP(launch_regroup(pl.dtype, psi, c.P1s, pl.D / 512, 512, eab, c.st));
+        TNSLQ_HIP(launch_regroup(pl.dtype, psi, 1, {{c.P1s, pl.D / 512, 512, eab}, {}}, c.chk, c.st));
         return TNSLQ_OK;
     }
     if (pl.stream) {
@@ -1345,8 +1346,8 @@ int do_layout(Ctx &c, const void *psi) {
         for (int i = 0; i < pl.nB; ++i) eb[pl.nE + i] = pl.qb[i];
         const PermDesc p1 = perm_two(pl.L, pl.qa, pl.nA, eb, pl.nE + pl.nB);
         const PermDesc p2 = perm_two(pl.L, eb, pl.nE + pl.nB, pl.qa, pl.nA);
-        TNSLQ_HIP(launch_regroup(pl.dtype, psi, c.P1s, pl.dA, pl.dE * pl.dB, p1, c.st));
-        TNSLQ_HIP(launch_regroup(pl.dtype, psi, c.P2s, pl.dE * pl.dB, pl.dA, p2, c.st));
+        TNSLQ_HIP(launch_regroup(pl.dtype, psi, 2,
+                                 {{c.P1s, pl.dA, pl.dE * pl.dB, p1}, {c.P2s, pl.dE * pl.dB, pl.dA, p2}}, c.chk, c.st));
         return TNSLQ_OK;
     }
     PermDesc aeb = perm_for(pl, pl.qa, pl.nA, pl.qe, pl.nE, pl.qb, pl.nB);
@@ -1782,7 +1783,11 @@ int run_start(Run &r, const tnslq_options *opt, const void *psi, void *ws, size_
     double *chk = (double *)(r.c.ws + r.c.pl.off_chk);
     TNSLQ_HIP(launch_zero(r.c.alpha, r.c.pl.end_out - r.c.pl.off_alpha, r.c.st));
     TNSLQ_HIP(launch_stamp(r.c.stamps, r.c.st));
-    if (!r.c.pl.mpsf) TNSLQ_HIP(launch_state_check(r.c.pl.dtype, psi, r.c.pl.D, chk, r.c.st));
+    // the streaming forms take the norm from the read that regroups psi
+    if (r.c.pl.stream)
+        r.c.chk = chk;
+    else if (!r.c.pl.mpsf)
+        TNSLQ_HIP(launch_state_check(r.c.pl.dtype, psi, r.c.pl.D, chk, r.c.st));
     roctxRangePush("tnslq layout");
     rc = slq_setup(r.c, psi, opt->seed, opt->probe_offset);
     roctxRangePop();
@@ -2059,12 +2064,10 @@ int spectral_run(const SPlan &sp, const void *psi, const tnslq_options *opt, uin
     uint64_t *stamps = (uint64_t *)(base + sp.off_stamp);
     const Stamps at{1};
     TNSLQ_HIP(launch_zero(alpha, sp.off_stamp + at.count(sp.m) * 8 - sp.off_alpha, st));
-    TNSLQ_HIP(launch_state_check(sp.dtype, psi, sp.D, chk, st));
     TNSLQ_HIP(launch_stamp(stamps, st));
     const PermDesc p1 = perm_two(sp.L, sp.side, sp.n_side, sp.rest, sp.n_rest);
     const PermDesc p2 = perm_two(sp.L, sp.rest, sp.n_rest, sp.side, sp.n_side);
-    TNSLQ_HIP(launch_regroup(sp.dtype, psi, P1, sp.d, sp.dR, p1, st));
-    TNSLQ_HIP(launch_regroup(sp.dtype, psi, P2, sp.dR, sp.d, p2, st));
+    TNSLQ_HIP(launch_regroup(sp.dtype, psi, 2, {{P1, sp.d, sp.dR, p1}, {P2, sp.dR, sp.d, p2}}, chk, st));
     TNSLQ_HIP(launch_probe_init(TNSLQ_FP64, z, opt->seed, offset, 0, Q, nullptr, 0, alpha, beta, st));
     int rc0;
     if ((rc0 = check_state(sp.dtype, chk, st))) return rc0;

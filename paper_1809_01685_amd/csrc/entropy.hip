@@ -22,6 +22,7 @@
 #include <type_traits>
 
 #include "tnslq_internal.h"
+#include "wave.h"
 
 namespace tnslq {
 namespace {
@@ -66,56 +67,150 @@ __global__ void __launch_bounds__(256) k_regroup(const void *__restrict__ psi, v
     }
 }
 
-// The same regrouping through LDS tiles, for D >= 2^TB: a tile is the 2^TB
-// elements that share every output bit outside td.wr.  They are read with the
-// input's lowest bits varying fastest (td.rd lists the tile's output bits in
-// that order: a wave reads runs of consecutive psi elements) and written with
-// the output's lowest bits varying fastest (td.wr: runs of consecutive panel
-// elements).  One LDS row of padding per 64 entries keeps the transposed
-// accesses off a single bank.
+// The regroupings of one pass over psi (one or two) through LDS tiles, for
+// L >= TB, with the state's norm and non-finite amplitudes taken from the same
+// read.  Both panel copies are permutations of psi's index bits, so a tile is
+// the 2^TB amplitudes that share every other bit, where its TB bits hold the
+// lowest bits of psi's index and of each copy's: it is read in psi's order and
+// written in each copy's, 16 bytes per lane and at least 128 consecutive bytes
+// each way.  Every index is a sum of one value per bit: a thread's bits are
+// added up once, the rest are scalars.  Slots in LDS are XORed with a mask per
+// tile bit (0 for the lowest five) that keeps the lanes of each of the orders on
+// distinct banks.  Bound by memory: a read and a write per copy.  30 qubits in
+// complex64, two copies: two passes of 4.6 ms each and 2.4 ms for the norm became
+// 5.2 ms, 5.0 TB/s.
+constexpr int RG_THREADS = 512, RG_UNITS = 8;   // 16-byte units per thread and tile: 64 KiB, two blocks per CU
+constexpr int RG_MAXBITS = 13;
+constexpr int RG_BLOCKS = 512;
+static_assert(RG_BLOCKS <= STATE_CHECK_BLOCKS, "one partial norm per block");
 struct RegroupTile {
     int nouter;
-    int outer[TNSLQ_MAX_QUBITS];   // output bits outside the tile, from the tile index
-    int rd[12], wr[12];            // the tile's output bits in read and in write order
-    int rd2wr[12];                 // position of rd[k] in wr
-    int64_t in_rd[12];             // psi index bit of rd[k]
+    int outer_in[TNSLQ_MAX_QUBITS];       // psi index bits outside the tile
+    int outer_out[2][TNSLQ_MAX_QUBITS];   // their places in the copies
+    int rd[RG_MAXBITS];                   // the tile's psi bits, ascending
+    int sw[RG_MAXBITS];                   // slot of tile bit k: (1 << k) ^ sw[k]
+    int wr[2][RG_MAXBITS];                // tile bits in the order of each copy's
+    int wd[2][RG_MAXBITS];                // and their places there
 };
 
-template <int DTYPE, int TB>
-__global__ void __launch_bounds__(256) k_regroup_tiled(const void *__restrict__ psi, void *__restrict__ out,
-                                                       int64_t R, int64_t C, int cl, PermDesc pd, RegroupTile td) {
+template <int DTYPE, int NOUT>
+__global__ void __launch_bounds__(RG_THREADS) k_regroup_tiles(const void *__restrict__ psi, int vec, int L,
+                                                              void *__restrict__ out0, void *__restrict__ out1,
+                                                              RegroupTile td, double *__restrict__ part) {
     using T = typename std::conditional<DTYPE == TNSLQ_C128, double2, float2>::type;
-    constexpr int TN = 1 << TB;
-    __shared__ T tile[TN + TN / 64];
-    const int64_t ntiles = (R * C) >> TB;
-    const int wl = cl < 9 ? cl : 9;
-    for (int64_t tl = blockIdx.x; tl < ntiles; tl += gridDim.x) {
-        int64_t ob = 0;
-        for (int k = 0; k < td.nouter; ++k) ob |= ((tl >> k) & 1) << td.outer[k];
-        int64_t ib = 0;
-        for (int t = 0; t < pd.L; ++t) ib |= ((ob >> t) & 1) << pd.map[t];
-        for (int j = threadIdx.x; j < TN; j += 256) {
-            int64_t in = ib;
-            int slot = 0;
+    constexpr int EPU = DTYPE == TNSLQ_C128 ? 1 : 2;        // elements per unit
+    constexpr int E0 = EPU - 1;                             // tile bits inside a unit
+    constexpr int TB = 12 + E0, THB = 9, NU = RG_UNITS;     // tile bits; bits from the thread
+    static_assert(RG_THREADS == 1 << THB && NU == 1 << (TB - E0 - THB) && TB <= RG_MAXBITS, "units of a tile");
+    __shared__ T tile[1 << TB];
+    __shared__ double red[RG_THREADS / 64][2];
+    const int t = threadIdx.x;
+    // psi index and slot of this thread's units, slot and place in each copy
+    int64_t in_t = 0, out_t[NOUT];
+    int rs_t = 0, ws_t[NOUT];
 #pragma unroll
-            for (int k = 0; k < TB; ++k) {
-                const int bit = (j >> k) & 1;
-                in |= (int64_t)bit << td.in_rd[k];
-                slot |= bit << td.rd2wr[k];
+    for (int o = 0; o < NOUT; ++o) out_t[o] = ws_t[o] = 0;
+#pragma unroll
+    for (int k = 0; k < THB; ++k) {
+        const int bit = (t >> k) & 1;
+        in_t |= (int64_t)bit << td.rd[k + E0];
+        rs_t ^= -bit & ((1 << (k + E0)) ^ td.sw[k + E0]);
+#pragma unroll
+        for (int o = 0; o < NOUT; ++o) {
+            out_t[o] |= (int64_t)bit << td.wd[o][k + E0];
+            const int w = td.wr[o][k + E0];
+            ws_t[o] ^= -bit & ((1 << w) ^ td.sw[w]);
+        }
+    }
+    auto load = [&](int64_t tl, T (&v)[NU][EPU]) __attribute__((always_inline)) {
+        int64_t in = in_t;
+        for (int k = 0; k < td.nouter; ++k) in |= ((tl >> k) & 1) << td.outer_in[k];
+#pragma unroll
+        for (int u = 0; u < NU; ++u) {
+            int64_t iu = in;
+#pragma unroll
+            for (int k = THB; k < TB - E0; ++k) iu |= (int64_t)((u >> (k - THB)) & 1) << td.rd[k + E0];
+            if constexpr (EPU == 1) {
+                v[u][0] = ((const T *)psi)[iu];
+            } else if (vec) {
+                const float4 f = *(const float4 *)((const T *)psi + iu);
+                v[u][0] = make_float2(f.x, f.y);
+                v[u][1] = make_float2(f.z, f.w);
+            } else {
+                v[u][0] = ((const T *)psi)[iu];
+                v[u][1] = ((const T *)psi)[iu + 1];
             }
-            tile[slot + (slot >> 6)] = ((const T *)psi)[in];
         }
-        __syncthreads();
-        for (int j = threadIdx.x; j < TN; j += 256) {
-            int64_t o = ob;
+    };
+    double s = 0.0, bad = 0.0;
+    T v[NU][EPU];
+    const int64_t ntiles = (int64_t)1 << (L - TB);
+    if (blockIdx.x < ntiles) load(blockIdx.x, v);
+    for (int64_t tl = blockIdx.x; tl < ntiles; tl += gridDim.x) {
 #pragma unroll
-            for (int k = 0; k < TB; ++k) o |= (int64_t)((j >> k) & 1) << td.wr[k];
-            // panel_index with R, C, and the panel width min(C, 512) powers of two
-            const int64_t i = o >> cl, c = o & (C - 1);
-            const int64_t dst = ((c >> wl) * R << wl) + (i << wl) + (c & ((int64_t(1) << wl) - 1));
-            ((T *)out)[dst] = tile[j + (j >> 6)];
+        for (int u = 0; u < NU; ++u) {
+            int sl = rs_t;
+#pragma unroll
+            for (int k = THB; k < TB - E0; ++k)
+                if ((u >> (k - THB)) & 1) sl ^= (1 << (k + E0)) ^ td.sw[k + E0];
+#pragma unroll
+            for (int e = 0; e < EPU; ++e) {
+                tile[sl ^ e] = v[u][e];
+                if (part) {
+                    const double re = v[u][e].x, im = v[u][e].y;
+                    if (isfinite(re) && isfinite(im))
+                        s += re * re + im * im;
+                    else
+                        bad += 1.0;
+                }
+            }
         }
         __syncthreads();
+        // the next tile's loads are in flight while this one is written
+        if (tl + gridDim.x < ntiles) load(tl + gridDim.x, v);
+#pragma unroll
+        for (int o = 0; o < NOUT; ++o) {
+            int64_t ot = out_t[o];
+            for (int k = 0; k < td.nouter; ++k) ot |= ((tl >> k) & 1) << td.outer_out[o][k];
+            T *out = (T *)(o == 0 ? out0 : out1) + ot;
+            const int w0 = E0 ? (1 << td.wr[o][0]) ^ td.sw[td.wr[o][0]] : 0;
+#pragma unroll
+            for (int u = 0; u < NU; ++u) {
+                int sl = ws_t[o];
+                int64_t ou = 0;
+#pragma unroll
+                for (int k = THB; k < TB - E0; ++k)
+                    if ((u >> (k - THB)) & 1) {
+                        const int w = td.wr[o][k + E0];
+                        sl ^= (1 << w) ^ td.sw[w];
+                        ou |= (int64_t)1 << td.wd[o][k + E0];
+                    }
+                if constexpr (EPU == 1) {
+                    out[ou] = tile[sl];
+                } else {
+                    const T x = tile[sl], y = tile[sl ^ w0];
+                    *(float4 *)(out + ou) = make_float4(x.x, x.y, y.x, y.y);
+                }
+            }
+        }
+        __syncthreads();
+    }
+    if (!part) return;
+    s = wave_total(s);
+    bad = wave_total(bad);
+    if ((t & 63) == 0) {
+        red[t >> 6][0] = s;
+        red[t >> 6][1] = bad;
+    }
+    __syncthreads();
+    if (t == 0) {
+        s = bad = 0.0;
+        for (int w = 0; w < RG_THREADS / 64; ++w) {
+            s += red[w][0];
+            bad += red[w][1];
+        }
+        part[2 * blockIdx.x] = s;
+        part[2 * blockIdx.x + 1] = bad;
     }
 }
 
@@ -483,64 +578,133 @@ hipError_t launch_sum_transpose_y(const double2 *Yt, int S, int K, int64_t dA, i
     return hipGetLastError();
 }
 
-hipError_t launch_regroup(int dtype, const void *psi, void *out, int64_t R, int64_t C, const PermDesc &pd,
+namespace {
+
+// The tile of a pass over psi's L index bits for the copies' bit places dst[o][q]
+// (psi bit q): psi's and the copies' lowest bits level by level until TB are
+// chosen, and the slot masks.
+RegroupTile regroup_tile(int L, int TB, int nout, const int (&dst)[2][TNSLQ_MAX_QUBITS]) {
+    RegroupTile td{};
+    int inv[2][TNSLQ_MAX_QUBITS];
+    for (int o = 0; o < nout; ++o)
+        for (int q = 0; q < L; ++q) inv[o][dst[o][q]] = q;
+    bool in[TNSLQ_MAX_QUBITS] = {false};
+    int n = 0;
+    for (int b = 0; b < L; ++b)
+        for (int o = -1; o < nout; ++o) {
+            const int q = o < 0 ? b : inv[o][b];
+            if (n < TB && !in[q]) {
+                in[q] = true;
+                ++n;
+            }
+        }
+    int pos[TNSLQ_MAX_QUBITS], k = 0;
+    for (int q = 0; q < L; ++q)
+        if (in[q]) {
+            pos[q] = k;
+            td.rd[k++] = q;
+        } else {
+            td.outer_in[td.nouter] = q;
+            for (int o = 0; o < nout; ++o) td.outer_out[o][td.nouter] = dst[o][q];
+            ++td.nouter;
+        }
+    for (int o = 0; o < nout; ++o) {
+        k = 0;
+        for (int t = 0; t < L; ++t)
+            if (in[inv[o][t]]) {
+                td.wr[o][k] = pos[inv[o][t]];
+                td.wd[o][k++] = t;
+            }
+    }
+    // Lanes of a half wave differ in five tile bits of each order (bits e0 ..
+    // e0 + 4, e0 the bits inside a unit); their slots' lowest five bits are a
+    // linear image of those.  Bit k's image is its own place for k < 5; the
+    // others get, in turn, the first mask that is independent of the images
+    // already given to the bits they share an order with.
+    const int e0 = TB - 12;
+    bool set[3][RG_MAXBITS] = {};
+    for (int i = e0; i < e0 + 5; ++i) {
+        set[0][i] = true;
+        for (int o = 0; o < nout; ++o) set[1 + o][td.wr[o][i]] = true;
+    }
+    for (int b = 5; b < TB; ++b) {
+        int best = 0, best_ok = -1;
+        for (int m = 0; m < 32; ++m) {
+            int ok = 0;
+            for (int g = 0; g <= nout; ++g) {
+                if (!set[g][b]) continue;
+                // is m outside the span of the images given in this order?
+                uint32_t span = 1;   // bit v: v is in the span
+                for (int i = 0; i < b; ++i) {
+                    if (!set[g][i]) continue;
+                    const int img = i < 5 ? 1 << i : td.sw[i];
+                    uint32_t more = 0;
+                    for (int x = 0; x < 32; ++x)
+                        if (span >> x & 1) more |= 1u << (x ^ img);
+                    span |= more;
+                }
+                ok += !(span >> m & 1);
+            }
+            if (ok > best_ok) {
+                best_ok = ok;
+                best = m;
+            }
+        }
+        td.sw[b] = best;
+    }
+    return td;
+}
+
+}  // namespace
+
+hipError_t launch_regroup(int dtype, const void *psi, int nout, const Regrouped (&outs)[2], double *chk,
                           hipStream_t st) {
-    const int TB = dtype == TNSLQ_C128 ? 11 : 12;   // 33 KiB of LDS either way
-    if (pd.L >= TB) {
-        // the tile: the output's 6 lowest bits, the output bits of psi's
-        // lowest TB - 6 bits, then further output bits up to TB
-        RegroupTile td{};
-        int inv[TNSLQ_MAX_QUBITS];
-        for (int t = 0; t < pd.L; ++t) inv[pd.map[t]] = t;
-        int in_tile[TNSLQ_MAX_QUBITS] = {0};
-        int nu = 0, u[12];
-        auto add = [&](int b) {
-            if (nu < TB && !in_tile[b]) {
-                in_tile[b] = 1;
-                u[nu++] = b;
-            }
-        };
-        for (int b = 0; b < 6; ++b) add(b);
-        for (int b = 0; b < TB - 6; ++b) add(inv[b]);
-        for (int b = 6; b < pd.L && nu < TB; ++b) add(b);
-        // write order: ascending output bits; read order: psi's lowest bits first
-        int nw = 0, nr = 0;
-        for (int b = 0; b < pd.L; ++b)
-            if (in_tile[b]) td.wr[nw++] = b;
-        int used[TNSLQ_MAX_QUBITS] = {0};
-        for (int b = 0; b < pd.L && nr < TB; ++b) {
-            const int ob = inv[b];
-            if (in_tile[ob] && !used[ob]) {
-                used[ob] = 1;
-                td.rd[nr++] = ob;
-            }
+    const int L = outs[0].pd.L;
+    const int TB = dtype == TNSLQ_C128 ? 12 : 13;   // 64 KiB of LDS either way
+    const int64_t D = outs[0].R * outs[0].C;
+    if (L < TB) {
+        if (chk) {
+            const hipError_t e = launch_state_check(dtype, psi, D, chk, st);
+            if (e != hipSuccess) return e;
         }
-        for (int k = 0; k < TB; ++k) {
-            for (int w = 0; w < TB; ++w)
-                if (td.wr[w] == td.rd[k]) td.rd2wr[k] = w;
-            td.in_rd[k] = pd.map[td.rd[k]];
-        }
-        td.nouter = 0;
-        for (int b = 0; b < pd.L; ++b)
-            if (!in_tile[b]) td.outer[td.nouter++] = b;
-        int cl = 0;
-        while ((int64_t(1) << cl) < C) ++cl;
-        const int64_t ntiles = (R * C) >> TB;
-        const unsigned g = (unsigned)(ntiles < 65535 * 8 ? ntiles : 65535 * 8);
-        if (dtype == TNSLQ_C128)
-            hipLaunchKernelGGL((k_regroup_tiled<TNSLQ_C128, 11>), dim3(g), dim3(256), 0, st, psi, out, R, C, cl, pd, td);
-        else
-            hipLaunchKernelGGL((k_regroup_tiled<TNSLQ_C64, 12>), dim3(g), dim3(256), 0, st, psi, out, R, C, cl, pd, td);
+        const unsigned g = (unsigned)((D + 1023) / 1024);
+        for (int o = 0; o < nout; ++o)
+            if (dtype == TNSLQ_C128)
+                hipLaunchKernelGGL((k_regroup<TNSLQ_C128>), dim3(g), dim3(256), 0, st, psi, outs[o].out, outs[o].R,
+                                   outs[o].C, outs[o].pd);
+            else
+                hipLaunchKernelGGL((k_regroup<TNSLQ_C64>), dim3(g), dim3(256), 0, st, psi, outs[o].out, outs[o].R,
+                                   outs[o].C, outs[o].pd);
         return hipGetLastError();
     }
-    int64_t g = (R * C + 1023) / 1024;
-    if (g < 1) g = 1;
-    if (g > 65535 * 8) g = 65535 * 8;
-    if (dtype == TNSLQ_C128)
-        hipLaunchKernelGGL((k_regroup<TNSLQ_C128>), dim3((unsigned)g), dim3(256), 0, st, psi, out, R, C, pd);
-    else
-        hipLaunchKernelGGL((k_regroup<TNSLQ_C64>), dim3((unsigned)g), dim3(256), 0, st, psi, out, R, C, pd);
-    return hipGetLastError();
+    // panel_index moves bit t of a copy's flat index i C + c: the panel's low
+    // bits of c stay, the rest of c goes above the rows
+    int dst[2][TNSLQ_MAX_QUBITS];
+    for (int o = 0; o < nout; ++o) {
+        int cl = 0, rl = 0;
+        while ((int64_t(1) << cl) < outs[o].C) ++cl;
+        while ((int64_t(1) << rl) < outs[o].R) ++rl;
+        const int wl = cl < 9 ? cl : 9;   // 2^9 = CM_COLS
+        for (int t = 0; t < L; ++t) dst[o][outs[o].pd.map[t]] = t < wl ? t : (t < cl ? t + rl : t - cl + wl);
+    }
+    const RegroupTile td = regroup_tile(L, TB, nout, dst);
+    const int64_t ntiles = D >> TB;
+    const unsigned g = (unsigned)(ntiles < RG_BLOCKS ? ntiles : RG_BLOCKS);
+    const int vec = (uintptr_t)psi % 16 == 0;   // complex64 in 16-byte units
+    void *o1 = nout > 1 ? outs[1].out : nullptr;
+#define TNSLQ_RG(T, N) \
+    hipLaunchKernelGGL((k_regroup_tiles<T, N>), dim3(g), dim3(RG_THREADS), 0, st, psi, vec, L, outs[0].out, o1, td, chk)
+    if (dtype == TNSLQ_C128) {
+        if (nout > 1) TNSLQ_RG(TNSLQ_C128, 2);
+        else TNSLQ_RG(TNSLQ_C128, 1);
+    } else {
+        if (nout > 1) TNSLQ_RG(TNSLQ_C64, 2);
+        else TNSLQ_RG(TNSLQ_C64, 1);
+    }
+#undef TNSLQ_RG
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess || !chk) return e;
+    return launch_state_sum((int)g, chk, st);
 }
 
 template <int KG, bool WIDE>

@@ -398,12 +398,16 @@ __global__ void __launch_bounds__(64) k_state_sum(const double *__restrict__ par
 
 hipError_t launch_state_check(int dtype, const void *psi, int64_t D, double *scratch, hipStream_t st) {
     const int nb = (int)std::max<int64_t>(1, std::min<int64_t>(STATE_CHECK_BLOCKS, (D + 4095) / 4096));
-    double *out = scratch + 2 * STATE_CHECK_BLOCKS;
     if (dtype == TNSLQ_C128)
         hipLaunchKernelGGL(k_state_partial<double2>, dim3(nb), dim3(256), 0, st, (const double2 *)psi, D, scratch);
     else
         hipLaunchKernelGGL(k_state_partial<float2>, dim3(nb), dim3(256), 0, st, (const float2 *)psi, D, scratch);
-    hipLaunchKernelGGL(k_state_sum, dim3(1), dim3(64), 0, st, (const double *)scratch, nb, out);
+    return launch_state_sum(nb, scratch, st);
+}
+
+hipError_t launch_state_sum(int nb, double *scratch, hipStream_t st) {
+    hipLaunchKernelGGL(k_state_sum, dim3(1), dim3(64), 0, st, (const double *)scratch, nb,
+                       scratch + 2 * STATE_CHECK_BLOCKS);
     return hipGetLastError();
 }
 

@@ -95,6 +95,8 @@ hipError_t launch_stamp(uint64_t *p, hipStream_t st);
 constexpr int STATE_CHECK_BLOCKS = 1024;
 constexpr size_t STATE_CHECK_BYTES = (2 * STATE_CHECK_BLOCKS + 2) * sizeof(double);
 hipError_t launch_state_check(int dtype, const void *psi, int64_t D, double *scratch, hipStream_t st);
+// Its last step, from nb pairs of partial sums at scratch.
+hipError_t launch_state_sum(int nb, double *scratch, hipStream_t st);
 
 struct PermDesc {
     int L;
@@ -199,8 +201,15 @@ hipError_t launch_features(const double *alpha, const double *beta, int K, int m
 
 // ------------------------------------------------------------ entropy
 // psi regrouped as an R x C matrix in column panels 512 wide (same dtype,
-// interleaved complex), and the sum of S partial arrays of n elements.
-hipError_t launch_regroup(int dtype, const void *psi, void *out, int64_t R, int64_t C, const PermDesc &pd,
+// interleaved complex): one or two of them in one read of psi, which also
+// gives the state's norm as launch_state_check does where chk is not null; and
+// the sum of S partial arrays of n elements.
+struct Regrouped {
+    void *out;
+    int64_t R, C;
+    PermDesc pd;
+};
+hipError_t launch_regroup(int dtype, const void *psi, int nout, const Regrouped (&outs)[2], double *chk,
                           hipStream_t st);
 // The column MAC: out(s, v, c) = sum_{i in split s} op(M[i][c]) V(v, i) over
 // an R x C panel-layout matrix M (C even, and dividing 512 when below it) for
