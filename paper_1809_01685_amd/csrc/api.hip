@@ -1636,6 +1636,32 @@ int lanczos_step(Ctx &c, int j) {
     return TNSLQ_OK;
 }
 
+// Steps j0 .. j1 of a small explicit operator in one launch.
+int small_steps(Ctx &c, int j0, int j1) {
+    const Plan &pl = c.pl;
+    SmallSteps g{};
+    g.rho = c.rho;
+    g.n = (int)pl.dAB;
+    g.nst = (int)pl.nst_rho;
+    g.S = pl.S;
+    g.K = pl.K;
+    g.m = pl.m;
+    g.reorth = pl.reorth;
+    g.j0 = j0;
+    g.j1 = j1;
+    g.Q = c.Q;
+    g.slot = (int64_t)pl.K * pl.dAB;
+    g.alpha = c.alpha;
+    g.beta = c.beta;
+    g.stamps = c.stamps + c.at.c1(1, 0);
+    g.step_stamps = (int64_t)(c.at.c1(2, 0) - c.at.c1(1, 0));
+    g.merge_stamp = (int64_t)(c.at.merge(1, 0) - c.at.c1(1, 0));
+    g.lanczos_stamp = (int64_t)(c.at.lanczos(1) - c.at.c1(1, 0));
+    TNSLQ_HIP(launch_small_steps(g, c.st));
+    c.n_launch += j1 - j0 + 1;
+    return TNSLQ_OK;
+}
+
 int slq_setup(Ctx &c, const void *psi, uint64_t seed, uint64_t offset) {
     const Plan &pl = c.pl;
     int rc;
@@ -1813,9 +1839,19 @@ int run_steps(Run &r, int jmax, double stop_tol, bool lanczos_only = false) {
     int rc;
     r.target = stop_tol > 0.0;
     r.met = false;
+    const Plan &pl = r.c.pl;
+    const bool small =
+        pl.expl && pl.prec == TNSLQ_FP64 && small_steps_supported(pl.dAB, pl.K, pl.m, pl.reorth);
+    const int check = r.rule == TNSLQ_STOP_FIT ? TNSLQ_FIT_MIN_POINTS + 1 : 6;   // first step that a target looks at
     for (int j = r.jdone + 1; j <= jmax; ++j) {
         roctxRangePush("tnslq lanczos step");
-        rc = lanczos_step(r.c, j);
+        if (small) {
+            const int j0 = j;
+            j = stop_tol <= 0.0 ? jmax : std::min(jmax, std::max(j, check));
+            rc = small_steps(r.c, j0, j);
+        } else {
+            rc = lanczos_step(r.c, j);
+        }
         roctxRangePop();
         if (rc) return rc;
         r.jdone = j;

@@ -170,6 +170,27 @@ hipError_t launch_reorth(const LzDims &z, const double *dotpart, const double2 *
 hipError_t launch_passC(int prec, const LzDims &z, const double *nrmpart, const double2 *w,
                         double2 *q_next, void *Xt, int64_t xt_nst, const double *alpha,
                         double *beta, int j, hipStream_t st);
+// Steps j0 .. j1 of the explicit FP64 operator rho (n x n bricks, nst along a
+// row) in one launch, from q_{j0} and, past the first step, q_{j0 - 1} in Q:
+// the vectors, alpha and beta as the passes leave them.  S: the splits of the
+// product that it stands for.  stamps: where step 1 stamps its start, step j
+// step_stamps (j - 1) further, the ends of its product and of passA at the two
+// offsets.  Up to 16 probes on each CU; the steps' dot products are kept by the
+// lanes of one wave.
+constexpr int SMALL_STEPS_MAX_N = 128;
+inline bool small_steps_supported(int64_t n, int K, int m, int reorth) {
+    return n <= SMALL_STEPS_MAX_N && K <= 16 * 256 && (!reorth || m <= 64);
+}
+struct SmallSteps {
+    const void *rho;
+    int n, nst, S, K, m, reorth, j0, j1;
+    double2 *Q;
+    int64_t slot;
+    double *alpha, *beta;
+    uint64_t *stamps;
+    int64_t step_stamps, merge_stamp, lanczos_stamp;
+};
+hipError_t launch_small_steps(const SmallSteps &g, hipStream_t st);
 // fn: TNSLQ_F_ABS, TNSLQ_F_ENTROPY or TNSLQ_F_PURITY
 hipError_t launch_quadrature(const double *alpha, const double *beta, const int *steps, int K,
                              int m, int jlo, int jhi, int fn, double *F, hipStream_t st);

@@ -36,4 +36,21 @@ __device__ inline double wave_total(double v) {
     return lane_value(v, 63);
 }
 
+// The same sum in the order of a shuffle-down tree: lanes 32 apart, then 16, 8,
+// 4, 2 and 1, returned to every lane.
+__device__ inline double wave_tree_total(double v) {
+    auto halves = [](double x, auto swap) {
+        const long long b = __double_as_longlong(x);
+        const auto lo = swap((unsigned)b), hi = swap((unsigned)(b >> 32));
+        return __longlong_as_double(((long long)hi[0] << 32) | lo[0]) +
+               __longlong_as_double(((long long)hi[1] << 32) | lo[1]);
+    };
+    v = halves(v, [](unsigned u) { return __builtin_amdgcn_permlane32_swap(u, u, false, false); });
+    v = halves(v, [](unsigned u) { return __builtin_amdgcn_permlane16_swap(u, u, false, false); });
+    v = dpp_add<0x128, 0xf>(v);   // row_ror:8
+    v = dpp_add<0x124, 0xf>(v);   // row_ror:4
+    v = dpp_add<0x4E, 0xf>(v);    // quad_perm [2, 3, 0, 1]
+    return dpp_add<0xB1, 0xf>(v);   // quad_perm [1, 0, 3, 2]
+}
+
 }  // namespace tnslq
