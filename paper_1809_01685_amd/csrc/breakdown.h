@@ -23,13 +23,8 @@ __device__ inline int first_break(const double *alpha_k, const double *beta_k, i
         const double next = in ? beta_k[s] : INFINITY;
         a = fmax(a, amax);
         b = fmax(b, bmax);
-        for (int o = 1; o < 64; o <<= 1) {
-            const double ua = __shfl_up(a, o, 64), ub = __shfl_up(b, o, 64);
-            if (lane >= o) {
-                a = fmax(a, ua);
-                b = fmax(b, ub);
-            }
-        }
+        a = wave_scan_max(a);
+        b = wave_scan_max(b);
         const unsigned long long hit = __ballot(in && next <= BREAKDOWN_TOL * (a + b));
         if (hit) return s0 + __builtin_ctzll(hit) + 1;
         amax = lane_value(a, 63);

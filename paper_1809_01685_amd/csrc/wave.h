@@ -5,14 +5,18 @@
 
 namespace tnslq {
 
-// v plus its DPP-moved copy (both 32-bit halves moved alike); lanes of rows
-// outside ROWS add 0
+// v's DPP-moved copy (both 32-bit halves moved alike); 0 in lanes of rows
+// outside ROWS and in those without a source
 template <int CTRL, int ROWS>
-__device__ inline double dpp_add(double v) {
+__device__ inline double dpp_move(double v) {
     const long long b = __double_as_longlong(v);
     const int lo = __builtin_amdgcn_update_dpp(0, (int)b, CTRL, ROWS, 0xf, false);
     const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, ROWS, 0xf, false);
-    return v + __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+    return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
+template <int CTRL, int ROWS>
+__device__ inline double dpp_add(double v) {
+    return v + dpp_move<CTRL, ROWS>(v);
 }
 
 // lane `lane`'s value (uniform `lane`), in every lane
@@ -51,6 +55,17 @@ __device__ inline double wave_tree_total(double v) {
     v = dpp_add<0x124, 0xf>(v);   // row_ror:4
     v = dpp_add<0x4E, 0xf>(v);    // quad_perm [2, 3, 0, 1]
     return dpp_add<0xB1, 0xf>(v);   // quad_perm [1, 0, 3, 2]
+}
+
+// Lane i: the largest of lanes 0 .. i, for values that are not negative (a NaN
+// counts as nothing, as with fmax).
+__device__ inline double wave_scan_max(double v) {
+    v = fmax(v, dpp_move<0x111, 0xf>(v));   // row_shr:1, 2, 4, 8
+    v = fmax(v, dpp_move<0x112, 0xf>(v));
+    v = fmax(v, dpp_move<0x114, 0xf>(v));
+    v = fmax(v, dpp_move<0x118, 0xf>(v));
+    v = fmax(v, dpp_move<0x142, 0xa>(v));   // row_bcast:15 into rows 1 and 3
+    return fmax(v, dpp_move<0x143, 0xc>(v));   // row_bcast:31 into rows 2 and 3
 }
 
 }  // namespace tnslq
