@@ -50,29 +50,30 @@ constexpr int TM = BM / (16 * WAVES_M), TN = BN / (16 * WAVES_N);
 constexpr int NT = 64 * WAVES_M * WAVES_N;
 static_assert(BM * ROWB / 16 == NT, "one 16-byte unit of every brick plane per thread");
 
-// Output tile (i0, j0) and reduction split s of block blockIdx.x: the
-// hardware deals blocks to the XCDs round robin, so block b is renumbered to
-// give XCD b % 8 a contiguous range, walked in groups of GROUP_M tile rows.
+// Output tile (i0, j0) and reduction split s of block b of nb (blockIdx.x of
+// gridDim.x): the hardware deals blocks to the XCDs round robin, so block b is
+// renumbered to give XCD b % 8 a contiguous range, walked in groups of GROUP_M
+// tile rows.  In 32 bits (launches hold nb below 2^31): a 64-bit division is a
+// microsecond of scalar code.
 struct TileAt {
     int64_t i0, j0, sbeg, send;
     int s;
 };
 template <int TBN = BN>
-__device__ inline TileAt tile_of(const GemmDesc &g) {
-    const int64_t ntm = (g.M + BM - 1) / BM, ntn = (g.N + TBN - 1) / TBN;
-    const int64_t per_split = ntm * ntn;
-    int64_t bid = blockIdx.x;
-    if (gridDim.x % 8 == 0) bid = (bid % 8) * (gridDim.x / 8) + bid / 8;
+__device__ inline TileAt tile_of(const GemmDesc &g, uint32_t b, uint32_t nb) {
+    const uint32_t ntm = (uint32_t)((g.M + BM - 1) / BM), ntn = (uint32_t)((g.N + TBN - 1) / TBN);
+    const uint32_t per_split = ntm * ntn;
+    if (nb % 8 == 0) b = (b % 8) * (nb / 8) + b / 8;
     TileAt r;
-    r.s = (int)(bid / per_split);
-    const int64_t t = bid % per_split;
-    const int64_t group = t / (GROUP_M * ntn);
-    const int64_t first_m = group * GROUP_M;
-    const int64_t gsize = (ntm - first_m) < GROUP_M ? (ntm - first_m) : GROUP_M;
-    r.i0 = (first_m + (t % (GROUP_M * ntn)) % gsize) * BM;
-    r.j0 = ((t % (GROUP_M * ntn)) / gsize) * TBN;
-    const int64_t per = g.nst / g.S;
-    r.sbeg = (int64_t)r.s * per;
+    r.s = (int)(b / per_split);
+    const uint32_t t = b % per_split;
+    const uint32_t group = t / (GROUP_M * ntn), in_group = t % (GROUP_M * ntn);
+    const uint32_t first_m = group * GROUP_M;
+    const uint32_t gsize = ntm - first_m < GROUP_M ? ntm - first_m : GROUP_M;
+    r.i0 = (int64_t)(first_m + in_group % gsize) * BM;
+    r.j0 = (int64_t)(in_group / gsize) * TBN;
+    const int64_t per = (uint32_t)g.nst / (uint32_t)g.S;
+    r.sbeg = r.s * per;
     r.send = r.sbeg + per;
     return r;
 }
@@ -117,7 +118,7 @@ __global__ void __launch_bounds__(NT, 1) k_cgemm_fp64(GemmDesc g) {
     __shared__ __attribute__((aligned(16))) char lB0[BSTEP], lB1[BSTEP], lB2[BSTEP], lB3[BSTEP];
     const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
     const int wm = wid / D_WAVES_N, wn = wid % D_WAVES_N;
-    const TileAt tl = tile_of<D_BN>(g);
+    const TileAt tl = tile_of<D_BN>(g, blockIdx.x, gridDim.x);
     const int64_t p0 = tl.sbeg, pend = tl.send, plast = pend - 1;
     const size_t blk = brick_block_bytes(TNSLQ_FP64, g.nst);
     const char *gA = (const char *)g.A + (size_t)(tl.i0 / BM) * blk;
@@ -311,7 +312,7 @@ __global__ void __launch_bounds__(NT, 1) k_cgemm_fp32(GemmDesc g) {
     typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
     const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
     const int wm = wid / WAVES_N, wn = wid % WAVES_N;
-    const TileAt tl = tile_of(g);
+    const TileAt tl = tile_of(g, blockIdx.x, gridDim.x);
     const size_t blk = brick_block_bytes(TNSLQ_FP32, g.nst);
     const char *gA = (const char *)g.A + (size_t)(tl.i0 / BM) * blk + 16 * tid;
     const char *gB = (const char *)g.B + (size_t)(tl.j0 / BN) * blk + 16 * tid;
@@ -499,8 +500,19 @@ hipError_t launch_fp32(const GemmDesc &g, hipStream_t st) {
 // 244 / 244 ms per launch against 283 / 282, 14% rather than 25%, the rest
 // taken by the 1.5x bytes staged per step (with the copies left out the loop
 // took 189 ms) and the power they cost under the chip's power limit.
+// Runs of up to X3_WALK bricks: a block per CU walks its tiles, and past a
+// tile's last phase the copies go on with the next tile's first four, in flight
+// through the tile's stores, so that a tile does not start with empty buffers
+// (where its phases are a multiple of the loop body; others start anew): 65536 x
+// 8192 outputs over 256 terms 3040 to 2930 us, 508 to 496 us over 1024 terms of
+// a 22-qubit state.  Longer runs take a block per tile: their start is 1 us in
+// 65, and blocks dealt as CUs come free keep neighbouring tiles together (a
+// 28-qubit estimate, 65536 x 32768 over 4096 terms and back, took 1525 ms walked
+// and 1482 dealt).
 constexpr int PHB = 2 * TILEB;    // one pair of planes of one operand: 16 KiB
 constexpr int X3_BODY = 12;       // phases per loop iteration: lcm(2 sets, 3 products, 4 buffers)
+constexpr int X3_BLOCKS = 256;    // one per CU
+constexpr int X3_WALK = 32;
 
 __global__ void __launch_bounds__(NT, 1) k_cgemm_bf16x3(GemmDesc g) {
     stamp(g.start);
@@ -508,12 +520,18 @@ __global__ void __launch_bounds__(NT, 1) k_cgemm_bf16x3(GemmDesc g) {
     __shared__ __attribute__((aligned(16))) char lB0[PHB], lB1[PHB], lB2[PHB], lB3[PHB];
     const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
     const int wm = wid / WAVES_N, wn = wid % WAVES_N;
-    const TileAt tl = tile_of(g);
-    // phases of this block's run of bricks (3 per brick)
-    const int64_t p0 = 3 * tl.sbeg, pend = 3 * tl.send, plast = pend - 1;
+    // the block's tiles: blockIdx.x, blockIdx.x + gridDim.x, ..
+    const uint32_t ntiles = (uint32_t)((g.M + BM - 1) / BM * ((g.N + BN - 1) / BN) * g.S);
     const size_t blk = brick_block_bytes(TNSLQ_BF16X3, g.nst);
-    const char *gA = (const char *)g.A + (size_t)(tl.i0 / BM) * blk;
-    const char *gB = (const char *)g.B + (size_t)(tl.j0 / BN) * blk;
+    TileAt tl = tile_of(g, blockIdx.x, ntiles);
+    // phases of the tile's run of bricks (3 per brick), as many in every tile
+    const int64_t np = 3 * (tl.send - tl.sbeg);
+    const char *gA = (const char *)g.A + (size_t)(tl.i0 / BM) * blk + 3 * tl.sbeg * PHB;
+    const char *gB = (const char *)g.B + (size_t)(tl.j0 / BN) * blk + 3 * tl.sbeg * PHB;
+    // what follows the run: the next tile's first phases, or the last phase again
+    const char *nA = gA, *nB = gB;
+    const int u0 = (int)((X3_BODY - (uint32_t)np % X3_BODY) % X3_BODY);
+    const bool seam = u0 == 0;
     const uint32_t toff = 16u * (uint32_t)tid;
     const int wofs = 1024 * __builtin_amdgcn_readfirstlane(wid);
     auto bufA = [&](auto bb) -> char * {
@@ -524,12 +542,12 @@ __global__ void __launch_bounds__(NT, 1) k_cgemm_bf16x3(GemmDesc g) {
         constexpr int B = decltype(bb)::value;
         return B == 0 ? lB0 : (B == 1 ? lB1 : (B == 2 ? lB2 : lB3));
     };
-    // copy phase ph (the last phase again past the end of the run) into
-    // buffer bb: thread t copies bytes [16 t, 16 t + 16) of both plane tiles
-    // of A and of B
+    // copy phase ph into buffer bb: thread t copies bytes [16 t, 16 t + 16) of
+    // both plane tiles of A and of B
     auto dma = [&](int64_t ph, auto bb) __attribute__((always_inline)) {
-        const int64_t q = ph <= plast ? ph : plast;
-        const char *pa = gA + q * PHB, *pb = gB + q * PHB;
+        const bool past = ph >= np;
+        const int64_t q = !past ? ph : (seam ? ph - np : np - 1);
+        const char *pa = (past ? nA : gA) + q * PHB, *pb = (past ? nB : gB) + q * PHB;
         char *As = bufA(bb) + wofs, *Bs = bufB(bb) + wofs;
 #pragma unroll
         for (int p = 0; p < 2; ++p) {
@@ -609,47 +627,25 @@ __global__ void __launch_bounds__(NT, 1) k_cgemm_bf16x3(GemmDesc g) {
         __builtin_amdgcn_sched_barrier(0);
     };
     // the run starts at body position U0 (0, 3, 6 or 9), so that it ends with
-    // a whole body: phases p0 .. p0 + 3 into buffers U0 .. U0 + 3 (mod 4),
-    // phase p0's fragments into set U0 % 2, then body positions U0 .. 11
+    // a whole body: phases 0 .. 3 into buffers U0 .. U0 + 3 (mod 4), phase 0's
+    // fragments into set U0 % 2, then body positions U0 .. 11
     auto start = [&](auto u0) __attribute__((always_inline)) {
         constexpr int V = decltype(u0)::value;
-        dma(p0, std::integral_constant<int, V % 4>{});
-        dma(p0 + 1, std::integral_constant<int, (V + 1) % 4>{});
-        dma(p0 + 2, std::integral_constant<int, (V + 2) % 4>{});
-        dma(p0 + 3, std::integral_constant<int, (V + 3) % 4>{});
-        __builtin_amdgcn_s_waitcnt(0x0f7c);   // vmcnt(12): phase p0 landed
+        dma(0, std::integral_constant<int, V % 4>{});
+        dma(1, std::integral_constant<int, (V + 1) % 4>{});
+        dma(2, std::integral_constant<int, (V + 2) % 4>{});
+        dma(3, std::integral_constant<int, (V + 3) % 4>{});
+        __builtin_amdgcn_s_waitcnt(0x0f7c);   // vmcnt(12): phase 0 landed
         __builtin_amdgcn_s_barrier();
         __builtin_amdgcn_sched_barrier(0);
         rd(std::integral_constant<int, V % 2>{}, std::integral_constant<int, V % 4>{});
-        __builtin_amdgcn_s_waitcnt(0x0078);   // vmcnt(8): phase p0 + 1 landed; lgkmcnt(0)
+        __builtin_amdgcn_s_waitcnt(0x0078);   // vmcnt(8): phase 1 landed; lgkmcnt(0)
         __builtin_amdgcn_s_barrier();
         __builtin_amdgcn_sched_barrier(0);
-        base = p0 - V;
+        base = -V;
         unroll_from<V, X3_BODY>(phase);
         base += X3_BODY;
     };
-    const int u0 = (int)((X3_BODY - (pend - p0) % X3_BODY) % X3_BODY);
-    switch (u0) {
-        case 3: start(std::integral_constant<int, 3>{}); break;
-        case 6: start(std::integral_constant<int, 6>{}); break;
-        case 9: start(std::integral_constant<int, 9>{}); break;
-        default: start(std::integral_constant<int, 0>{}); break;
-    }
-    for (; base < pend; base += X3_BODY) unroll_from<0, X3_BODY>(phase);
-
-    __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0): no copy (the clamped ones past the end) outlives the block
-    f32x4 accr[TM][TN], acci[TM][TN];
-#pragma unroll
-    for (int a = 0; a < TM; ++a)
-#pragma unroll
-        for (int b = 0; b < TN; ++b) {
-            accr[a][b] = t[0][a][b] - t[1][a][b];
-            acci[a][b] = t[2][a][b] - t[0][a][b] - t[1][a][b];
-        }
-    if (g.out_mode != 0 || g.cnb_log2 < 3) {
-        store_tiles<TNSLQ_BF16X3, TM, TN, true>(g, tl.s, tl.i0 + wm * TM * 16, tl.j0 + wn * TN * 16, lane, accr, acci);
-        return;
-    }
     // Output as bricks (the first contraction's intermediary).  A lane holds
     // four columns of one row per tile: 8 bytes of a plane.  Exchanging the
     // odd 16 lanes of the first column tile with the even ones of the second
@@ -659,39 +655,107 @@ __global__ void __launch_bounds__(NT, 1) k_cgemm_bf16x3(GemmDesc g) {
     // a store is 1 KiB of consecutive bytes of a plane.  65536 x 8192 outputs
     // over 256 terms, where a tile's output weighs as much as its 24 phases:
     // 4350 us with rows of 2-byte writes into LDS and roundings in integers,
-    // 3380 through LDS in 8-byte writes, 3050 this way, without LDS or barriers.
-    static_assert(TN == 2, "32 columns: a brick row");
-    constexpr int64_t PS = brick_ps(TNSLQ_BF16X3);
-    const int64_t cnb_mask = ((int64_t)1 << g.cnb_log2) - 1;
-    const int64_t j = tl.j0 + wn * TN * 16 + 16 * (fk & 1) + 8 * (fk >> 1);
-    const int64_t jrow = (j >> g.cnb_log2) * g.crs, jcol = j & cnb_mask;
+    // 3380 through LDS in 8-byte writes, 3040 this way, without LDS or barriers.
+    auto store_bricks = [&](const TileAt &tl, int lane, const f32x4 (&accr)[TM][TN], const f32x4 (&acci)[TM][TN])
+                            __attribute__((always_inline)) {
+        const int frow = lane & 15, fk = lane >> 4;
+        static_assert(TN == 2, "32 columns: a brick row");
+        constexpr int64_t PS = brick_ps(TNSLQ_BF16X3);
+        const int64_t cnb_mask = ((int64_t)1 << g.cnb_log2) - 1;
+        const int64_t j = tl.j0 + wn * TN * 16 + 16 * (fk & 1) + 8 * (fk >> 1);
+        const int64_t jrow = (j >> g.cnb_log2) * g.crs, jcol = j & cnb_mask;
 #pragma unroll
-    for (int a = 0; a < TM; ++a) {
-        const int64_t i = tl.i0 + wm * TM * 16 + a * 16 + frow;
-        uint16_t *out = (uint16_t *)g.C + brick_index(TNSLQ_BF16X3, g.c_nst, jrow + (i & cnb_mask), (i & ~cnb_mask) + jcol);
+        for (int a = 0; a < TM; ++a) {
+            const int64_t i = tl.i0 + wm * TM * 16 + a * 16 + frow;
+            uint16_t *out = (uint16_t *)g.C + brick_index(TNSLQ_BF16X3, g.c_nst, jrow + (i & cnb_mask), (i & ~cnb_mask) + jcol);
 #pragma unroll
-        for (int q = 0; q < 3; ++q) {
-            uint32_t h[TN][2][2];   // tile, piece, pair of columns
+            for (int q = 0; q < 3; ++q) {
+                uint32_t h[TN][2][2];   // tile, piece, pair of columns
 #pragma unroll
-            for (int b = 0; b < TN; ++b) {
-                const f32x4 re = accr[a][b], im = acci[a][b];
-                const f32x4 v = q == 0 ? re : (q == 1 ? im : re + im);
-                split_bf16_pair(v[0], v[1], h[b][0][0], h[b][1][0]);
-                split_bf16_pair(v[2], v[3], h[b][0][1], h[b][1][1]);
-            }
+                for (int b = 0; b < TN; ++b) {
+                    const f32x4 re = accr[a][b], im = acci[a][b];
+                    const f32x4 v = q == 0 ? re : (q == 1 ? im : re + im);
+                    split_bf16_pair(v[0], v[1], h[b][0][0], h[b][1][0]);
+                    split_bf16_pair(v[2], v[3], h[b][0][1], h[b][1][1]);
+                }
 #pragma unroll
-            for (int p = 0; p < 2; ++p) {
-                const auto x = __builtin_amdgcn_permlane16_swap(h[0][p][0], h[1][p][0], false, false);
-                const auto y = __builtin_amdgcn_permlane16_swap(h[0][p][1], h[1][p][1], false, false);
-                if (i < g.M && j < g.N) *(uint4 *)(out + (2 * q + p) * PS) = make_uint4(x[0], y[0], x[1], y[1]);
+                for (int p = 0; p < 2; ++p) {
+                    const auto x = __builtin_amdgcn_permlane16_swap(h[0][p][0], h[1][p][0], false, false);
+                    const auto y = __builtin_amdgcn_permlane16_swap(h[0][p][1], h[1][p][1], false, false);
+                    if (i < g.M && j < g.N) *(uint4 *)(out + (2 * q + p) * PS) = make_uint4(x[0], y[0], x[1], y[1]);
+                }
             }
         }
+    };
+
+    for (uint32_t at = blockIdx.x;; at += gridDim.x) {
+        const bool last = at + gridDim.x >= ntiles;
+        TileAt next = tl;
+        if (!last) {
+            next = tile_of(g, at + gridDim.x, ntiles);
+            nA = (const char *)g.A + (size_t)(next.i0 / BM) * blk + 3 * next.sbeg * PHB;
+            nB = (const char *)g.B + (size_t)(next.j0 / BN) * blk + 3 * next.sbeg * PHB;
+        } else {
+            nA = gA;
+            nB = gB;
+        }
+        if (seam && at != blockIdx.x) {
+            // phases 0 and 1 are there, 2 and 3 on their way; phase 0's
+            // fragments again, rather than held through the last tile's stores
+            rd(std::integral_constant<int, 0>{}, std::integral_constant<int, 0>{});
+            __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt(0)
+            __builtin_amdgcn_s_barrier();
+            __builtin_amdgcn_sched_barrier(0);
+            base = 0;
+        } else {
+            switch (u0) {
+                case 3: start(std::integral_constant<int, 3>{}); break;
+                case 6: start(std::integral_constant<int, 6>{}); break;
+                case 9: start(std::integral_constant<int, 9>{}); break;
+                default: start(std::integral_constant<int, 0>{}); break;
+            }
+        }
+        for (; base < np; base += X3_BODY) unroll_from<0, X3_BODY>(phase);
+        if (last || !seam) {
+            // no copy outlives the block, and none is in a buffer that start() fills
+            __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0)
+            __builtin_amdgcn_s_barrier();
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    f32x4 accr[TM][TN], acci[TM][TN];
+#pragma unroll
+    for (int a = 0; a < TM; ++a)
+#pragma unroll
+        for (int b = 0; b < TN; ++b) {
+            accr[a][b] = t[0][a][b] - t[1][a][b];
+            acci[a][b] = t[2][a][b] - t[0][a][b] - t[1][a][b];
+        }
+        // the addresses of the stores are worked out here, not kept in registers
+        // through the next tile
+        int elane = lane;
+        asm volatile("" : "+v"(elane));
+        if (g.out_mode != 0 || g.cnb_log2 < 3) {
+            store_tiles<TNSLQ_BF16X3, TM, TN, true>(g, tl.s, tl.i0 + wm * TM * 16, tl.j0 + wn * TN * 16, elane, accr, acci);
+        } else {
+            store_bricks(tl, elane, accr, acci);
+        }
+        if (last) break;
+        tl = next;
+        gA = nA;
+        gB = nB;
+#pragma unroll
+        for (int q = 0; q < 3; ++q)
+#pragma unroll
+            for (int a = 0; a < TM; ++a)
+#pragma unroll
+                for (int b = 0; b < TN; ++b) t[q][a][b] = f32x4{0, 0, 0, 0};
     }
 }
 
 hipError_t launch_bf16x3(const GemmDesc &g, hipStream_t st) {
-    const int64_t nblocks = ((g.M + BM - 1) / BM) * ((g.N + BN - 1) / BN) * g.S;
-    if (nblocks < 1 || nblocks > 0x7fffffff) return hipErrorInvalidConfiguration;
+    const int64_t ntiles = ((g.M + BM - 1) / BM) * ((g.N + BN - 1) / BN) * g.S;
+    if (ntiles < 1 || ntiles > 0x7fffffff) return hipErrorInvalidConfiguration;
+    const int64_t nblocks = g.nst / g.S <= X3_WALK ? std::min<int64_t>(ntiles, X3_BLOCKS) : ntiles;
     hipLaunchKernelGGL(k_cgemm_bf16x3, dim3((unsigned)nblocks), dim3(NT), 0, st, g);
     return hipGetLastError();
 }
@@ -722,7 +786,7 @@ __global__ void __launch_bounds__(X6_NT, 1) k_cgemm_bf16x6(GemmDesc g) {
     __shared__ __attribute__((aligned(16))) char ldsA0[ABRICK], ldsA1[ABRICK], ldsB0[BSTAGE], ldsB1[BSTAGE];
     const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
     const int wm = wid / X6_WAVES_N, wn = wid % X6_WAVES_N;
-    const TileAt tl = tile_of<X6_BN>(g);
+    const TileAt tl = tile_of<X6_BN>(g, blockIdx.x, gridDim.x);
     const int64_t sbeg = tl.sbeg, send = tl.send;
 
     const size_t blk = brick_block_bytes(TNSLQ_BF16X6, g.nst);
