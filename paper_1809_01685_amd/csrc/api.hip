@@ -1620,8 +1620,34 @@ int lanczos_step(Ctx &c, int j) {
             return rc;
         }
         // the streaming passes leave Y already summed over their splits
-        TNSLQ_HIP(launch_passA(accfp64, c.z, pl.stream && !pl.fused ? (const void *)c.Ym : c.Ypart,
-                               pl.stream && !pl.fused ? 1 : pl.S,
+        const bool summed = pl.stream && !pl.fused;
+        if (kcur == pl.K && step_rest_supported(n, pl.K, j, pl.reorth, pl.nblk)) {
+            StepRest g{};
+            g.part = summed ? (const void *)c.Ym : c.Ypart;
+            g.S = summed ? 1 : pl.S;
+            g.split = (int64_t)pl.kc * n;
+            g.n = (int)n;
+            g.m = pl.m;
+            g.j = j;
+            g.nblk = pl.nblk;
+            g.reorth = pl.reorth;
+            g.rchunk = reorth_chunk(n, pl.K);
+            g.slot = slot;
+            g.q_prev = q_prev;
+            g.q_cur = q_cur;
+            g.Q = c.Q;
+            g.q_next = q_next;
+            g.Xt = pl.stream ? nullptr : c.Xt;
+            g.xt_nst = pl.nst1;
+            g.dB = c.z.dB;
+            g.alpha = c.alpha;
+            g.beta = c.beta;
+            g.merge_stamp = c.stamps + c.at.merge(j, ch);
+            g.lanczos_stamp = c.stamps + c.at.lanczos(j);
+            TNSLQ_HIP(launch_step_rest(accfp64, pl.prec, g, pl.K, c.st));
+            return TNSLQ_OK;
+        }
+        TNSLQ_HIP(launch_passA(accfp64, c.z, summed ? (const void *)c.Ym : c.Ypart, summed ? 1 : pl.S,
                                (int64_t)pl.kc * n, k0, kcur, q_prev, q_cur, c.w, c.alpha, c.beta, j, c.dotpart,
                                c.st, c.stamps + c.at.merge(j, ch)));
     }

@@ -191,6 +191,30 @@ struct SmallSteps {
     int64_t step_stamps, merge_stamp, lanczos_stamp;
 };
 hipError_t launch_small_steps(const SmallSteps &g, hipStream_t st);
+// What follows the contraction in step j of short vectors, one block per probe:
+// passA (the S partials at `part`, `split` apart), passB or the
+// reorthogonalisation (stored vectors Q, `slot` apart) and passC.  nblk and
+// rchunk: the blocks of the general passes and the chunks of the general dot
+// products, whose order of summation it keeps.
+constexpr int STEP_REST_MAX_N = 1024;
+constexpr int STEP_REST_UNITS = 16;   // 64 elements of a general block each
+inline bool step_rest_supported(int64_t n, int K, int j, int reorth, int nblk) {
+    if (n > STEP_REST_MAX_N || K > 512 || nblk < 1 || (reorth && j * n > 16384)) return false;
+    const int64_t chunk = (n + nblk - 1) / nblk;
+    return chunk <= 256 && nblk * ((chunk + 63) / 64) <= STEP_REST_UNITS;
+}
+struct StepRest {
+    const void *part;
+    int n, S, m, j, nblk, reorth, rchunk;
+    int64_t split, slot, xt_nst, dB;
+    const double2 *q_prev, *q_cur, *Q;
+    double2 *q_next;
+    void *Xt;
+    double *alpha, *beta;
+    uint64_t *merge_stamp, *lanczos_stamp;
+};
+// accfp64: FP64 partials (Xt then FP64 or null), else FP32 and `prec` bricks
+hipError_t launch_step_rest(int accfp64, int prec, const StepRest &g, int K, hipStream_t st);
 // fn: TNSLQ_F_ABS, TNSLQ_F_ENTROPY or TNSLQ_F_PURITY
 hipError_t launch_quadrature(const double *alpha, const double *beta, const int *steps, int K,
                              int m, int jlo, int jhi, int fn, double *F, hipStream_t st);
