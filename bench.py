@@ -22,11 +22,14 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 METRIC = "s per ±1% logneg estimate @26-qubit ρ_AB; ρ^T_B matvec GB/s or MFMA util"
-PEAK_TFLOPS = {"bf16x3": 2500.0, "bf16x6": 2500.0, "fp32": 157.3, "fp64": 78.6}
+# the matrix cores that the contractions of each precision run on (FP32 on the
+# BF16 ones, in exact pieces)
+PEAK_TFLOPS = {"bf16x3": 2500.0, "bf16x6": 2500.0, "fp32": 2500.0, "fp64": 78.6}
 # matrix-core products per real product of the algorithm (4 per complex
 # product): split BF16 takes 3 products of pieces per real product and 3 real
-# products per complex one (9 / 4); BF16X6 6 products of pieces, 4 real products
-MFMA_PER_ALGO = {"bf16x3": 2.25, "bf16x6": 6.0, "fp32": 1.0, "fp64": 1.0}
+# products per complex one (9 / 4); BF16X6 6 products of pieces, 4 real
+# products; FP32 6 products of pieces, 3 real products; FP64 3 real products
+MFMA_PER_ALGO = {"bf16x3": 2.25, "bf16x6": 6.0, "fp32": 4.5, "fp64": 0.75}
 # rocprofv3 counter summary of the split-BF16 contraction kernel at the default workload
 COUNTERS = os.path.join(ROOT, "profiles", "gemm_bf16x3_haar30_counters.txt")
 
