@@ -1,5 +1,5 @@
 // The 16 x 16 tiles of the contraction kernels: fragments of brick rows, one
-// reduction stage of the complex product in FP32 or FP64, and the epilogue.
+// reduction stage of the complex product in FP64, and the epilogue.
 #pragma once
 #include "operands.h"
 
@@ -32,8 +32,8 @@ template <> struct MP<TNSLQ_FP64> {
     static constexpr int NPL = 2;
     using acc = f64x4;
 };
-// a 16-byte unit of a brick row feeds one 16x16x32 BF16 MFMA, four 16x16x4
-// FP32 MFMAs or two 16x16x4 FP64 MFMAs per lane
+// a 16-byte unit of a brick row feeds one 16x16x32 BF16 MFMA per lane, two of
+// them one in FP32 (split in BF16 pieces), and one two 16x16x4 FP64 MFMAs
 static_assert(brick_epr(TNSLQ_BF16X3) == 32 && brick_epr(TNSLQ_FP32) == 16 && brick_epr(TNSLQ_FP64) == 8,
               "brick rows of 64 bytes");
 static_assert(MP<TNSLQ_BF16X3>::NPL == planes_of(TNSLQ_BF16X3) && MP<TNSLQ_BF16X6>::NPL == planes_of(TNSLQ_BF16X6) &&
@@ -44,13 +44,7 @@ __device__ inline bf16x8 as_bf16x8(uint4 v) { return __builtin_bit_cast(bf16x8, 
 __device__ inline uint4 neg_bf16x8(uint4 v) {
     return make_uint4(v.x ^ 0x80008000u, v.y ^ 0x80008000u, v.z ^ 0x80008000u, v.w ^ 0x80008000u);
 }
-__device__ inline uint4 neg_f32x4(uint4 v) {
-    return make_uint4(v.x ^ 0x80000000u, v.y ^ 0x80000000u, v.z ^ 0x80000000u, v.w ^ 0x80000000u);
-}
 __device__ inline uint4 neg_f64x2(uint4 v) { return make_uint4(v.x, v.y ^ 0x80000000u, v.z, v.w ^ 0x80000000u); }
-__device__ inline float f32_at(uint4 v, int t) {
-    return __uint_as_float(t == 0 ? v.x : (t == 1 ? v.y : (t == 2 ? v.z : v.w)));
-}
 __device__ inline double f64_at(uint4 v, int t) {
     return t == 0 ? __hiloint2double((int)v.y, (int)v.x) : __hiloint2double((int)v.w, (int)v.z);
 }
@@ -58,48 +52,26 @@ __device__ inline double f64_at(uint4 v, int t) {
 // byte offset of 16-byte unit `u` of staged row `row` within a plane tile
 __device__ inline int loff(int row, int u) { return row * ROWB + 16 * (u ^ brick_swizzle(row)); }
 
-// One reduction stage of the complex product for a wave's WTM x WTN tiles.
-template <int PREC, int WTM, int WTN>
-__device__ __forceinline__ void stage_mfma(const uint4 (&fa)[WTM][MP<PREC>::NPL],
-                                           const uint4 (&fb)[WTN][MP<PREC>::NPL],
-                                           typename MP<PREC>::acc (&accr)[WTM][WTN],
-                                           typename MP<PREC>::acc (&acci)[WTM][WTN]) {
-    static_assert(PREC != TNSLQ_BF16X3, "split BF16 runs in k_cgemm_bf16x3");
-    if constexpr (PREC == TNSLQ_FP32) {
-        uint4 nai[WTM];
+// One FP64 reduction stage of the complex product for a wave's WTM x WTN tiles.
+template <int WTM, int WTN>
+__device__ __forceinline__ void stage_mfma(const uint4 (&fa)[WTM][2], const uint4 (&fb)[WTN][2],
+                                           f64x4 (&accr)[WTM][WTN], f64x4 (&acci)[WTM][WTN]) {
+    uint4 nai[WTM];
 #pragma unroll
-        for (int x = 0; x < WTM; ++x) nai[x] = neg_f32x4(fa[x][1]);
+    for (int x = 0; x < WTM; ++x) nai[x] = neg_f64x2(fa[x][1]);
 #pragma unroll
-        for (int t = 0; t < 4; ++t)
+    for (int t = 0; t < 2; ++t)
 #pragma unroll
-            for (int a = 0; a < WTM; ++a)
+        for (int a = 0; a < WTM; ++a)
 #pragma unroll
-                for (int b = 0; b < WTN; ++b) {
-                    const float ar = f32_at(fa[a][0], t), ai = f32_at(fa[a][1], t), nai_t = f32_at(nai[a], t);
-                    const float br = f32_at(fb[b][0], t), bi = f32_at(fb[b][1], t);
-                    accr[a][b] = __builtin_amdgcn_mfma_f32_16x16x4f32(ar, br, accr[a][b], 0, 0, 0);
-                    accr[a][b] = __builtin_amdgcn_mfma_f32_16x16x4f32(nai_t, bi, accr[a][b], 0, 0, 0);
-                    acci[a][b] = __builtin_amdgcn_mfma_f32_16x16x4f32(ar, bi, acci[a][b], 0, 0, 0);
-                    acci[a][b] = __builtin_amdgcn_mfma_f32_16x16x4f32(ai, br, acci[a][b], 0, 0, 0);
-                }
-    } else {
-        uint4 nai[WTM];
-#pragma unroll
-        for (int x = 0; x < WTM; ++x) nai[x] = neg_f64x2(fa[x][1]);
-#pragma unroll
-        for (int t = 0; t < 2; ++t)
-#pragma unroll
-            for (int a = 0; a < WTM; ++a)
-#pragma unroll
-                for (int b = 0; b < WTN; ++b) {
-                    const double ar = f64_at(fa[a][0], t), ai = f64_at(fa[a][1], t), nai_t = f64_at(nai[a], t);
-                    const double br = f64_at(fb[b][0], t), bi = f64_at(fb[b][1], t);
-                    accr[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(ar, br, accr[a][b], 0, 0, 0);
-                    accr[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(nai_t, bi, accr[a][b], 0, 0, 0);
-                    acci[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(ar, bi, acci[a][b], 0, 0, 0);
-                    acci[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(ai, br, acci[a][b], 0, 0, 0);
-                }
-    }
+            for (int b = 0; b < WTN; ++b) {
+                const double ar = f64_at(fa[a][0], t), ai = f64_at(fa[a][1], t), nai_t = f64_at(nai[a], t);
+                const double br = f64_at(fb[b][0], t), bi = f64_at(fb[b][1], t);
+                accr[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(ar, br, accr[a][b], 0, 0, 0);
+                accr[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(nai_t, bi, accr[a][b], 0, 0, 0);
+                acci[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(ar, bi, acci[a][b], 0, 0, 0);
+                acci[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(ai, br, acci[a][b], 0, 0, 0);
+            }
 }
 
 // Epilogue of a wave's WTM x WTN tiles of 16 x 16 whose first output row and

@@ -248,7 +248,7 @@ struct GemmDesc {
 };
 
 // Whether an M x N product over nst bricks in S splits runs in 16-row tiles
-// against up to 64 columns (k_thin_product) instead of 128-row tiles: FP32 and
+// against up to 64 columns (k_thin_fp32, k_thin_product) instead of 128-row tiles: FP32 and
 // FP64 up to 64 columns, where a 128-column tile is at least half padding (at
 // 65 to 128 columns the large tile's reuse of A through LDS is worth the
 // padding), and FP64 over at most four bricks (32 terms), where four real
