@@ -1164,13 +1164,10 @@ void bind(Ctx &c, void *ws, hipStream_t st) {
 int form_rho(const Plan &pl, int prec, const void *psi, void *Pabe, void *Pabc, void *Cd, hipStream_t st) {
     const int64_t n = pl.dAB, dE = pl.dE;
     if (pl.mixed) {
-        TNSLQ_HIP(launch_permute_mixed(prec, pl.dtype, psi, Pabe, pl.md, 0, st));
-        TNSLQ_HIP(launch_permute_mixed(prec, pl.dtype, psi, Pabc, pl.md, 1, st));
+        TNSLQ_HIP(launch_permute_mixed(prec, pl.dtype, psi, Pabe, Pabc, pl.md, st));
     } else {
         const PermDesc abe = perm_for(pl, pl.qa, pl.nA, pl.qb, pl.nB, pl.qe, pl.nE);
-        const int rs = low_bit_row(abe, pl.nE);
-        TNSLQ_HIP(launch_permute(prec, pl.dtype, psi, Pabe, n, dE, abe, 0, rs, st));
-        TNSLQ_HIP(launch_permute(prec, pl.dtype, psi, Pabc, n, dE, abe, 1, rs, st));
+        TNSLQ_HIP(launch_permute(prec, pl.dtype, psi, Pabe, Pabc, n, dE, abe, low_bit_row(abe, pl.nE), st));
     }
     GemmDesc g{};
     g.A = Pabe;
@@ -1352,9 +1349,9 @@ int do_layout(Ctx &c, const void *psi) {
     }
     PermDesc aeb = perm_for(pl, pl.qa, pl.nA, pl.qe, pl.nE, pl.qb, pl.nB);
     PermDesc eba = perm_for(pl, pl.qe, pl.nE, pl.qb, pl.nB, pl.qa, pl.nA);
-    TNSLQ_HIP(launch_permute(pl.prec, pl.dtype, psi, c.Paeb, pl.dA, pl.dE * pl.dB, aeb, 0,
+    TNSLQ_HIP(launch_permute(pl.prec, pl.dtype, psi, c.Paeb, nullptr, pl.dA, pl.dE * pl.dB, aeb,
                              low_bit_row(aeb, pl.nE + pl.nB), c.st));
-    TNSLQ_HIP(launch_permute(pl.prec, pl.dtype, psi, c.Peba, pl.dB * pl.dE, pl.dA, eba, 1,
+    TNSLQ_HIP(launch_permute(pl.prec, pl.dtype, psi, nullptr, c.Peba, pl.dB * pl.dE, pl.dA, eba,
                              low_bit_row(eba, pl.nA), c.st));
     const int64_t epr = brick_epr(pl.prec);
     if (pl.dA % epr)

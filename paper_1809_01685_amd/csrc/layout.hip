@@ -23,9 +23,9 @@ __device__ inline double2 load_psi(const void *psi, int64_t i) {
     }
 }
 
-// Brick operand of R x Kr entries from psi: entry (r, l) = psi[in(r Kr + l)]
-// (conjugated if asked), where bit t of the regrouped index is bit map[t] of
-// in, and zeros in the padding (Kr a power of two).  A thread gathers the
+// Brick operand of R x Kr entries from psi: entry (r, l) = psi[in(r Kr + l)] in
+// out, its conjugate in outc (either may be null), where bit t of the regrouped
+// index is bit map[t] of in, and zeros in the padding (Kr a power of two).  A thread gathers the
 // terms of one 16-byte unit and stores whole units, one per plane.  Bound by
 // the gather: consecutive threads take the units of a row, then the rows, when
 // psi runs along the reduction index, and the rows of a brick in steps of
@@ -34,8 +34,9 @@ __device__ inline double2 load_psi(const void *psi, int64_t i) {
 // 2-byte stores in plane order took 3.12 ms for 28 qubits in split BF16
 // per operand (1.7 TB/s read and written), this 2.05 (2.6).
 template <int PREC, int DTYPE>
-__global__ void __launch_bounds__(256) k_permute(const void *__restrict__ psi, void *__restrict__ out, int64_t R,
-                                                 int64_t Kr, int64_t nst, PermDesc pd, int conj, int rs) {
+__global__ void __launch_bounds__(256) k_permute(const void *__restrict__ psi, void *__restrict__ out,
+                                                 void *__restrict__ outc, int64_t R, int64_t Kr, int64_t nst,
+                                                 PermDesc pd, int rs) {
     constexpr int EPR = brick_epr(PREC), EPU = brick_epu(PREC), NPL = planes_of(PREC);
     const int64_t total = brick_rows(R) * nst * 4;
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
@@ -69,12 +70,16 @@ __global__ void __launch_bounds__(256) k_permute(const void *__restrict__ psi, v
             for (int t = 0; t < pd.L; ++t) in |= ((o >> t) & 1) << pd.map[t];
 #pragma unroll
             for (int t = 0; t < EPU; ++t)
-                if (l + t < Kr) {
-                    v[t] = load_psi<DTYPE>(psi, in + dl[t]);
-                    if (conj) v[t].y = -v[t].y;
-                }
+                if (l + t < Kr) v[t] = load_psi<DTYPE>(psi, in + dl[t]);
         }
-        store_unit<PREC>(out, (b * NPL * BRICK_ROWS + rr) * EPR + (u ^ brick_swizzle(rr)) * EPU, v);
+        const int64_t at = (b * NPL * BRICK_ROWS + rr) * EPR + (u ^ brick_swizzle(rr)) * EPU;
+        if (out) store_unit<PREC>(out, at, v);
+        if (outc) {
+#pragma unroll
+            for (int t = 0; t < EPU; ++t)
+                if (r < R && l + t < Kr) v[t].y = -v[t].y;
+            store_unit<PREC>(outc, at, v);
+        }
     }
 }
 
@@ -90,12 +95,13 @@ __device__ inline int64_t mixed_offset(const MixedDesc &md, int g, int64_t v) {
 }
 
 // P[(a, b)][c] = psi at A's digits of a, B's of b and E's of c, as a brick
-// operand of d_A d_B rows and d_E reduction terms (conjugated if asked), zeros
-// in the padding; threads step over the bricks in memory order as in
-// k_permute.
+// operand of d_A d_B rows and d_E reduction terms, and its conjugate, zeros in
+// the padding; a thread per entry, in the bricks' memory order (four entries per
+// thread, and a launch for each operand, took 26 us for 864 rows of 20 terms; now
+// 6.8).
 template <int PREC, int DTYPE>
 __global__ void __launch_bounds__(256) k_permute_mixed(const void *__restrict__ psi, void *__restrict__ out,
-                                                       MixedDesc md, int64_t nst, int conj) {
+                                                       void *__restrict__ outc, MixedDesc md, int64_t nst) {
     constexpr int EPR = brick_epr(PREC), EPU = EPR / 4, NPL = planes_of(PREC);
     constexpr int64_t PER_BRICK = (int64_t)BRICK_ROWS * EPR;
     const int64_t R = md.d[0] * md.d[1], Kr = md.d[2];
@@ -107,13 +113,15 @@ __global__ void __launch_bounds__(256) k_permute_mixed(const void *__restrict__ 
         const int64_t ll = (((pos / EPU) ^ brick_swizzle(rr)) * EPU) + pos % EPU;
         const int64_t r = (b / nst) * BRICK_ROWS + rr, l = (b % nst) * EPR + ll;
         double2 v = make_double2(0.0, 0.0);
-        if (r < R && l < Kr) {
+        const bool entry = r < R && l < Kr;
+        if (entry) {
             const int64_t in = mixed_offset(md, 0, r / md.d[1]) + mixed_offset(md, 1, r % md.d[1]) +
                                mixed_offset(md, 2, l);
             v = load_psi<DTYPE>(psi, in);
-            if (conj) v.y = -v.y;
         }
-        store_planes<PREC>(out, brick_ps(PREC), (b * NPL * BRICK_ROWS + rr) * EPR + pos, v.x, v.y);
+        const int64_t at = (b * NPL * BRICK_ROWS + rr) * EPR + pos;
+        store_planes<PREC>(out, brick_ps(PREC), at, v.x, v.y);
+        store_planes<PREC>(outc, brick_ps(PREC), at, v.x, entry ? -v.y : v.y);
     }
 }
 
@@ -436,13 +444,13 @@ hipError_t launch_zero(void *p, size_t bytes, hipStream_t st) {
     return hipGetLastError();
 }
 
-hipError_t launch_permute(int prec, int dtype, const void *psi, void *out, int64_t R, int64_t Kr,
-                          const PermDesc &pd, int conj, int rs, hipStream_t st) {
+hipError_t launch_permute(int prec, int dtype, const void *psi, void *out, void *outc, int64_t R, int64_t Kr,
+                          const PermDesc &pd, int rs, hipStream_t st) {
     const int64_t nst = brick_stages(prec, Kr);
     rs = rs < 7 ? rs : 7;
     dim3 grid(grid_for(brick_rows(R) * nst * 4, 256 * 2, 65535 * 8)), block(256);
 #define TNSLQ_PERM(P, T) \
-    hipLaunchKernelGGL((k_permute<P, T>), grid, block, 0, st, psi, out, R, Kr, nst, pd, conj, rs)
+    hipLaunchKernelGGL((k_permute<P, T>), grid, block, 0, st, psi, out, outc, R, Kr, nst, pd, rs)
     if (dtype == TNSLQ_C128) {
         switch (prec) {
             case TNSLQ_FP64: TNSLQ_PERM(TNSLQ_FP64, TNSLQ_C128); break;
@@ -527,12 +535,12 @@ hipError_t launch_partials_to_bricks(int prec, const void *part, int S, int64_t 
     return hipGetLastError();
 }
 
-hipError_t launch_permute_mixed(int prec, int dtype, const void *psi, void *out, const MixedDesc &md, int conj,
+hipError_t launch_permute_mixed(int prec, int dtype, const void *psi, void *out, void *outc, const MixedDesc &md,
                                 hipStream_t st) {
     const int64_t R = md.d[0] * md.d[1];
     const int64_t nst = brick_stages(prec, md.d[2]);
-    dim3 grid(grid_for(brick_rows(R) * nst * brick_epr(prec), 256 * 4, 65535 * 8)), block(256);
-#define TNSLQ_PM(P, T) hipLaunchKernelGGL((k_permute_mixed<P, T>), grid, block, 0, st, psi, out, md, nst, conj)
+    dim3 grid(grid_for(brick_rows(R) * nst * brick_epr(prec), 256, 65535 * 8)), block(256);
+#define TNSLQ_PM(P, T) hipLaunchKernelGGL((k_permute_mixed<P, T>), grid, block, 0, st, psi, out, outc, md, nst)
     if (dtype == TNSLQ_C128) {
         switch (prec) {
             case TNSLQ_FP64: TNSLQ_PM(TNSLQ_FP64, TNSLQ_C128); break;

@@ -102,12 +102,12 @@ struct PermDesc {
     int L;
     int map[TNSLQ_MAX_QUBITS];   // output bit t <- input bit map[t]
 };
-// Regroup psi into an R x Kr brick operand (output flat index r * Kr + l),
-// writing every brick entry including the zero padding.  rs: -1 when psi's
-// low bits run along the reduction index, else the number of row bits below
-// those they run along.
-hipError_t launch_permute(int prec, int dtype, const void *psi, void *out, int64_t R, int64_t Kr,
-                          const PermDesc &pd, int conj, int rs, hipStream_t st);
+// Regroup psi into an R x Kr brick operand (output flat index r * Kr + l) in out
+// and its conjugate in outc (either may be null), writing every brick entry
+// including the zero padding.  rs: -1 when psi's low bits run along the reduction
+// index, else the number of row bits below those they run along.
+hipError_t launch_permute(int prec, int dtype, const void *psi, void *out, void *outc, int64_t R, int64_t Kr,
+                          const PermDesc &pd, int rs, hipStream_t st);
 
 // Explicit rho^{T_B} (intermediary (iii) of Sec. V) from the dense product
 // C[i][j] = rho_AB[i][j] (n x n, row-major, accumulator type: FP64 when
@@ -119,9 +119,9 @@ hipError_t launch_pt_bricks(int prec, int accfp64, const void *C, int64_t n, int
 // As a dense complex128 row-major matrix (from an FP64 product):
 hipError_t launch_pt_dense(const double2 *C, int64_t n, int64_t dB, double2 *out, hipStream_t st);
 
-// P[(a, b)][c] of d_A d_B rows and d_E reduction terms as a brick operand
-// (conjugated if asked), zeros in the padding.
-hipError_t launch_permute_mixed(int prec, int dtype, const void *psi, void *out, const MixedDesc &md, int conj,
+// P[(a, b)][c] of d_A d_B rows and d_E reduction terms as a brick operand and
+// its conjugate, zeros in the padding.
+hipError_t launch_permute_mixed(int prec, int dtype, const void *psi, void *out, void *outc, const MixedDesc &md,
                                 hipStream_t st);
 
 // ------------------------------------------------------------ Lanczos etc.
