@@ -293,6 +293,8 @@ hipError_t launch_fp64(const GemmDesc &g, hipStream_t st) {
 // turns on one set of accumulators.  Error of a block matvec against 64 bits:
 // 1.1e-7 to 2.2e-7 of the result from 10 to 24 qubits, where the FP32 unit with
 // sums restarted every 64 terms had 2.0e-7 to 3.3e-7.
+// Values that the pieces do not reach, and sums that overflow, go to the FP32
+// unit (gemm_tiles.h): 1% of the time at 26 qubits, 2% at 22, for the test.
 // Block, waves and tiles as k_cgemm_bf16x3: 128 x 128 outputs, 8 waves of
 // 64 x 32; 48 matrix instructions per wave and step for 18 fragment reads.  Two
 // LDS buffers (96 KiB), one barrier per step: the step after next is loaded, the
@@ -308,6 +310,7 @@ __global__ void __launch_bounds__(NT, 1) k_cgemm_fp32(GemmDesc g) {
     constexpr int FBRICK = 2 * TILEB;   // an FP32 brick: re, im
     constexpr int BUF = 3 * TILEB;      // an operand's three BF16 planes of a step
     __shared__ __attribute__((aligned(16))) char lds[2][2][BUF];
+    __shared__ int some_low;   // a row of the tile held no value that the pieces reach
     typedef __attribute__((ext_vector_type(2))) float f32x2;
     typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
     const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
@@ -364,9 +367,11 @@ __global__ void __launch_bounds__(NT, 1) k_cgemm_fp32(GemmDesc g) {
             y -= __uint_as_float(h[p] & 0xffff0000u);
         }
     };
+    uint64_t full[2] = {0, 0};   // lanes that held a value of A, of B that the pieces reach (gemm_tiles.h)
     auto put = [&](int q, int buf) __attribute__((always_inline)) {
 #pragma unroll
-        for (int o = 0; o < 2; ++o)
+        for (int o = 0; o < 2; ++o) {
+            uint32_t bits = 0;   // of the leading pieces
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
                 float4 x = v[o][h];
@@ -379,23 +384,24 @@ __global__ void __launch_bounds__(NT, 1) k_cgemm_fp32(GemmDesc g) {
                 uint32_t a[3], b[3];
                 split2(x.x, x.y, a);
                 split2(x.z, x.w, b);
+                bits |= a[0] | b[0];
                 char *d = lds[buf][o] + (h ? so1 : so0);
 #pragma unroll
                 for (int p = 0; p < 3; ++p) *(uint2 *)(d + p * TILEB) = make_uint2(a[p], b[p]);
             }
+            if (q != 2) full[o] |= pieces_full(bits);
+        }
     };
     const int frow = lane & 15, fk = lane >> 4;
-    int oa[TM], ob[TN];
-#pragma unroll
-    for (int x = 0; x < TM; ++x) oa[x] = loff(wm * TM * 16 + x * 16 + frow, fk);
-#pragma unroll
-    for (int x = 0; x < TN; ++x) ob[x] = loff(wn * TN * 16 + x * 16 + frow, fk);
+    // (rows 16 apart have their units in the same order)
+    const int oa = loff(wm * TM * 16 + frow, fk), ob = loff(wn * TN * 16 + frow, fk);
     f32x4 t[TM][TN], tlow[TM][TN], accr[TM][TN], acci[TM][TN];
 #pragma unroll
     for (int a = 0; a < TM; ++a)
 #pragma unroll
         for (int b = 0; b < TN; ++b) t[a][b] = tlow[a][b] = accr[a][b] = acci[a][b] = f32x4{0, 0, 0, 0};
 
+    if (tid == 0) some_low = 0;
     Cursor cur{0, 0, 0}, nxt{0, 0, 0}, ld{0, 0, 0};
     load(ld);
     advance(ld);
@@ -412,9 +418,9 @@ __global__ void __launch_bounds__(NT, 1) k_cgemm_fp32(GemmDesc g) {
 #pragma unroll
         for (int p = 0; p < 3; ++p) {
 #pragma unroll
-            for (int x = 0; x < TM; ++x) fa[x][p] = *(const uint4 *)(As + p * TILEB + oa[x]);
+            for (int x = 0; x < TM; ++x) fa[x][p] = *(const uint4 *)(As + p * TILEB + oa + x * 16 * ROWB);
 #pragma unroll
-            for (int x = 0; x < TN; ++x) fb[x][p] = *(const uint4 *)(Bs + p * TILEB + ob[x]);
+            for (int x = 0; x < TN; ++x) fb[x][p] = *(const uint4 *)(Bs + p * TILEB + ob + x * 16 * ROWB);
         }
         if (i + 1 < total) put(nxt.q, buf ^ 1);
         nxt = ld;
@@ -456,7 +462,50 @@ __global__ void __launch_bounds__(NT, 1) k_cgemm_fp32(GemmDesc g) {
         }
         __syncthreads();
     }
-    store_tiles<TNSLQ_FP32, TM, TN>(g, tl.s, tl.i0 + wm * TM * 16, tl.j0 + wn * TN * 16, lane, accr, acci);
+    // The range (gemm_tiles.h), worked out anew from the thread's number, so that no
+    // register is kept for it through the loop.  Wave w holds rows 16 w .. 16 w + 15
+    // of an operand, four lanes each.
+    int t2 = tid;
+    asm volatile("" : "+v"(t2));
+    const int l2 = t2 & 63, r2 = t2 >> 2, m2 = (t2 >> 6) / WAVES_N, n2 = (t2 >> 6) % WAVES_N;
+    const char *bA = (const char *)g.A + (size_t)(tl.i0 / BM) * blk, *bB = (const char *)g.B + (size_t)(tl.j0 / BN) * blk;
+    const bool have[2] = {tl.i0 + r2 < g.M, tl.j0 + r2 < g.N};
+    const uint64_t arows = __ballot(have[0]), brows = __ballot(have[1]);
+    if (((full[0] & arows) != arows || (full[1] & brows) != brows) && l2 == 0) some_low = 1;
+    __syncthreads();
+    bool low = some_low;
+    if (low) {
+        low = false;
+        uint64_t *waves = (uint64_t *)lds;   // [operand][wave]
+        if (l2 == 0) {
+            waves[t2 >> 6] = full[0] & arows;
+            waves[8 + (t2 >> 6)] = full[1] & brows;
+        }
+        __syncthreads();
+#pragma unroll 1
+        for (int o = 0; o < 2; ++o) {
+            // the rows of this thread's group: all of A's, those of one vector (cnb) of B's
+            const int group = o == 0 || g.cnb_log2 > 6 ? BM : 1 << g.cnb_log2;
+            uint64_t m = 0;
+            if (group >= 16)
+                for (int w = (r2 & -group) / 16; w < ((r2 & -group) + group) / 16; ++w) m |= waves[8 * o + w];
+            else
+                m = waves[8 * o + r2 / 16] >> (4 * (r2 & 15 & -group)) & (((uint64_t)1 << (4 * group)) - 1);
+            if (m == 0 && (o == 0 ? have[0] : have[1]))
+                low = low || units_nonzero((o == 0 ? bA : bB) + 16 * t2, tl.sbeg, tl.send);
+        }
+        low = __syncthreads_or(low);
+    }
+    const int64_t wi0 = tl.i0 + m2 * TM * 16, wj0 = tl.j0 + n2 * TN * 16;
+    if (low || nonfinite_tiles<TNSLQ_FP32, TM, TN>(g, wi0, wj0, l2, accr, acci)) {
+        int pa[TM], pb[TN];
+#pragma unroll
+        for (int x = 0; x < TM; ++x) pa[x] = loff(m2 * TM * 16 + x * 16 + (l2 & 15), l2 >> 4);
+#pragma unroll
+        for (int x = 0; x < TN; ++x) pb[x] = loff(n2 * TN * 16 + x * 16 + (l2 & 15), l2 >> 4);
+        plain_tiles<TNSLQ_FP32, TM, TN>(bA, pa, bB, pb, tl.sbeg, tl.send, accr, acci);
+    }
+    store_tiles<TNSLQ_FP32, TM, TN>(g, tl.s, wi0, wj0, l2, accr, acci);
 }
 
 hipError_t launch_fp32(const GemmDesc &g, hipStream_t st) {

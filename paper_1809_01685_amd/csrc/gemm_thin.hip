@@ -57,7 +57,7 @@ __global__ void __launch_bounds__(64 * THIN_WAVES) k_thin_product(GemmDesc g) {
             for (int h = 0; h < 2; ++h) {
                 if (st + h >= send) break;
                 load(st + h + 1 < send ? st + h + 1 : send - 1, fa[h ^ 1], fb[h ^ 1]);
-                stage_mfma<1, NTC>(fa[h], fb[h], accr, acci);
+                stage_mfma<PREC, 1, NTC>(fa[h], fb[h], accr, acci);
             }
         }
     }
@@ -74,11 +74,12 @@ __global__ void __launch_bounds__(64 * THIN_WAVES) k_thin_product(GemmDesc g) {
 // leading pieces and the small ones have accumulators of their own; both restart
 // every 128 terms and are added in FP64: a block matvec is off by 0.8e-7 to
 // 1.3e-7 of its result, where the FP32 unit with sums restarted every 64 terms
-// had 2.0e-7 to 2.9e-7.
+// had 2.0e-7 to 2.9e-7.  Values that the pieces do not reach, and results that are
+// not finite, go to that unit (gemm_tiles.h).
 constexpr int THIN_FLUSH = 4;   // steps of 32 terms per restart
 
 template <int NTC>
-__global__ void __launch_bounds__(64 * THIN_WAVES) k_thin_fp32(GemmDesc g) {
+__global__ void __launch_bounds__(64 * THIN_WAVES, 5 - NTC) k_thin_fp32(GemmDesc g) {
     stamp(g.start);
     constexpr int BRICKB = 2 * TILEB;
     const int lane = threadIdx.x & 63, frow = lane & 15, fk = lane >> 4;
@@ -90,9 +91,9 @@ __global__ void __launch_bounds__(64 * THIN_WAVES) k_thin_fp32(GemmDesc g) {
     const int64_t sbeg = g.nst * s / g.S, send = g.nst * (s + 1) / g.S;
     const char *ga = (const char *)g.A + (size_t)rb * brick_block_bytes(TNSLQ_FP32, g.nst) + loff(16 * r8 + frow, fk);
     const char *gb = (const char *)g.B;
-    int ob[NTC];
-#pragma unroll
-    for (int c = 0; c < NTC; ++c) ob[c] = loff(16 * c + frow, fk);
+    // (rows 16 apart have their units in the same order)
+    const int ob = loff(frow, fk);
+    constexpr int OC = 16 * ROWB;   // from a column tile's rows to the next one's
     // a step's fragments: [plane][brick]; a last odd brick's second half is zeros
     auto load = [&](int64_t st, float4 (&fa)[2][2], float4 (&fb)[NTC][2][2]) __attribute__((always_inline)) {
         const int64_t s1 = st + 1 < send ? st + 1 : st;
@@ -102,8 +103,8 @@ __global__ void __launch_bounds__(64 * THIN_WAVES) k_thin_fp32(GemmDesc g) {
             fa[p][1] = *(const float4 *)(ga + s1 * BRICKB + p * TILEB);
 #pragma unroll
             for (int c = 0; c < NTC; ++c) {
-                fb[c][p][0] = *(const float4 *)(gb + st * BRICKB + p * TILEB + ob[c]);
-                fb[c][p][1] = *(const float4 *)(gb + s1 * BRICKB + p * TILEB + ob[c]);
+                fb[c][p][0] = *(const float4 *)(gb + st * BRICKB + p * TILEB + ob + c * OC);
+                fb[c][p][1] = *(const float4 *)(gb + s1 * BRICKB + p * TILEB + ob + c * OC);
             }
         }
     };
@@ -146,6 +147,9 @@ __global__ void __launch_bounds__(64 * THIN_WAVES) k_thin_fp32(GemmDesc g) {
             }
     };
     float4 fa[2][2], fb[NTC][2][2];
+    uint32_t bitsA = 0, bitsB[NTC];   // of the leading pieces (gemm_tiles.h)
+#pragma unroll
+    for (int c = 0; c < NTC; ++c) bitsB[c] = 0;
     if (sbeg < send) load(sbeg, fa, fb);
     int cnt = 0;
     for (int64_t st = sbeg; st < send; st += 2) {
@@ -157,8 +161,12 @@ __global__ void __launch_bounds__(64 * THIN_WAVES) k_thin_fp32(GemmDesc g) {
 #pragma unroll
         for (int p = 0; p < 2; ++p) {
             split(fa[p], ha[p]);
+            bitsA |= or_bits(ha[p][0]);
 #pragma unroll
-            for (int c = 0; c < NTC; ++c) split(fb[c][p], hb[c][p]);
+            for (int c = 0; c < NTC; ++c) {
+                split(fb[c][p], hb[c][p]);
+                bitsB[c] |= or_bits(hb[c][p][0]);
+            }
         }
 #pragma unroll
         for (int p = 0; p < 3; ++p) na[p] = neg_bf16x8(ha[1][p]);
@@ -195,7 +203,43 @@ __global__ void __launch_bounds__(64 * THIN_WAVES) k_thin_fp32(GemmDesc g) {
             accr[0][c][r] = (float)out[0][c][r];
             acci[0][c][r] = (float)out[1][c][r];
         }
-    store_tiles<TNSLQ_FP32, 1, NTC>(g, s, i0, 0, lane, accr, acci);
+    // The range, worked out anew from the thread's number, so that no register is
+    // kept for it through the loop.  Bit j of `rows`: row j of B is full; a vector is
+    // cnb rows, and B holds whole vectors.
+    int l2 = threadIdx.x & 63;
+    asm volatile("" : "+v"(l2));
+    const int r2 = l2 & 15, o2 = loff(r2, l2 >> 4);
+    const bool arow = i0 + r2 < g.M;
+    const char *a2 = (const char *)g.A + (size_t)rb * brick_block_bytes(TNSLQ_FP32, g.nst) + loff(16 * r8 + r2, l2 >> 4);
+    uint64_t rows = 0;
+#pragma unroll
+    for (int c = 0; c < NTC; ++c) {
+        uint64_t m = pieces_full(bitsB[c]);
+        m |= m >> 32;
+        rows |= ((m | m >> 16) & 0xffffu) << (16 * c);
+    }
+    bool low = pieces_full(arow ? bitsA : 0) == 0 && arow && units_nonzero(a2, sbeg, send);
+    const uint64_t all = g.N < 64 ? ((uint64_t)1 << g.N) - 1 : ~(uint64_t)0;
+    if ((rows & all) != all) {
+        const int cnb = 1 << (g.cnb_log2 < 6 ? g.cnb_log2 : 6);
+        const uint64_t vec = cnb < 64 ? ((uint64_t)1 << cnb) - 1 : ~(uint64_t)0;
+        for (int v = 0; v < g.N; v += cnb) {
+            if (rows & vec << v) continue;
+#pragma unroll
+            for (int c = 0; c < NTC; ++c) {
+                const int j = 16 * c + r2;
+                if (j < g.N && vec << v >> j & 1) low = low || units_nonzero(gb + o2 + c * OC, sbeg, send);
+            }
+        }
+    }
+    if (__ballot(low) || nonfinite_tiles<TNSLQ_FP32, 1, NTC>(g, i0, 0, l2, accr, acci)) {
+        const int pa[1] = {0};
+        int pb[NTC];
+#pragma unroll
+        for (int c = 0; c < NTC; ++c) pb[c] = o2 + c * OC;
+        plain_tiles<TNSLQ_FP32, 1, NTC>(a2, pa, gb, pb, sbeg, send, accr, acci);
+    }
+    store_tiles<TNSLQ_FP32, 1, NTC>(g, s, i0, 0, l2, accr, acci);
 }
 
 }  // namespace

@@ -86,7 +86,7 @@ __global__ void __launch_bounds__(64 * SM_PROBES) k_small_steps(SmallSteps g) {
                     uint4 fb[1][2];
 #pragma unroll
                     for (int p = 0; p < 2; ++p) fb[0][p] = *(const uint4 *)&xs[p][frow][8 * st + 2 * fk];
-                    stage_mfma<1, 1>(fa[0], fb, accr, acci);
+                    stage_mfma<TNSLQ_FP64, 1, 1>(fa[0], fb, accr, acci);
                     fa[0][0][0] = fa[1][0][0];
                     fa[0][0][1] = fa[1][0][1];
                 }
