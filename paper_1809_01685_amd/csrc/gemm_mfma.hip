@@ -80,6 +80,7 @@ __device__ inline TileAt tile_of(const GemmDesc &g, uint32_t b, uint32_t nb) {
 
 typedef __attribute__((address_space(3))) void lds_void_t;
 typedef __attribute__((address_space(1))) const void gbl_void_t;
+typedef __attribute__((address_space(1))) const char gbl_char_t;
 
 template <int U, int END, typename F>
 __device__ __forceinline__ void unroll_from(F &f) {
@@ -95,20 +96,26 @@ __device__ __forceinline__ void unroll_from(F &f) {
 //   Re C = T1 - T2,      Im C = T3 - T1 - T2,
 // a quarter fewer v_mfma_f64_16x16x4f64 than four; the sums Re + Im are formed
 // from the fragments in registers (8 additions per 24 matrix instructions).
-// T3's terms are larger, so its sum is restarted every four steps (32 terms)
-// and kept in a second accumulator: the error against 80-bit sums is 5.1e-16 of
-// the result where the four-product form's was 5.5e-16 (14 to 18 qubits).
+// T1 and T3 restart every two steps (16 terms), together, and are added into
+// accumulators of their own.  Together, so that a real state and real vectors
+// (T2 = 0, T3's terms T1's) give imaginary parts of exactly zero, as four products
+// do; every 16 terms, so that the sums round less than a run of 64 terms in four
+// products whatever is real (two operands real, state real, vectors real, none):
+// 2.2, 3.2, 3.7, 4.1e-16 of the result against 80-bit sums where four products had
+// 3.7, 3.8, 4.6, 5.4e-16 (restarts every 32 terms 2.8, 4.0, 4.3, 4.6; T3's alone 5.3,
+// 4.7, 4.9, 4.9).  Their additions, on the matrix instructions' own FP64 units, are 3%
+// of the time; a non-finite tile goes to four products (gemm_tiles.h).
 // FP64 is bound by the matrix cores alone (a fragment read feeds six matrix
 // instructions of 64 cycles), so the tile is chosen for the number of blocks:
-// 128 x 64 outputs, 8 waves of 32 x 32 (2 x 2 tiles, 96 accumulator registers;
-// 64 x 32 would take 192).  A step is one brick of A and half a brick of B
+// 128 x 64 outputs, 8 waves of 32 x 32 (2 x 2 tiles, 160 accumulator registers;
+// 64 x 32 would take 320).  A step is one brick of A and half a brick of B
 // (24 KiB), copied straight into a ring of four LDS buffers, four steps ahead;
 // fragments of the next step are read between the current step's matrix
 // instructions; one barrier per step.  Buffers and register sets are chosen at
-// compile time (the loop body is four steps; a run of another length starts
-// inside it), as in k_cgemm_bf16x3.  A 22-qubit block matvec of 5 vectors took
-// 1573 us with 128 x 128 tiles of four products and 2048 splits' worth of
-// partial sums, 863 with this; 68 TFLOP/s (of 78.6 issued in four products).
+// compile time (the loop body is four steps; what is left of a run, up to three,
+// follows it without copies or barriers).  A 22-qubit block matvec of 5 vectors
+// took 1575 us with 128 x 128 tiles of four products and 2048 splits' worth of
+// partial sums, 690 with this.
 constexpr int D_BN = 64, D_WAVES_N = 2, D_TM = 2, D_TN = 2, D_BODY = 4;
 
 __global__ void __launch_bounds__(NT, 1) k_cgemm_fp64(GemmDesc g) {
@@ -138,21 +145,18 @@ __global__ void __launch_bounds__(NT, 1) k_cgemm_fp64(GemmDesc g) {
     // both planes of A, and quarter w % 4 of plane w / 4 of B
     auto dma = [&](int64_t st, auto bb) __attribute__((always_inline)) {
         const int64_t q = st <= plast ? st : plast;
-        const char *pa = gA + q * ABRICK, *pb = gB + q * ABRICK;
+        gbl_char_t *pa = (gbl_char_t *)(gA + q * ABRICK + 1024 * w), *pa1 = pa + TILEB;
+        gbl_char_t *pb = (gbl_char_t *)(gB + q * ABRICK + (w >> 2) * TILEB + (w & 3) * 1024);
         char *As = bufA(bb) + 1024 * w, *Bs = bufB(bb) + 1024 * w;
-#pragma unroll
-        for (int p = 0; p < NPL; ++p)
-            __builtin_amdgcn_global_load_lds((gbl_void_t *)(pa + p * TILEB + 1024 * w + l16),
-                                             (lds_void_t *)(As + p * TILEB), 16, 0, 0);
-        __builtin_amdgcn_global_load_lds((gbl_void_t *)(pb + (w >> 2) * TILEB + (w & 3) * 1024 + l16),
-                                         (lds_void_t *)Bs, 16, 0, 0);
+        // (the bases stay in scalar registers)
+        asm volatile("" : "+s"(pa), "+s"(pa1), "+s"(pb));
+        __builtin_amdgcn_global_load_lds((gbl_void_t *)(pa + l16), (lds_void_t *)As, 16, 0, 0);
+        __builtin_amdgcn_global_load_lds((gbl_void_t *)(pa1 + l16), (lds_void_t *)(As + TILEB), 16, 0, 0);
+        __builtin_amdgcn_global_load_lds((gbl_void_t *)(pb + l16), (lds_void_t *)Bs, 16, 0, 0);
     };
     const int frow = lane & 15, fk = lane >> 4;
-    int oa[D_TM], ob[D_TN];
-#pragma unroll
-    for (int x = 0; x < D_TM; ++x) oa[x] = loff(wm * D_TM * 16 + x * 16 + frow, fk);
-#pragma unroll
-    for (int x = 0; x < D_TN; ++x) ob[x] = loff(wn * D_TN * 16 + x * 16 + frow, fk);
+    // (rows 16 apart have their units in the same order)
+    const int oa = loff(wm * D_TM * 16 + frow, fk), ob = loff(wn * D_TN * 16 + frow, fk);
     uint4 fa[2][D_TM][NPL], fb[2][D_TN][NPL];
     auto rd = [&](auto ss, auto bb) __attribute__((always_inline)) {
         constexpr int S = decltype(ss)::value;
@@ -160,39 +164,31 @@ __global__ void __launch_bounds__(NT, 1) k_cgemm_fp64(GemmDesc g) {
 #pragma unroll
         for (int x = 0; x < D_TM; ++x)
 #pragma unroll
-            for (int p = 0; p < NPL; ++p) fa[S][x][p] = *(const uint4 *)(As + p * TILEB + oa[x]);
+            for (int p = 0; p < NPL; ++p) fa[S][x][p] = *(const uint4 *)(As + p * TILEB + oa + x * 16 * ROWB);
 #pragma unroll
         for (int x = 0; x < D_TN; ++x)
 #pragma unroll
-            for (int p = 0; p < NPL; ++p) fb[S][x][p] = *(const uint4 *)(Bs + p * BHALF + ob[x]);
+            for (int p = 0; p < NPL; ++p) fb[S][x][p] = *(const uint4 *)(Bs + p * BHALF + ob + x * 16 * ROWB);
     };
-    f64x4 t[3][D_TM][D_TN];
-#pragma unroll
-    for (int q = 0; q < 3; ++q)
-#pragma unroll
-        for (int a = 0; a < D_TM; ++a)
-#pragma unroll
-            for (int b = 0; b < D_TN; ++b) t[q][a][b] = f64x4{0, 0, 0, 0};
-    // T3 of the finished bodies
-    f64x4 t3[D_TM][D_TN];
+    // sums of the current chunk (T2's of all), and T1's and T3's of the chunks before
+    f64x4 t[3][D_TM][D_TN], t1[D_TM][D_TN], t3[D_TM][D_TN];
 #pragma unroll
     for (int a = 0; a < D_TM; ++a)
 #pragma unroll
-        for (int b = 0; b < D_TN; ++b) t3[a][b] = f64x4{0, 0, 0, 0};
-    auto flush3 = [&]() __attribute__((always_inline)) {
+        for (int b = 0; b < D_TN; ++b) t[0][a][b] = t[1][a][b] = t[2][a][b] = t1[a][b] = t3[a][b] = f64x4{0, 0, 0, 0};
+    auto restart = [&]() __attribute__((always_inline)) {
 #pragma unroll
         for (int a = 0; a < D_TM; ++a)
 #pragma unroll
             for (int b = 0; b < D_TN; ++b) {
+                t1[a][b] += t[0][a][b];
                 t3[a][b] += t[2][a][b];
-                t[2][a][b] = f64x4{0, 0, 0, 0};
+                t[0][a][b] = t[2][a][b] = f64x4{0, 0, 0, 0};
             }
     };
-    int64_t base = 0;
-    auto step = [&](auto uu) __attribute__((always_inline)) {
-        constexpr int U = decltype(uu)::value, C = U % 2;
-        rd(std::integral_constant<int, C ^ 1>{}, std::integral_constant<int, (U + 1) % 4>{});
-        dma(base + U + 4, std::integral_constant<int, U>{});
+    // the products of fragment set C
+    auto products = [&](auto cc) __attribute__((always_inline)) {
+        constexpr int C = decltype(cc)::value;
 #pragma unroll
         for (int h = 0; h < 2; ++h)
 #pragma unroll
@@ -207,6 +203,14 @@ __global__ void __launch_bounds__(NT, 1) k_cgemm_fp64(GemmDesc g) {
                             q == 0 ? ar : (q == 1 ? ai : ar + ai), q == 0 ? br : (q == 1 ? bi : br + bi), t[q][a][b], 0, 0,
                             0);
                     }
+    };
+    int64_t base = p0;
+    auto step = [&](auto uu) __attribute__((always_inline)) {
+        constexpr int U = decltype(uu)::value, C = U % 2;
+        constexpr std::integral_constant<int, C> cc{};
+        rd(std::integral_constant<int, C ^ 1>{}, std::integral_constant<int, (U + 1) % 4>{});
+        dma(base + U + 4, std::integral_constant<int, U>{});
+        products(cc);
         // 2 MFMA, 8 x (LDS read, MFMA), 3 x (copy, MFMA), 11 MFMA
         __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
 #pragma unroll
@@ -224,47 +228,63 @@ __global__ void __launch_bounds__(NT, 1) k_cgemm_fp64(GemmDesc g) {
         __builtin_amdgcn_s_waitcnt(0x0076);   // vmcnt(6): step st + 2 landed; lgkmcnt(0)
         __builtin_amdgcn_s_barrier();
         __builtin_amdgcn_sched_barrier(0);
+        if constexpr (U % 2 == 1) {
+            restart();
+            __builtin_amdgcn_sched_barrier(0);
+        }
     };
-    // the run starts at body position U0, so that it ends with a whole body
-    auto start = [&](auto u0) __attribute__((always_inline)) {
-        constexpr int V = decltype(u0)::value;
-        dma(p0, std::integral_constant<int, V % 4>{});
-        dma(p0 + 1, std::integral_constant<int, (V + 1) % 4>{});
-        dma(p0 + 2, std::integral_constant<int, (V + 2) % 4>{});
-        dma(p0 + 3, std::integral_constant<int, (V + 3) % 4>{});
-        __builtin_amdgcn_s_waitcnt(0x0f79);   // vmcnt(9): step p0 landed
-        __builtin_amdgcn_s_barrier();
-        __builtin_amdgcn_sched_barrier(0);
-        rd(std::integral_constant<int, V % 2>{}, std::integral_constant<int, V % 4>{});
-        __builtin_amdgcn_s_waitcnt(0x0076);   // vmcnt(6): step p0 + 1 landed; lgkmcnt(0)
-        __builtin_amdgcn_s_barrier();
-        __builtin_amdgcn_sched_barrier(0);
-        base = p0 - V;
-        unroll_from<V, D_BODY>(step);
-        flush3();
-        base += D_BODY;
-    };
-    switch ((int)((D_BODY - (pend - p0) % D_BODY) % D_BODY)) {
-        case 1: start(std::integral_constant<int, 1>{}); break;
-        case 2: start(std::integral_constant<int, 2>{}); break;
-        case 3: start(std::integral_constant<int, 3>{}); break;
-        default: start(std::integral_constant<int, 0>{}); break;
+    dma(p0, std::integral_constant<int, 0>{});
+    dma(p0 + 1, std::integral_constant<int, 1>{});
+    dma(p0 + 2, std::integral_constant<int, 2>{});
+    dma(p0 + 3, std::integral_constant<int, 3>{});
+    __builtin_amdgcn_s_waitcnt(0x0f79);   // vmcnt(9): step p0 landed
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+    rd(std::integral_constant<int, 0>{}, std::integral_constant<int, 0>{});
+    __builtin_amdgcn_s_waitcnt(0x0076);   // vmcnt(6): step p0 + 1 landed; lgkmcnt(0)
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+    for (; base + D_BODY <= pend; base += D_BODY) unroll_from<0, D_BODY>(step);
+    __builtin_amdgcn_s_waitcnt(0x0f70);   // the last steps and the copies past the end, before LDS is given up
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+    if (base < pend) {
+        products(std::integral_constant<int, 0>{});
+        if (base + 1 < pend) {
+            rd(std::integral_constant<int, 1>{}, std::integral_constant<int, 1>{});
+            products(std::integral_constant<int, 1>{});
+            restart();
+            if (base + 2 < pend) {
+                rd(std::integral_constant<int, 0>{}, std::integral_constant<int, 2>{});
+                products(std::integral_constant<int, 0>{});
+            }
+        }
     }
-    for (; base < pend; base += D_BODY) {
-        unroll_from<0, D_BODY>(step);
-        flush3();
-    }
-    __builtin_amdgcn_s_waitcnt(0x0f70);   // the copies past the end, before LDS is given up
+    restart();
 
     f64x4 accr[D_TM][D_TN], acci[D_TM][D_TN];
 #pragma unroll
     for (int a = 0; a < D_TM; ++a)
 #pragma unroll
         for (int b = 0; b < D_TN; ++b) {
-            accr[a][b] = t[0][a][b] - t[1][a][b];
-            acci[a][b] = t3[a][b] - t[0][a][b] - t[1][a][b];
+            accr[a][b] = t1[a][b] - t[1][a][b];
+            acci[a][b] = t3[a][b] - t1[a][b] - t[1][a][b];
         }
-    store_tiles<TNSLQ_FP64, D_TM, D_TN>(g, tl.s, tl.i0 + wm * D_TM * 16, tl.j0 + wn * D_TN * 16, lane, accr, acci);
+    // worked out anew from what the loop keeps: no registers for it through the loop
+    int l2 = threadIdx.x & 63;
+    asm volatile("" : "+v"(l2));
+    const int m2 = w / D_WAVES_N * D_TM * 16, n2 = w % D_WAVES_N * D_TN * 16;
+    if (nonfinite_tiles<TNSLQ_FP64, D_TM, D_TN>(g, tl.i0 + m2, tl.j0 + n2, (int)l2, accr, acci)) {
+        // T3, or a sum Re + Im, may be infinite where the result is not (gemm_tiles.h)
+        int pa[D_TM], pb[D_TN];
+#pragma unroll
+        for (int x = 0; x < D_TM; ++x) pa[x] = loff(m2 + x * 16 + (l2 & 15), l2 >> 4);
+#pragma unroll
+        for (int x = 0; x < D_TN; ++x) pb[x] = loff(n2 + x * 16 + (l2 & 15), l2 >> 4);
+        plain_tiles<TNSLQ_FP64, D_TM, D_TN>(gA, pa, gB, pb, tl.sbeg, tl.send, accr, acci);
+    }
+    asm volatile("" : "+v"(l2));   // nor for the stores' addresses through this one
+    store_tiles<TNSLQ_FP64, D_TM, D_TN>(g, tl.s, tl.i0 + m2, tl.j0 + n2, (int)l2, accr, acci);
 }
 
 hipError_t launch_fp64(const GemmDesc &g, hipStream_t st) {
