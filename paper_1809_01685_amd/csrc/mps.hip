@@ -187,14 +187,16 @@ template <> struct ZT<float> {
 // G3 (the matvec's products over 64 terms or more, bound by the matrix cores):
 // three real products per complex one, T1 = sum Ar Br, T2 = sum Ai Bi,
 // T3 = sum (Ar + Ai)(Br + Bi), Cr = T1 - T2, Ci = T3 - T1 - T2, a quarter fewer
-// matrix instructions; T3, whose terms are larger, restarts every 16 terms into
-// a second accumulator, so that its rounding stays below the four-product
-// form's.  The slices are double buffered, one barrier per step, since the
-// accumulators leave two blocks per CU, and a tile inside the matrices loads
-// without bounds tests (8% of the time).  256 x 4096 outputs over 4096 terms, 8
+// matrix instructions.  T1 and T3 restart together every 16 terms into
+// accumulators of their own: real matrices keep imaginary parts of exactly zero
+// (T2 = 0, T3's terms T1's), and the sums round less than the four products',
+// whatever is real (with T3's restarts alone up to 1.4 times as much).  The slices
+// are double buffered, one barrier per step, since the accumulators leave two
+// blocks per CU (FP32: three, 8% faster than two), and a tile inside the matrices
+// loads without bounds tests (8% of the time).  256 x 4096 outputs over 4096 terms, 8
 // of them: 4.18 to 3.32 ms (66 to 83 TFLOP/s, 79% of the matrix cores' rate).
 template <int OPA, int OPB, typename T, bool XC = false, bool G3 = false>
-__global__ void __launch_bounds__(256) k_zgemm(const typename ZT<T>::C2 *__restrict__ A,
+__global__ void __launch_bounds__(256, G3 && sizeof(T) == 4 ? 3 : 1) k_zgemm(const typename ZT<T>::C2 *__restrict__ A,
                                                const typename ZT<T>::C2 *__restrict__ B,
                                                typename ZT<T>::C2 *__restrict__ C, int M, int N, int K, int64_t lda,
                                                int64_t ldb, int64_t ldc, int64_t sa, int64_t sb, int64_t sc,
@@ -223,7 +225,7 @@ __global__ void __launch_bounds__(256) k_zgemm(const typename ZT<T>::C2 *__restr
             accr[i][j] = V{0, 0, 0, 0};
             acci[i][j] = V{0, 0, 0, 0};
         }
-    // G3: accr holds T1, acci T2, t3 the finished part of T3
+    // G3: accr holds the finished part of T1, acci T2, t3 the finished part of T3
     V t3[2][2];
 #pragma unroll
     for (int i = 0; i < 2; ++i)
@@ -236,29 +238,27 @@ __global__ void __launch_bounds__(256) k_zgemm(const typename ZT<T>::C2 *__restr
     // a tile inside the matrices with whole steps: no bounds tests, and the
     // entries' addresses advance by a constant
     const bool inside = G3 && r0 + TM <= M && c0 + TN <= N && (kend - kbeg) % TK == 0;
-    const C2 *pa[4], *pb[4];
+    // (a thread's four entries are 16 rows or four terms apart)
+    const C2 *pa = A, *pb = B;
+    const int64_t qa = (OPA == 0 ? 16 : 4) * lda, qb = (OPB == 0 ? 4 : 16) * ldb;
     if (G3) {
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int e = t + 256 * q;
-            const int64_t rr = r0 + (OPA == 0 ? e / TK : e % TM), ka = kbeg + (OPA == 0 ? e % TK : e / TM);
-            const int64_t cc = c0 + (OPB == 0 ? e % TN : e / TK), kb = kbeg + (OPB == 0 ? e / TN : e % TK);
-            pa[q] = A + (OPA == 0 ? rr * lda + ka : ka * lda + rr);
-            pb[q] = B + (OPB == 0 ? kb * ldb + cc : cc * ldb + kb);
-        }
+        const int64_t rr = r0 + (OPA == 0 ? t / TK : t % TM), ka = kbeg + (OPA == 0 ? t % TK : t / TM);
+        const int64_t cc = c0 + (OPB == 0 ? t % TN : t / TK), kb = kbeg + (OPB == 0 ? t / TN : t % TK);
+        pa += OPA == 0 ? rr * lda + ka : ka * lda + rr;
+        pb += OPB == 0 ? kb * ldb + cc : cc * ldb + kb;
     }
     const int64_t da = OPA == 0 ? TK : TK * lda, db = OPB == 0 ? TK * ldb : TK;
     auto load = [&](int k0) {
         if (inside) {
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                ra[q] = *pa[q];
-                rb[q] = *pb[q];
+                ra[q] = pa[q * qa];
+                rb[q] = pb[q * qb];
                 if (OPA == 2) ra[q].y = -ra[q].y;
                 if (OPB == 2) rb[q].y = -rb[q].y;
-                pa[q] += da;
-                pb[q] += db;
             }
+            pa += da;
+            pb += db;
             return;
         }
         // 1024 entries of each slice, four per thread
@@ -312,11 +312,11 @@ __global__ void __launch_bounds__(256) k_zgemm(const typename ZT<T>::C2 *__restr
         __syncthreads();
         int buf = 0;
         for (int k0 = kbeg; k0 < kend; k0 += TK, buf ^= 1) {
-            V ts[2][2];
+            V us[2][2], ts[2][2];   // T1, T3 of the slice
 #pragma unroll
             for (int i = 0; i < 2; ++i)
 #pragma unroll
-                for (int j = 0; j < 2; ++j) ts[i][j] = V{0, 0, 0, 0};
+                for (int j = 0; j < 2; ++j) us[i][j] = ts[i][j] = V{0, 0, 0, 0};
 #pragma unroll
             for (int k4 = 0; k4 < TK / 4; ++k4) {
                 C2 av[2], bv[2];
@@ -327,7 +327,7 @@ __global__ void __launch_bounds__(256) k_zgemm(const typename ZT<T>::C2 *__restr
                     for (int i = 0; i < 2; ++i)
 #pragma unroll
                         for (int j = 0; j < 2; ++j) {
-                            if (q == 0) accr[i][j] = ZT<T>::mfma(av[i].x, bv[j].x, accr[i][j]);
+                            if (q == 0) us[i][j] = ZT<T>::mfma(av[i].x, bv[j].x, us[i][j]);
                             if (q == 1) acci[i][j] = ZT<T>::mfma(av[i].y, bv[j].y, acci[i][j]);
                             if (q == 2) ts[i][j] = ZT<T>::mfma(av[i].x + av[i].y, bv[j].x + bv[j].y, ts[i][j]);
                         }
@@ -339,7 +339,10 @@ __global__ void __launch_bounds__(256) k_zgemm(const typename ZT<T>::C2 *__restr
 #pragma unroll
             for (int i = 0; i < 2; ++i)
 #pragma unroll
-                for (int j = 0; j < 2; ++j) t3[i][j] += ts[i][j];
+                for (int j = 0; j < 2; ++j) {
+                    accr[i][j] += us[i][j];
+                    t3[i][j] += ts[i][j];
+                }
             __syncthreads();
         }
 #pragma unroll
@@ -372,13 +375,18 @@ __global__ void __launch_bounds__(256) k_zgemm(const typename ZT<T>::C2 *__restr
             __syncthreads();
         }
     }
+    // (FP32, where registers bound the blocks: the stores' places from the thread's
+    // number anew, none kept for them through the loop)
+    int te = t;
+    if constexpr (sizeof(T) == 4) asm volatile("" : "+v"(te));
+    const int re = r0 + (te >> 7) * 32, ce = c0 + (te >> 6 & 1) * 32 + (te & 15), ke = te >> 4 & 3;
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
         for (int j = 0; j < 2; ++j)
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                const int r = r0 + wm * 32 + i * 16 + ZT<T>::row(q, fk), c = c0 + wn * 32 + j * 16 + fr;
+                const int r = re + i * 16 + ZT<T>::row(q, ke), c = ce + j * 16;
                 if (r < M && c < N) {
                     int64_t at;
                     if constexpr (XC) {
