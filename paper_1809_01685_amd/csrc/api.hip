@@ -206,12 +206,14 @@ NetBufs net_bufs(const Plan &pl) {
 }
 
 // Where the kernels of a run stamp their starts (operands.h): the run itself;
-// per step, for each probe chunk the first contraction, the second and the
+// the end of its layout where the host looks at the state's norm before the
+// first step (spectral sums); per step, for each probe chunk the first contraction, the second and the
 // merge of Y, then the rest of the Lanczos step, and its end where something
 // other than the next step's first contraction follows.
 struct Stamps {
     int nchunk;
-    size_t count(int m) const { return 1 + (size_t)m * (2 + 3 * nchunk) + 1; }
+    size_t count(int m) const { return layout_end(m) + 1; }
+    size_t layout_end(int m) const { return 1 + (size_t)m * (2 + 3 * nchunk); }
     size_t step(int j) const { return 1 + (size_t)(j - 1) * (2 + 3 * nchunk); }
     size_t c1(int j, int ch) const { return step(j) + 3 * ch; }
     size_t c2(int j, int ch) const { return step(j) + 3 * ch + 1; }
@@ -2128,6 +2130,7 @@ int spectral_run(const SPlan &sp, const void *psi, const tnslq_options *opt, uin
     const PermDesc p2 = perm_two(sp.L, sp.rest, sp.n_rest, sp.side, sp.n_side);
     TNSLQ_HIP(launch_regroup(sp.dtype, psi, 2, {{P1, sp.d, sp.dR, p1}, {P2, sp.dR, sp.d, p2}}, chk, st));
     TNSLQ_HIP(launch_probe_init(TNSLQ_FP64, z, opt->seed, offset, 0, Q, nullptr, 0, alpha, beta, st));
+    TNSLQ_HIP(launch_stamp(stamps + at.layout_end(sp.m), st));
     int rc0;
     if ((rc0 = check_state(sp.dtype, chk, st))) return rc0;
     auto slot_of = [&](int jj) { return sp.reorth ? jj : jj % 3; };
@@ -2172,7 +2175,7 @@ int spectral_run(const SPlan &sp, const void *psi, const tnslq_options *opt, uin
     res->complement = sp.complement;
     res->n_qubits_side = sp.n_side;
     const double ms = tick_ms();
-    res->t_layout_ms = ms * elapsed(t.data(), 0, at.c1(1, 0));
+    res->t_layout_ms = ms * elapsed(t.data(), 0, at.layout_end(sp.m));
     for (int j = 1; j <= sp.m; ++j) {
         res->t_matvec_ms += ms * elapsed(t.data(), at.c1(j, 0), at.lanczos(j));
         res->t_lanczos_ms += ms * elapsed(t.data(), at.lanczos(j), j < sp.m ? at.c1(j + 1, 0) : at.end(j));
