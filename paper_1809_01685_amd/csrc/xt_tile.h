@@ -9,12 +9,12 @@
 
 namespace tnslq {
 
-// a tile: up to 32 b by 64 a, or 256 entries where d_B is 1 or 2 (the explicit
-// operator's vectors have d_B = 1)
+// a tile: up to 32 b by 64 a, or up to 256 entries where d_B is below 4 (the
+// explicit operator's vectors have d_B = 1); whole units of a
 constexpr int XT_TA = 64, XT_TB = 32;
 __host__ __device__ inline int xt_tb(int64_t dB) { return (int)(dB < XT_TB ? dB : XT_TB); }
 __host__ __device__ inline int xt_ta(int64_t dA, int64_t dB) {
-    const int t = dB < 4 ? 256 / (int)dB : XT_TA;
+    const int t = dB < 4 ? 256 / (int)dB / 8 * 8 : XT_TA;
     return (int)(dA < t ? dA : t);
 }
 __host__ __device__ inline int64_t xt_tiles(int64_t dA, int64_t dB) {
