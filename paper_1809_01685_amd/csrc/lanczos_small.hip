@@ -12,7 +12,9 @@
 // with four SIMDs: 1.7 us at n = 64 and 6.8 us at 128, where the general step's
 // five launches (and their gaps) are level with it; beyond, more CUs are worth
 // more than fewer launches.  Products and sums are those of the general
-// kernels, in their order, so that the results are the same bit for bit.
+// kernels, in their order, so that the results are the same bit for bit up to 64
+// probes or n = 32; more probes on a larger n take three real products per complex
+// one there (gemm_mfma.hip) and four here.
 // n = 64, 16 probes, 20 steps: 400 us in 80 launches to 82 us in one.
 #include "breakdown.h"
 #include "gemm_tiles.h"
@@ -192,8 +194,9 @@ __global__ void __launch_bounds__(64 * SM_PROBES) k_small_steps(SmallSteps g) {
 // waves per probe: passA, passB or the reorthogonalisation, and passC.  As
 // three to five kernels, launches and the latencies of small blocks were most
 // of it.  A lane holds one element of its wave's unit: 64 elements of a 256-thread
-// block of the general passes, at most 16 units, which is n <= 640 and the powers
-// of two up to 1024 (two units per wave lost: 14 KB of code that runs once, 33 us
+// block of the general passes, at most 16 units (blocks times waves per block; the
+// blocks depend on n and on the number of probes: up to 256 probes n <= 768, 896 and
+// 1024, at 512 every n up to 1024; two units per wave lost: 14 KB of code that runs once, 33 us
 // where the general kernels take 31 at n = 864).  w goes through LDS for the dot
 // products, (vector, chunk) pairs of the general kernels dealt to the waves.
 // Sums keep the general kernels' order and roundings: the results are the same
