@@ -77,8 +77,21 @@ enum { TNSLQ_C64 = 0, TNSLQ_C128 = 1 };
  * the contractions are bound by HBM, not by arithmetic, and run instead as two
  * streaming passes over psi in its own dtype with FP64 products and sums,
  * whatever the precision (tnslq_result.streamed).
- *   FP64    complex FP64 products and sums.
- *   FP32    complex FP32 products, FP32 sums in blocks, blocks summed in FP64.
+ *   FP64    complex FP64 products, as three real products of FP64 matrix
+ *           instructions (T1 = Re Re, T2 = Im Im, T3 = (Re + Im)(Re + Im)) with
+ *           T1 and T3 restarted every 16 terms, or as four (few columns or few
+ *           terms, and where T3 or a sum Re + Im would overflow).  The rounding
+ *           is no larger than that of four products, and of real operands the
+ *           imaginary parts are exactly zero.
+ *   FP32    FP32 operands, each the exact sum of three BF16 values; the six
+ *           largest of their nine products (the rest is below 2^-24 of a
+ *           product) on BF16 matrix cores, three real products per complex one
+ *           with Re + Im rounded to FP32 (four where there are up to 64
+ *           columns).  FP32 sums in blocks of 128 or 256 terms, blocks added in
+ *           FP32 (up to 64 columns: FP64), splits of a long sum in FP64.
+ *           Operands all below 2^-95, where the BF16 values no longer add up to
+ *           them, and results that overflow that way, are worked out with FP32
+ *           matrix instructions instead: FP32's range is that of the products.
  *   BF16X3  each FP32 operand split as hi + lo (two BF16 values); products
  *           hi*hi + hi*lo + lo*hi on BF16 matrix cores with FP32 accumulation,
  *           three real products per complex product (the operands also carry
@@ -221,8 +234,13 @@ typedef struct {
     int swapped_ab;         /* 1 if the roles of A and B were exchanged so that
                                the transposed side is the smaller one          */
     int n_matvecs;          /* block matvecs performed                          */
-    int n_contract_launches;/* launches of each contraction kernel             */
-    double t_layout_ms;     /* psi regrouping + operand preparation (device)   */
+    int n_contract_launches;/* times each contraction was applied (a chunk of
+                               probes at a time; the steps of a small explicit
+                               operator are one launch and count one each)     */
+    /* Device times, by a clock that kernels read as they start: a phase runs
+     * from the start of its first kernel to the start of the next phase's. */
+    double t_layout_ms;     /* psi regrouping + operand preparation, with the
+                               wait for the check of psi                       */
     double t_matvec_ms;     /* both contractions + split-K merge (device)      */
     double t_contract1_ms;  /* first contraction (over a'), all launches       */
     double t_contract2_ms;  /* second contraction (over b', c), all launches   */
@@ -427,7 +445,8 @@ int tnslq_mps_effective_state(const tnslq_mps *mps, int a0, int n_a, int b0, int
  * probes with max_probes).
  *   opt->precision TNSLQ_FP64 (complex products in FP64) or TNSLQ_FP32
  *   (complex64 factors and intermediates on the FP32 matrix instructions;
- *   the Lanczos recurrence stays FP64), and
+ *   the Lanczos recurrence stays FP64), the matvec's products over 64 terms or
+ *   more as three real products each, T1 and T3 restarted every 16 terms, and
  *   opt->operator_form TNSLQ_OPERATOR_AUTO; res->streamed and
  *   res->explicit_operator are 0.  Probes are processed in chunks whose
  *   intermediates fit 8 GiB.  Errors as tnslq_logneg, plus those of

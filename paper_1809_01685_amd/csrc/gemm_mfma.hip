@@ -12,7 +12,7 @@
 //   FP64    v_mfma_f64_16x16x4_f64 (k_cgemm_fp64, 128 x 64 output tiles).
 //
 // A complex product takes three real ones (Gauss's form) but in BF16X6, which
-// uses four:
+// uses four, and in the FP32 and FP64 tiles that three do not reach (gemm_tiles.h):
 //   Re C += Re A Re B + (-Im A) Im B,   Im C += Re A Im B + Im A Re B,
 // the sign of Im A applied by flipping sign bits in registers.
 //
@@ -319,7 +319,7 @@ hipError_t launch_fp64(const GemmDesc &g, hipStream_t st) {
 // 64 x 32; 48 matrix instructions per wave and step for 18 fragment reads.  Two
 // LDS buffers (96 KiB), one barrier per step: the step after next is loaded, the
 // next one split and written, then the current one's matrix instructions run.
-// 26 qubits (65536 x 8192 outputs over 1024 terms): 34.0 to 21.5 ms, 130 to 205
+// 26 qubits (65536 x 8192 outputs over 1024 terms): 34.0 to 22.2 ms, 130 to 198
 // TFLOP/s.  Bound by the split and the loads ahead of each step's matrix
 // instructions: interleaving them needs registers (it spilled 220), and giving
 // the two waves of a SIMD alternate phases took 23.7 ms.
@@ -547,7 +547,7 @@ hipError_t launch_fp32(const GemmDesc &g, hipStream_t st) {
 // of LDS; the kernel stages instead one pair of planes of each operand per
 // "phase" (32 KiB), and the phases of a block's run of bricks are consecutive
 // 16 KiB pieces of its rows of A and of B.  Same block, waves and tiles as
-// k_cgemm_nt_mfma (128 x 128 outputs, 8 waves of 64 x 32); per phase a wave
+// k_cgemm_fp32 (128 x 128 outputs, 8 waves of 64 x 32); per phase a wave
 // issues 24 matrix instructions into the accumulators of that phase's product.
 // Pipeline over a ring of four LDS buffers (128 KiB): in phase ph the matrix
 // instructions run on phase ph's fragments while, issued between them, a wave
@@ -791,14 +791,14 @@ __global__ void __launch_bounds__(NT, 1) k_cgemm_bf16x3(GemmDesc g) {
             __builtin_amdgcn_s_barrier();
             __builtin_amdgcn_sched_barrier(0);
         }
-    f32x4 accr[TM][TN], acci[TM][TN];
+        f32x4 accr[TM][TN], acci[TM][TN];
 #pragma unroll
-    for (int a = 0; a < TM; ++a)
+        for (int a = 0; a < TM; ++a)
 #pragma unroll
-        for (int b = 0; b < TN; ++b) {
-            accr[a][b] = t[0][a][b] - t[1][a][b];
-            acci[a][b] = t[2][a][b] - t[0][a][b] - t[1][a][b];
-        }
+            for (int b = 0; b < TN; ++b) {
+                accr[a][b] = t[0][a][b] - t[1][a][b];
+                acci[a][b] = t[2][a][b] - t[0][a][b] - t[1][a][b];
+            }
         // the addresses of the stores are worked out here, not kept in registers
         // through the next tile
         int elane = lane;

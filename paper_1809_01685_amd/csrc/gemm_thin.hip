@@ -8,7 +8,7 @@
 // bricks ahead made no difference).  B's bricks (N rows) stay in the caches: the
 // 8 waves of a block of 128 rows and one split read the same ones.  The
 // reduction is split in S runs that need not be equal, so that any S gives the
-// chip enough waves.  n = 4096, 32 columns, FP32: 159 to 34 us (the operator's
+// chip enough waves.  n = 4096, 32 columns, FP32: 159 to 35 us (the operator's
 // 128 MB once are 27); n = 864, 8 columns, FP64: 104 to 7 us; n = 64, 16 columns,
 // FP64: 34 to 4 us.
 #include "gemm_tiles.h"
@@ -68,7 +68,7 @@ __global__ void __launch_bounds__(64 * THIN_WAVES) k_thin_product(GemmDesc g) {
 // pieces, split from the fragments in registers, and a product of two values the
 // six products of pieces (p, q) with p + q < 3.  The FP32 unit took 29 us of n =
 // 4096's 42 for 32 columns; 24 BF16 instructions per 32 terms are a third less
-// and leave the split to the vector units: 34 us, and 20 steps of 64 columns 2.50
+// and leave the split to the vector units: 35 us, and 20 steps of 64 columns 2.50
 // to 2.08 ms.  A step is two bricks: lane (l % 16, l / 16) holds unit l / 16 of
 // both as the 8 terms of its BF16 fragment, of A and of B alike.  The products of
 // leading pieces and the small ones have accumulators of their own; both restart

@@ -90,7 +90,7 @@ __device__ inline void load8(const float *__restrict__ row, int64_t step, int l,
 // waves of a row in a fixed order.  As kernels of their own the three column
 // sums walked the batch in one thread per column, 34 us each, two thirds of a
 // 256-row gradient; with the sums here and the independent products of a
-// layer in one launch it takes 46 us instead of 157, in 7 launches, each
+// layer in one launch it takes 34 us instead of 157, in 7 launches, each
 // bound by its latency.
 template <bool BSPLIT, bool STD>
 __device__ __forceinline__ void mm_tile(const MM &p, const float *__restrict__ norm, float *__restrict__ xh,

@@ -1,7 +1,8 @@
 // Operand formats of the two contractions and the contraction launcher
 // interface: precisions and their BF16 splits, plane stores, the brick layout
 // of an operand, and the GEMM descriptor.  Everything the contraction kernels
-// are compiled from, apart from their own source file, is here.
+// are compiled from, apart from their own source file and their tiles
+// (gemm_tiles.h), is here.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -248,13 +249,18 @@ struct GemmDesc {
 };
 
 // Whether an M x N product over nst bricks in S splits runs in 16-row tiles
-// against up to 64 columns (k_thin_fp32, k_thin_product) instead of 128-row tiles: FP32 and
-// FP64 up to 64 columns, where a 128-column tile is at least half padding (at
-// 65 to 128 columns the large tile's reuse of A through LDS is worth the
-// padding), and FP64 over at most four bricks (32 terms), where four real
-// products round less than three (10 qubits: 3.73e-16 of the result against
-// 4.18e-16) and the matrix cores are not the bound.  Its splits need not
-// divide the bricks.
+// against up to 64 columns (k_thin_fp32, k_thin_product) instead of 128-row tiles:
+//   FP32 up to 64 columns, where a 128-column tile is at least half padding (at
+//     65 to 128 columns the large tile's reuse of A through LDS is worth the
+//     padding);
+//   FP64 up to 64 columns, a column tile of k_cgemm_fp64, which issues three
+//     products to the four here but needs more rows to fill the chip: at 64
+//     columns n = 864 takes 19 us a product here and 48 there, 2048 44 and 46,
+//     4096 154 and 142, a 22-qubit block matvec 204 and 197;
+//   FP64 over at most four bricks (32 terms), where four real products round less
+//     than three (10 qubits: 3.73e-16 of the result against 4.18e-16) and the
+//     matrix cores are not the bound.
+// Its splits need not divide the bricks.
 __host__ inline bool thin_product(int prec, int64_t M, int64_t N, int S, int64_t nst) {
     if ((prec != TNSLQ_FP32 && prec != TNSLQ_FP64) || S < 1 || (M + 127) / 128 * 2 * S > 0xffffff) return false;
     return N <= 64 || (prec == TNSLQ_FP64 && nst <= 4 * (int64_t)S && (N + 63) / 64 <= 65535);
