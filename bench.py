@@ -205,7 +205,7 @@ def run_forms(args, w, psi, L, a, b, m, ws):
                                    seed=args.seed, stop_tol=args.stop_tol, workspace=ws, stop_rule=rule)
         else:
             r = T.tnslq_logneg(psi, L, a, b, w["n_probes"], m, reorth=w["reorth"], precision=prec, seed=args.seed,
-                               stop_tol=args.stop_tol, workspace=None if prec in ("fp64", "fp32", "bf16x6") else ws,
+                               stop_tol=args.stop_tol, workspace=ws if prec == w["precision"] else None,
                                stop_rule=rule)
         torch.cuda.synchronize()
         dt = time.perf_counter() - t0
