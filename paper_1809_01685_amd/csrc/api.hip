@@ -1157,12 +1157,18 @@ void bind(Ctx &c, void *ws, hipStream_t st) {
     c.z = pl.expl ? LzDims{pl.dAB, 1, pl.dAB, pl.K, pl.m, pl.nblk} : LzDims{pl.dA, pl.dB, pl.dAB, pl.K, pl.m, pl.nblk};
 }
 
-// Regroup psi into both contraction layouts, and zero the padding of Xt and
-// Ups along their reduction index (written nowhere else; padded rows need no
-// clearing, their products land outside C).
 // rho_AB = P P^dagger (Sec. V: the partial trace over E) as a dense n x n
 // product in the accumulator type, from P[(a, b)][c] = psi regrouped as
 // (A, B, E) and its conjugate, both as brick operands of precision `prec`.
+// Sums: the diagonal's terms are all positive, and their long FP32 sums on the
+// BF16 matrix cores lean to one side: restarted every 256 terms they put the trace
+// of a random complex state's rho off by 2.2e-8 of it (d_E 256 to 4096) and a
+// positive one's by -3e-8.  Restarted every 64 terms they are off by -2e-9 and
+// -9e-9 (the FP32 unit's: up to 7e-9 and 1.6e-8, either way), and a 20-qubit
+// estimate by 1.9e-10 rms where it was 1.05e-9 and the FP32 unit's 6.4e-10, for
+// 90 us of 4.0 ms.
+constexpr int FORM_CHUNK = 2;   // steps of 32 terms
+
 int form_rho(const Plan &pl, int prec, const void *psi, void *Pabe, void *Pabc, void *Cd, hipStream_t st) {
     const int64_t n = pl.dAB, dE = pl.dE;
     if (pl.mixed) {
@@ -1185,6 +1191,7 @@ int form_rho(const Plan &pl, int prec, const void *psi, void *Pabe, void *Pabc, 
     g.ldc = n;
     g.cbs = 1;
     g.c_split = 0;
+    g.chunk = FORM_CHUNK;
     TNSLQ_HIP(launch_gemm(prec, g, st));
     return TNSLQ_OK;
 }
@@ -1274,6 +1281,9 @@ int net_layout(Ctx &c, const void *psi) {
     return mps_check(*c.mp, mws, c.st);
 }
 
+// Regroup psi into both contraction layouts, and zero the padding of Xt and
+// Ups along their reduction index (written nowhere else; padded rows need no
+// clearing, their products land outside C).
 int do_layout(Ctx &c, const void *psi) {
     const Plan &pl = c.pl;
     if (pl.mpsf && pl.mnet) return net_layout(c, psi);

@@ -339,7 +339,7 @@ __global__ void __launch_bounds__(NT, 1) k_cgemm_fp32(GemmDesc g) {
     const size_t blk = brick_block_bytes(TNSLQ_FP32, g.nst);
     const char *gA = (const char *)g.A + (size_t)(tl.i0 / BM) * blk + 16 * tid;
     const char *gB = (const char *)g.B + (size_t)(tl.j0 / BN) * blk + 16 * tid;
-    const int nsteps = (int)((tl.send - tl.sbeg + 1) / 2);
+    const int nsteps = (int)((tl.send - tl.sbeg + 1) / 2), chunk = g.chunk ? g.chunk : FP32_CHUNK;
     // thread t holds unit t % 4 of row t / 4 of a brick plane: four terms, 8
     // bytes of a BF16 row, in its first half (first brick) or second
     const int srow = tid >> 2, su = (tid & 3) ^ brick_swizzle(srow);
@@ -350,12 +350,12 @@ __global__ void __launch_bounds__(NT, 1) k_cgemm_fp32(GemmDesc g) {
         int c0, q, s;
     };
     auto advance = [&](Cursor &c) __attribute__((always_inline)) {
-        const int len = min(FP32_CHUNK, nsteps - c.c0);
+        const int len = min(chunk, nsteps - c.c0);
         if (++c.s == len) {
             c.s = 0;
             if (++c.q == 3) {
                 c.q = 0;
-                c.c0 += FP32_CHUNK;
+                c.c0 += chunk;
             }
         }
     };
