@@ -305,14 +305,14 @@ hipError_t launch_fp64(const GemmDesc &g, hipStream_t st) {
 // packed conversion, its widening and a subtraction per pair and piece) and
 // written to LDS as three BF16 planes, so that memory and L2 see 8 bytes per
 // value and not 18.
-// Sums: each of T1, T2, T3 is accumulated over FP32_CHUNK steps (256 terms) in
-// matrix-core accumulators that start from zero, the products of leading
-// pieces apart from the five small ones (an addition rounds at the size of the
-// sum, so adding those five to it rounds six times as often: 5.2e-7 instead of
-// 2.0e-7 at 22 qubits), then added into Re C and Im C; T1, T2 and T3 take
-// turns on one set of accumulators.  Error of a block matvec against 64 bits:
-// 1.1e-7 to 2.2e-7 of the result from 10 to 24 qubits, where the FP32 unit with
-// sums restarted every 64 terms had 2.0e-7 to 3.3e-7.
+// Sums: each of T1, T2, T3 is accumulated over FP32_CHUNK steps (256 terms, or
+// what GemmDesc::chunk says) in matrix-core accumulators that start from zero,
+// the products of leading pieces apart from the five small ones (an addition
+// rounds at the size of the sum, so adding those five to it rounds six times as
+// often: 5.2e-7 instead of 2.0e-7 at 22 qubits), then added into Re C and Im C;
+// T1, T2 and T3 take turns on one set of accumulators.  Error of a block matvec
+// against 64 bits: 1.1e-7 to 2.2e-7 of the result from 10 to 24 qubits, where the
+// FP32 unit with sums restarted every 64 terms had 2.0e-7 to 3.3e-7.
 // Values that the pieces do not reach, and sums that overflow, go to the FP32
 // unit (gemm_tiles.h): 1% of the time at 26 qubits, 2% at 22, for the test.
 // Block, waves and tiles as k_cgemm_bf16x3: 128 x 128 outputs, 8 waves of
