@@ -74,8 +74,9 @@ __global__ void __launch_bounds__(64 * THIN_WAVES) k_thin_product(GemmDesc g) {
 // leading pieces and the small ones have accumulators of their own; both restart
 // every 128 terms and are added in FP64: a block matvec is off by 0.8e-7 to
 // 1.3e-7 of its result, where the FP32 unit with sums restarted every 64 terms
-// had 2.0e-7 to 2.9e-7.  Values that the pieces do not reach, and results that are
-// not finite, go to that unit (gemm_tiles.h).
+// had 2.0e-7 to 2.9e-7.  GemmDesc::chunk restarts them sooner; two products add to
+// each here, so its terms are half as many steps.  Values that the pieces do not
+// reach, and results that are not finite, go to that unit (gemm_tiles.h).
 constexpr int THIN_FLUSH = 4;   // steps of 32 terms per restart
 
 template <int NTC>
@@ -151,7 +152,8 @@ __global__ void __launch_bounds__(64 * THIN_WAVES, 5 - NTC) k_thin_fp32(GemmDesc
 #pragma unroll
     for (int c = 0; c < NTC; ++c) bitsB[c] = 0;
     if (sbeg < send) load(sbeg, fa, fb);
-    int cnt = 0;
+    const int every = g.chunk ? (g.chunk + 1) / 2 : THIN_FLUSH;
+    int left = every;   // (counted up, two column tiles spilled 40 registers: 20 qubits 4.6 ms for 4.07)
     for (int64_t st = sbeg; st < send; st += 2) {
         if (st + 1 >= send) {
 #pragma unroll
@@ -189,9 +191,9 @@ __global__ void __launch_bounds__(64 * THIN_WAVES, 5 - NTC) k_thin_fp32(GemmDesc
 #pragma unroll
             for (int c = 0; c < NTC; ++c) mac(ha[1][p], hb[c][0][q], acc[1][z][c]);
         }
-        if (++cnt == THIN_FLUSH) {
+        if (--left == 0) {
             flush();
-            cnt = 0;
+            left = every;
         }
     }
     flush();

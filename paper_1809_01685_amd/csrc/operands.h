@@ -246,7 +246,7 @@ struct GemmDesc {
     int64_t crs, c_nst;
     int64_t ldc, cbs, c_split;
     uint64_t *start;   // where the kernel stamps its start, or null
-    int chunk;         // k_cgemm_fp32: steps of 32 terms per restarted sum, 0 for its own choice
+    int chunk;         // FP32: steps of 32 terms per restarted sum, 0 for the kernel's own choice
 };
 
 // Whether an M x N product over nst bricks in S splits runs in 16-row tiles
